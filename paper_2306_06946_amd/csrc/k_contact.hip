@@ -399,92 +399,92 @@ __device__ inline double frsqrt1(double x) {
   return fma(0.5 * y, fma(-x * y, y, 1.0), y);
 }
 
-// Per-contact record of the active-set PGS, computed once per active set from
-// the symmetric 3x3 block w of h^2 W_aa and mu (kappa = (w11 + w22) / 2):
-//   0-5  w00 w01 w02 w11 w12 w22      6-11 the same entries of -w^-1
-//   12   mu (w11 - kappa)   13 mu (w22 - kappa)   14 mu w12
-//   15   mu w01             16 mu w02             17 mu
-//   18   1 if w00 > mu |(w01, w02)| with margin (then den(u) > 0 on the unit
-//        circle and the slip pass needs no fallback), else 0
+// Per-contact record of the Gauss-Seidel chains, computed once per active set
+// from the symmetric 3x3 block w of h^2 W_aa and mu.  Everything the slip
+// passes use is divided by w00, so that a pass needs no product with it:
+//   i..    the entries of -w^-1 (the stick trial is -w^-1 d)
+//   it00   1 / w00, negated when w00 <= mu |(w01, w02)| (with margin): only
+//          with the margin is den(u) > 0 on the whole unit circle, and only
+//          then does the slip pass need no fallback
+//   wh0/1  w01 / w00, w02 / w00
+//   a2/b2  2 mu wh0, 2 mu wh1
+//   m11    2 mu (w11 - kappa) / w00 = -2 mu (w22 - kappa) / w00, kappa = (w11 + w22) / 2
+//   m12    2 mu w12 / w00
 // FAST (a record built inside a Gauss-Seidel visit, on its dependent chain):
-// the refined reciprocal for 1 / det and the margin test compared squared.
-constexpr int PGS_RW = kPgsRecWidth;   // record width: 19 entries, then the contact's current force (chain)
+// refined reciprocals and the margin test compared squared.
+constexpr int PGS_RW = kPgsRecWidth;   // rows of a stored record: these 14, then up to 6 of the caller's
+struct PgsRec {
+  double i00, i01, i02, i11, i12, i22, mu, it00, wh0, wh1, a2, b2, m11, m12;
+};
+constexpr int PGS_RC = 14;
+static_assert(sizeof(PgsRec) == PGS_RC * sizeof(double) && PGS_RW == PGS_RC + 6, "record rows");
 template <bool FAST = false>
-__device__ inline void make_record(const double w[3][3], double mu, double *rec) {
+__device__ __forceinline__ PgsRec make_record(const double w[3][3], double mu) {
+  PgsRec r;
   const double w00 = w[0][0], w01 = w[0][1], w02 = w[0][2], w11 = w[1][1], w12 = w[1][2], w22 = w[2][2];
   const double c00 = w11 * w22 - w12 * w12, c01 = w02 * w12 - w01 * w22, c02 = w01 * w12 - w02 * w11;
   const double c11 = w00 * w22 - w02 * w02, c12 = w01 * w02 - w00 * w12, c22 = w00 * w11 - w01 * w01;
   const double det = w00 * c00 + w01 * c01 + w02 * c02;
   const double idet = FAST ? frcp(det) : 1.0 / det;
-  const double kap = 0.5 * (w11 + w22);
-  rec[0] = w00;
-  rec[1] = w01;
-  rec[2] = w02;
-  rec[3] = w11;
-  rec[4] = w12;
-  rec[5] = w22;
-  rec[6] = -(c00 * idet);
-  rec[7] = -(c01 * idet);
-  rec[8] = -(c02 * idet);
-  rec[9] = -(c11 * idet);
-  rec[10] = -(c12 * idet);
-  rec[11] = -(c22 * idet);
-  rec[12] = mu * (w11 - kap);
-  rec[13] = mu * (w22 - kap);
-  rec[14] = mu * w12;
-  rec[15] = mu * w01;
-  rec[16] = mu * w02;
-  rec[17] = mu;
+  const double i00 = FAST ? frcp(w00) : 1.0 / w00;
+  r.i00 = -(c00 * idet);
+  r.i01 = -(c01 * idet);
+  r.i02 = -(c02 * idet);
+  r.i11 = -(c11 * idet);
+  r.i12 = -(c12 * idet);
+  r.i22 = -(c22 * idet);
+  r.mu = mu;
+  bool safe;
   if (FAST) {
     const double mm = 1.000001 * mu;   // w00 > mm |(w01, w02)| squared, w00 > 0
-    rec[18] = (w00 > 0.0 && w00 * w00 > (mm * mm) * (w01 * w01 + w02 * w02)) ? 1.0 : 0.0;
+    safe = w00 > 0.0 && w00 * w00 > (mm * mm) * (w01 * w01 + w02 * w02);
   } else {
-    rec[18] = (w00 > 1.000001 * mu * sqrt(w01 * w01 + w02 * w02)) ? 1.0 : 0.0;
+    safe = w00 > 1.000001 * mu * sqrt(w01 * w01 + w02 * w02);
   }
+  r.it00 = safe ? i00 : -fabs(i00);
+  r.wh0 = w01 * i00;
+  r.wh1 = w02 * i00;
+  const double m2 = 2.0 * mu;
+  r.a2 = m2 * r.wh0;
+  r.b2 = m2 * r.wh1;
+  r.m11 = m2 * (0.5 * (w11 - w22)) * i00;
+  r.m12 = m2 * w12 * i00;
+  return r;
 }
 
-// Guarded slip pass (rare: the record's den > 0 guarantee fails, or |v| = 0
-// occurred): den <= 0 replaced by w_nn as in the direct form, |v| = 0 keeps
-// the direction; restarts from the same initial direction.  Out of line, so
-// the chains' straight-line code keeps its registers.
+// Guarded slip pass (rare: the record's den > 0 guarantee fails, |v| = 0
+// occurred, or the unnormalised iterate left the safe range): den <= 0
+// replaced by w_nn as in the direct form, |v| = 0 keeps the direction;
+// restarts from the initial direction and normalises every pass.  Out of
+// line, so the chains' straight-line code keeps its registers.
 struct SlipIn {
-  double w00, w01, w02, mm11, mm22, mw12, mw01, mw02;   // record entries
-  double d0, d1, d2, lt1, lt2, nt2;                     // gap, stick trial
-  double n0, n1, n00, n01, n10, n11;                    // -v(u) = n + N u
+  double wh0, wh1, a2, b2, m11, m12;    // record entries
+  double d0, d1, d2, lt1, lt2, nt2;     // gap, stick trial
 };
-__device__ __noinline__ double2 guarded_slip(const SlipIn a, int j_inner) {
-  const double w00 = a.w00, w01 = a.w01, w02 = a.w02, mm11 = a.mm11, mm22 = a.mm22, mw12 = a.mw12, mw01 = a.mw01,
-               mw02 = a.mw02;
-  const double d[3] = {a.d0, a.d1, a.d2};
-  const double lt1 = a.lt1, lt2 = a.lt2, nt2 = a.nt2;
-  const double n0 = a.n0, n1 = a.n1, n00 = a.n00, n01 = a.n01, n10 = a.n10, n11 = a.n11;
+__device__ __forceinline__ double2 guarded_slip(const SlipIn a, int j_inner) {
   double u0, u1;
-  if (nt2 > 0.0) {
-    const double inv = frsqrt(nt2);
-    u0 = lt1 * inv;
-    u1 = lt2 * inv;
+  if (a.nt2 > 0.0) {
+    const double inv = frsqrt(a.nt2);
+    u0 = a.lt1 * inv;
+    u1 = a.lt2 * inv;
   } else {
-    const double nd2 = d[1] * d[1] + d[2] * d[2];
+    const double nd2 = a.d1 * a.d1 + a.d2 * a.d2;
     if (nd2 > 0.0) {
       const double inv = frsqrt(nd2);
-      u0 = -d[1] * inv;
-      u1 = -d[2] * inv;
+      u0 = -a.d1 * inv;
+      u1 = -a.d2 * inv;
     } else {
       u0 = 1.0;
       u1 = 0.0;
     }
   }
+  const double al = 0.5 * a.a2, be = 0.5 * a.b2, m11 = 0.5 * a.m11, m12 = 0.5 * a.m12;
   for (int it = 0; it < j_inner; ++it) {
-    const double den = fma(mw01, u0, fma(mw02, u1, w00));
-    double v0, v1;
-    if (den > 0.0) {
-      v0 = fma(n00, u0, fma(n01, u1, n0));
-      v1 = fma(n10, u0, fma(n11, u1, n1));
-    } else {
-      const double e1 = fma(mm11, u0, fma(mw12, u1, w01)), e2 = fma(mw12, u0, fma(mm22, u1, w02));
-      v0 = fma(d[0], e1, -w00 * d[1]);
-      v1 = fma(d[0], e2, -w00 * d[2]);
-    }
+    // -r(u) up to a positive factor: d_n e(u) - den(u) d_t over w00
+    double den = fma(al, u0, fma(be, u1, 1.0));
+    if (!(den > 0.0)) den = 1.0;
+    const double e1 = fma(m11, u0, fma(m12, u1, a.wh0)), e2 = fma(m12, u0, fma(-m11, u1, a.wh1));
+    const double v0 = fma(a.d0, e1, -den * a.d1), v1 = fma(a.d0, e2, -den * a.d2);
     const double s2 = v0 * v0 + v1 * v1;
     if (s2 > 0.0) {
       const double inv = frsqrt(s2);
@@ -495,90 +495,139 @@ __device__ __noinline__ double2 guarded_slip(const SlipIn a, int j_inner) {
   return make_double2(u0, u1);
 }
 
-// Same branches and fixed point as local_solve, from the record: stick trial
-// by the precomputed inverse, refined reciprocals instead of divisions, and
-// the slip pass on the direction u alone.  With den(u) > 0 the tangential
-// residual r = d_t + lam_n(u) e(u), lam_n = -d_n / den(u),
-// e(u) = w_tn + mu (W_tt - kappa I) u, is parallel to
-//   v(u) = den(u) d_t - d_n e(u) = c + G u,
-// an affine map of u, so a pass is u <- -v / |v| (same iterates up to
-// rounding).  Every VALU instruction of the single issuing wave costs the
-// same whatever its dependences, so the pass is kept to 14 of them.
-// J = 8: the default pass count, straight-line; J = 0: j_inner passes in a loop.
+// The local solve of one Gauss-Seidel visit, run by a whole wave: every lane
+// works on its own record and gap, and the branches follow the lane li whose
+// contact is visited, so control flow is uniform and the other lanes' values
+// are unused.  Same branches and fixed point as local_solve, from the record:
+// stick trial by the precomputed inverse, refined reciprocals instead of
+// divisions, and the slip pass on the direction alone.  With den(u) =
+// 1 + al u0 + be u1 > 0 (over w00; al = a2 / 2, be = b2 / 2) the tangential
+// residual r = d_t + lam_n(u) e(u), lam_n = -d_n / (w00 den(u)),
+// e(u) = w_tn + mu (W_tt - kappa I) u, gives the direction
+//   -r / |r| = v / |v|,   v(u) = n + N u,
+//   n = d_n w_tn / w00 - d_t,   N = d_n mu (W_tt - kappa I) / w00 - d_t (al, be).
+// A pass is u <- v(u) / |v(u)|.  The iterate is kept unnormalised: with
+// u = v / r, r = |v|, the next one is taken as v' = n (2 r) + (2 N) v, which
+// has the same direction (12 instructions and no reciprocal; the normalised
+// form took 13, and 11 more for the start direction: the stick trial's
+// tangential part is a start as it is).  The magnitude is multiplied by
+// 2 |n + N u| in each pass; when it has left 1e-125 .. 1e125 after the last
+// one, the guarded pass runs instead.  What bounds a visit is one wave's issue
+// rate: whatever its dependences, an instruction of 4 bytes takes 5 cycles
+// and one of 8 bytes 6, an rsq or rcp 17, a taken branch 22, a scalar
+// instruction that reads a comparison's mask at once 16 more (measured, one
+// wave on its SIMD).  So every form here is chosen for its instruction count
+// and size; a pass takes 68 cycles.
+// J = 8: the default pass count, straight-line; J = 0: j_inner passes in a
+// loop, normalised (their number is not bounded).
+// `bit` selects the visited lane in the masks.
+__device__ __forceinline__ bool lane_in(unsigned long long mask, unsigned long long bit) { return (mask & bit) != 0; }
+struct Trial {
+  double ln, lt1, lt2, nt2;
+  double p, q;                // d_n m11, d_n m12 of the slip passes
+  unsigned long long stick;   // lanes whose trial lies inside the cone
+};
+__device__ __forceinline__ Trial stick_trial(const PgsRec &rc, double d0, double d1, double d2) {
+  Trial t;
+  t.ln = fma(rc.i02, d2, fma(rc.i01, d1, rc.i00 * d0));
+  t.lt1 = fma(rc.i12, d2, fma(rc.i11, d1, rc.i01 * d0));
+  t.lt2 = fma(rc.i22, d2, fma(rc.i12, d1, rc.i02 * d0));
+  t.nt2 = fma(t.lt1, t.lt1, t.lt2 * t.lt2);
+  const double ml = rc.mu * t.ln;
+  const bool in = t.nt2 <= ml * ml, pos = t.ln > 0.0;
+  t.p = d0 * rc.m11;
+  t.q = d0 * rc.m12;
+  // A scalar instruction waits some 16 cycles for a comparison's mask: the
+  // two products, which only the slip passes use, are issued meanwhile.
+  asm("" : "+v"(t.p), "+v"(t.q));
+  t.stick = __ballot(in) & __ballot(pos);
+  return t;
+}
 template <int J>
-__device__ Local local_solve_rec(const double *rc, const double d[3], int j_inner) {
-  Local out;
-  if (d[0] >= 0.0) {
-    out.l[0] = out.l[1] = out.l[2] = 0.0;
-    out.st = ICR_SEPARATE;
-    return out;
-  }
-  const double w00 = rc[0], w01 = rc[1], w02 = rc[2];
-  const double mm11 = rc[12], mm22 = rc[13], mw12 = rc[14], mw01 = rc[15], mw02 = rc[16], mu = rc[17];
-  // the record holds -w^-1: the stick trial lambda = -w^-1 d without a negation
-  const double ln = rc[6] * d[0] + rc[7] * d[1] + rc[8] * d[2];
-  const double lt1 = rc[7] * d[0] + rc[9] * d[1] + rc[10] * d[2];
-  const double lt2 = rc[8] * d[0] + rc[10] * d[1] + rc[11] * d[2];
-  const double nt2 = lt1 * lt1 + lt2 * lt2;
-  if (ln > 0.0 && nt2 <= (mu * ln) * (mu * ln)) {
-    out.l[0] = ln;
-    out.l[1] = lt1;
-    out.l[2] = lt2;
-    out.st = ICR_STICK;
-    return out;
-  }
-  double u0, u1;
-  if (nt2 > 0.0) {
-    const double inv = frsqrt(nt2);
-    u0 = lt1 * inv;
-    u1 = lt2 * inv;
-  } else {
-    const double nd2 = d[1] * d[1] + d[2] * d[2];
-    if (nd2 > 0.0) {
-      const double inv = frsqrt(nd2);
-      u0 = -d[1] * inv;
-      u1 = -d[2] * inv;
-    } else {
-      u0 = 1.0;
-      u1 = 0.0;
-    }
-  }
-  // -v(u) = n + N u
-  const double n0 = fma(d[0], w01, -w00 * d[1]), n1 = fma(d[0], w02, -w00 * d[2]);
-  const double n00 = fma(d[0], mm11, -d[1] * mw01), n01 = fma(d[0], mw12, -d[1] * mw02);
-  const double n10 = fma(d[0], mw12, -d[2] * mw01), n11 = fma(d[0], mm22, -d[2] * mw02);
-  bool safe = rc[18] != 0.0;
-  if (safe) {
-    auto pass = [&]() {
-      const double v0 = fma(n00, u0, fma(n01, u1, n0));
-      const double v1 = fma(n10, u0, fma(n11, u1, n1));
-      const double inv = frsqrt1(fma(v0, v0, v1 * v1));
-      u0 = v0 * inv;
-      u1 = v1 * inv;
-    };
-    if constexpr (J == 8) {   // the default count: straight-line passes, no loop branch
+__device__ __forceinline__ void slip_solve(const PgsRec &rc, const Trial &tr, double d0, double d1, double d2,
+                                           int j_inner, unsigned long long bit, unsigned long long safe,
+                                           double (&l)[3]) {
+  const double t = -d0 * fabs(rc.it00);
+  const double n0 = fma(d0, rc.wh0, -d1), n1 = fma(d0, rc.wh1, -d2);
+  const double p = tr.p, q = tr.q;
+  const double M00 = fma(-d1, rc.a2, p), M01 = fma(-d1, rc.b2, q);   // 2 N
+  const double M10 = fma(-d2, rc.a2, q), M11 = fma(-d2, rc.b2, -p);
+  double v0 = tr.lt1, v1 = tr.lt2, s = tr.nt2;
+  if constexpr (J == 8) {
 #pragma unroll
-      for (int it = 0; it < 8; ++it) pass();
-    } else {
-      for (int it = 0; it < j_inner; ++it) pass();
+    for (int it = 0; it < 8; ++it) {
+      // R = 2 |v|: the estimate s y of |v| refined by one Newton step; two
+      // products cover the wait state that the estimate's first use needs
+      const double y = __builtin_amdgcn_rsq(s);
+      __builtin_amdgcn_sched_barrier(0);
+      const double a0 = M01 * v1, a1 = M11 * v1;
+      __builtin_amdgcn_sched_barrier(0);
+      const double r0 = s * y;
+      const double R = r0 * fma(-r0, y, 3.0);
+      const double x0 = fma(n0, R, fma(M00, v0, a0));
+      const double x1 = fma(n1, R, fma(M10, v0, a1));
+      v0 = x0;
+      v1 = x1;
+      s = fma(v0, v0, v1 * v1);
     }
-    safe = (u0 == u0) && (u1 == u1);   // |v| = 0 (a NaN) takes the guarded pass below
+  } else {
+    const double inv0 = frsqrt(tr.nt2);
+    v0 *= inv0;
+    v1 *= inv0;
+    for (int it = 0; it < j_inner; ++it) {
+      const double x0 = fma(0.5 * M00, v0, fma(0.5 * M01, v1, n0));
+      const double x1 = fma(0.5 * M10, v0, fma(0.5 * M11, v1, n1));
+      const double inv = frsqrt1(fma(x0, x0, x1 * x1));
+      v0 = x0 * inv;
+      v1 = x1 * inv;
+    }
+    s = fma(v0, v0, v1 * v1);
   }
-  if (!safe) {
-    const SlipIn a{w00, w01, w02, mm11, mm22, mw12, mw01, mw02, d[0], d[1], d[2], lt1, lt2, nt2,
-                   n0, n1, n00, n01, n10, n11};
+  // r = |v| and 1 / D by one third-order step each; lam_n = t / den(u),
+  // lam_t = mu lam_n v / r with den(u) = D / (2 r)
+  const double y = __builtin_amdgcn_rsq(s);
+  const double r0 = s * y;
+  const double e = fma(-r0, y, 1.0);
+  const double r = fma(r0, fma(e, 0.375, 0.5) * e, r0);
+  const double rr = r + r;
+  const double D = fma(rc.a2, v0, fma(rc.b2, v1, rr));
+  const double z = __builtin_amdgcn_rcp(D);
+  const double c = fma(-D, z, 1.0);
+  const double g = t * fma(z, fma(c, c, c), z);
+  const double k = (rc.mu + rc.mu) * g;
+  l[0] = g * rr;
+  l[1] = k * v0;
+  l[2] = k * v1;
+  // a zero, a NaN or a magnitude near the ends of the range fails this
+  if (__builtin_expect(!lane_in(safe & __ballot(s > 1e-250) & __ballot(s < 1e250), bit), 0)) {
+    const SlipIn a{rc.wh0, rc.wh1, rc.a2, rc.b2, rc.m11, rc.m12, d0, d1, d2, tr.lt1, tr.lt2, tr.nt2};
     const double2 u = guarded_slip(a, j_inner);
-    u0 = u.x;
-    u1 = u.y;
+    double den = 0.5 * fma(rc.a2, u.x, fma(rc.b2, u.y, 2.0));
+    if (den <= 0.0) den = 1.0;
+    const double lam_n = t * frcp(den);
+    const double mln = rc.mu * lam_n;
+    l[0] = lam_n;
+    l[1] = mln * u.x;
+    l[2] = mln * u.y;
   }
-  double den = fma(mw01, u0, fma(mw02, u1, w00));
-  if (den <= 0.0) den = w00;
-  const double lam_n = -d[0] * frcp(den);
-  const double mln = mu * lam_n;
-  out.l[0] = lam_n;
-  out.l[1] = mln * u0;
-  out.l[2] = mln * u1;
-  out.st = ICR_SLIP;
+}
+// One contact's solve where every lane holds the same values.
+template <int J>
+__device__ __forceinline__ Local local_solve_rec(const PgsRec &rc, const double d[3], int j_inner) {
+  Local out;
+  out.l[0] = out.l[1] = out.l[2] = 0.0;
+  out.st = ICR_SEPARATE;
+  if (lane_in(__ballot(d[0] >= 0.0), 1ull)) return out;
+  const Trial t = stick_trial(rc, d[0], d[1], d[2]);
+  if (lane_in(t.stick, 1ull)) {
+    out.l[0] = t.ln;
+    out.l[1] = t.lt1;
+    out.l[2] = t.lt2;
+    out.st = ICR_STICK;
+  } else {
+    slip_solve<J>(rc, t, d[0], d[1], d[2], j_inner, 1ull, __ballot(rc.it00 > 0.0), out.l);
+    out.st = ICR_SLIP;
+  }
   return out;
 }
 
@@ -943,9 +992,9 @@ __global__ __launch_bounds__(1024) void k_pgs_pc(int nc, const StepCtx *__restri
           double lr[3], dd[3];
           for (int i = 0; i < 3; ++i) lr[i] = F[i][0] * fo[0] + F[i][1] * fo[1] + F[i][2] * fo[2];
           for (int i = 0; i < 3; ++i) dd[i] = delta[i] - (w[i][0] * lr[0] + w[i][1] * lr[1] + w[i][2] * lr[2]);
-          double rec[PGS_RW];
-          make_record(w, mu[next], rec);
-          const Local r = j_inner == 8 ? local_solve_rec<8>(rec, dd, j_inner) : local_solve_rec<0>(rec, dd, j_inner);
+          const PgsRec rec = make_record(w, mu[next]);
+          const Local r =
+              j_inner == 8 ? local_solve_rec<8>(rec, dd, j_inner) : local_solve_rec<0>(rec, dd, j_inner);
           double fn[3], df[3];
           for (int q = 0; q < 3; ++q) {
             fn[q] = F[0][q] * r.l[0] + F[1][q] * r.l[1] + F[2][q] * r.l[2];
@@ -1002,9 +1051,8 @@ __global__ __launch_bounds__(1024) void k_pgs_pc(int nc, const StepCtx *__restri
 // Gauss-Seidel.  The kernel keeps the set S of contacts that may change and
 // runs the sequential sweep over S alone, with the compact coupling block
 // W~_SS (gathered once per set) and per-contact records (3x3 block, its
-// factor, mu) in LDS.  Up to PGS_WAVE_MAX contacts the sweep is one wave's
-// barrier-free chain over register-resident gaps and forces (chain_wave);
-// larger sets use a block-wide chain with two barriers per contact.  It
+// inverse, mu) in LDS.  The sweep is a barrier-free chain over gaps and
+// forces in registers, of one wave for every 64 contacts (chain_sweep).  It
 // then verifies that every contact outside S was a no-op at its turn, i.e.
 // that its normal gap
 //   g_n(c) = g_n^set(c) + W~_{n(c),S} (lambda^turn - lambda^set) >= 0,
@@ -1022,17 +1070,19 @@ constexpr int PGS_NW = PGS_NT / 64;
 constexpr int PGS_WAVE_MAX = kPgsWaveMax;   // largest set swept by the register chains (= PGS_SMAX)
 constexpr int PGS_BLK = kPgsBlk;            // doubles per 3x3 block of the blocked W~_SS (9 used, 16-byte aligned)
 struct PgsLds {
+  // gaps without the own term, current forces (written by the running sweep),
+  // forces at the sweep's start and at the set's
   double gS[PGS_S3], lamS[PGS_S3], lamS0[PGS_S3], lamSet[PGS_S3];
-  double rec[PGS_SMAX * PGS_RW];
+  double rec[PGS_RW * PGS_SMAX];   // row q of contact i at q PGS_SMAX + i (see pgs_rec_load)
   double red[48];
   int Sidx[PGS_SMAX];
   unsigned char stS[PGS_SMAX];
   int wcount[64];
-  int ulist[PGS_MAX_NC];
+  unsigned short ulist[PGS_MAX_NC];
   unsigned char inS[PGS_MAX_NC];
   double Rmin;   // settle threshold of the set: B below it settles every skipped contact
-  int nS, flag, stop, nu, zflag, settled;
-  int cprog, cflag;   // contacts done by the solving chain; block Gauss-Seidel: next block staged
+  int nS, flag, stop, nu, zflag;
+  int cprog, cflag;   // contacts solved by the chain (counted on over the sweeps); block Gauss-Seidel: next block staged
   int perr;           // a wait of the ring sweep ran out
 };
 
@@ -1047,185 +1097,230 @@ __device__ inline double readlane_f64(double v, int lane) {
   return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
 }
 
-// Blocks W~(rows of contacts ln + 64k, columns of contact i) for every slot k
-// (uniform base, fixed per-lane offset).
-template <int NS>
-__device__ inline void chain_load(double2 (&X)[NS][PGS_BLK / 2], const double *__restrict__ Wb, int i, int ln) {
-  const double2 *base = reinterpret_cast<const double2 *>(Wb + (long)i * (64 * NS * PGS_BLK));
-  const int lo = ln * (PGS_BLK / 2);
-#pragma unroll
-  for (int k = 0; k < NS; ++k)
-#pragma unroll
-    for (int j = 0; j < PGS_BLK / 2; ++j) X[k][j] = base[lo + k * 64 * (PGS_BLK / 2) + j];
+// Blocked couplings of a set padded to nsp contacts (a multiple of 64): the
+// 3x3 block (rows of contact c, columns of contact i) of column i lies in the
+// group of 64 rows c / 64, 576 doubles each, entry j (row-major) of lane
+// l = c % 64 at blk_entry(l, j): pairs of entries lane by lane, so that each
+// of a wave's five loads of a column's group is contiguous.  (With the nine
+// doubles of a lane side by side every load touched all 40 cache lines of the
+// group, which cost sets of several waves a third of their time.)
+constexpr int BLK_GROUP = 64 * PGS_BLK;
+__host__ __device__ constexpr inline int blk_entry(int l, int j) {
+  return j < 8 ? 128 * (j / 2) + 2 * l + (j & 1) : 512 + l;
 }
-
-// Record and current force of contact i: 11 broadcast 16-byte LDS reads.
-struct ChainRec {
-  double2 r2[PGS_RW / 2];
-  __device__ double operator[](int q) const { return (q & 1) ? r2[q >> 1].y : r2[q >> 1].x; }
+// entry r of a group, 0 <= r < BLK_GROUP -> lane and block entry
+__device__ inline void blk_index(int r, int &l, int &j) {
+  l = r < 512 ? (r & 127) >> 1 : r - 512;
+  j = r < 512 ? 2 * (r >> 7) + (r & 1) : 8;
+}
+struct BlkCol {
+  double2 x[4];
+  double y;
 };
-__device__ inline void chain_rec(ChainRec &c, const PgsLds &L, int i) {
-  const double2 *rp = reinterpret_cast<const double2 *>(L.rec + PGS_RW * i);
+// A buffer of blocked couplings: column groups are read with the column's
+// byte offset in a scalar register and per-lane constants in vector
+// registers, so a load needs no address arithmetic.  Reads past its end
+// return zero.
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+struct BlkBuf {
+  __amdgpu_buffer_rsrc_t rsrc;
+  __device__ __forceinline__ BlkBuf(const double *p, unsigned bytes)
+      : rsrc(__builtin_amdgcn_make_buffer_rsrc(const_cast<double *>(p), 0, bytes, 0x00027000)) {}
+};
+// off: byte offset of the column's group (uniform)
+__device__ __forceinline__ void blk_load(BlkCol &X, const BlkBuf &b, unsigned off, int ln) {
+  const unsigned o = 16u * (unsigned)ln, o8 = 4096u + 8u * (unsigned)ln;
 #pragma unroll
-  for (int q = 0; q < PGS_RW / 2; ++q) c.r2[q] = rp[q];
+  for (int k = 0; k < 4; ++k)
+    X.x[k] = __builtin_bit_cast(double2, (u32x4)__builtin_amdgcn_raw_buffer_load_b128(b.rsrc, o + 1024u * k, off, 0));
+  X.y = __builtin_bit_cast(double, (u32x2)__builtin_amdgcn_raw_buffer_load_b64(b.rsrc, o8, off, 0));
+}
+// e += block * (d0, d1, d2)
+__device__ __forceinline__ void blk_apply(double (&e)[3], const BlkCol &X, double d0, double d1, double d2) {
+  e[0] = fma(X.x[1].x, d2, fma(X.x[0].y, d1, fma(X.x[0].x, d0, e[0])));
+  e[1] = fma(X.x[2].y, d2, fma(X.x[2].x, d1, fma(X.x[1].y, d0, e[1])));
+  e[2] = fma(X.y, d2, fma(X.x[3].y, d1, fma(X.x[3].x, d0, e[2])));
+}
+// Columns of a group in flight ahead of the one in use.  A stick visit takes
+// 0.17 us, an L2 hit 0.07 us and a miss 0.35 us; two columns were as fast as
+// four on sets that stay in L2, eight no faster.  The loads run past the last
+// column (they return zero), so no visit computes a clamped address.
+constexpr int PGS_AHEAD = kPgsAhead;
+
+// The chain's state of one contact, in one lane's registers.
+struct ChainLane {
+  PgsRec rc;
+  double e[3], l[3];   // gap without the own term, force
+  int st;
+};
+__device__ __forceinline__ PgsRec pgs_rec_load(const PgsLds &L, int c) {
+  PgsRec r;
+  double *x = reinterpret_cast<double *>(&r);
+#pragma unroll
+  for (int q = 0; q < PGS_RC; ++q) x[q] = L.rec[q * PGS_SMAX + c];
+  return r;
 }
 
-// One Gauss-Seidel step of the single-wave chain.  Contact i's gap without
-// its own term, e_i = g_i - W~_ii lambda_i (the input of the local solve),
-// is in lane i % 64, register slot K = i / 64 (compile-time: no register
-// selection); the blocked W~ has zero diagonal blocks, so the update keeps
-// e exact.  Every lane runs the local solve on the same broadcast data;
-// lane 0 stores the new force and status in LDS; every lane applies
-// W~(own rows, i) dlambda_i to its gaps.  Straight-line apart from the local
-// solve and the one-lane store, so loads in flight are waited for only where
-// they are used.
-template <int K, int NS, int J>
-__device__ inline void chain_step(int i, const double2 (&X)[NS][PGS_BLK / 2], const ChainRec &c,
-                                  double (&g)[NS][3], PgsLds &L, int j_inner, int ln, int o) {
-  const int li = i & 63;
-  double rc[19];
-#pragma unroll
-  for (int q = 0; q < 19; ++q) rc[q] = c[q];
-  const double lo0 = c[19], lo1 = c[20], lo2 = c[21];
-  double dd[3];
-  dd[0] = readlane_f64(g[K][0], li);
-  dd[1] = readlane_f64(g[K][1], li);
-  dd[2] = readlane_f64(g[K][2], li);
-  const Local rs = local_solve_rec<J>(rc, dd, j_inner);
-  if (ln == 0) {
-    double *lp = L.rec + PGS_RW * (i + o) + 19;
-    lp[0] = rs.l[0];
-    lp[1] = rs.l[1];
-    lp[2] = rs.l[2];
-    L.stS[i + o] = (unsigned char)rs.st;
-  }
-  const double d0 = rs.l[0] - lo0, d1 = rs.l[1] - lo1, d2 = rs.l[2] - lo2;
-#pragma unroll
-  for (int k = 0; k < NS; ++k) {
-    const double b[9] = {X[k][0].x, X[k][0].y, X[k][1].x, X[k][1].y, X[k][2].x,
-                         X[k][2].y, X[k][3].x, X[k][3].y, X[k][4].x};
-#pragma unroll
-    for (int a = 0; a < 3; ++a) g[k][a] = fma(b[3 * a + 2], d2, fma(b[3 * a + 1], d1, fma(b[3 * a], d0, g[k][a])));
-  }
+// One Gauss-Seidel visit: the contact of lane li, whose own lane holds its
+// record, force and gap without the own term e = g - W~_cc lambda_c (the
+// blocked W~ has zero diagonal blocks, so the update keeps it exact).  The
+// force change is broadcast through scalar registers and every lane applies
+// W~(own rows, contact) to its gap.  Nothing is read from LDS; lane li stores
+// its new force to L.lamS and, with PUB (another wave follows), then the count
+// of solved contacts, which each lane holds in `prog`, to L.cprog (LDS
+// operations of one wave complete in order, so a reader that sees the count
+// sees the force; the compiler fence keeps the stores in that order).  A wave
+// runs every instruction for all lanes and pays for each 4 to 6 cycles, so
+// what counts is their number and size: a visit has two branches, each on one
+// bit of a mask, and lane li's stores and the broadcast share one change of
+// the execution mask (a v_readlane with the lane in a scalar register takes
+// 9.5 cycles, the v_readfirstlane of the only active lane 5.5).  A stick visit
+// takes 410 cycles, a slip visit 1090, a visit that ends at once 130.  With
+// the record read from LDS, the solve repeated on broadcast data and the
+// normalised passes, a visit of half sticking, half slipping contacts took
+// 425 ns in a set of 64 contacts and 621 in one of 512; now 322 and 367.
+// nz: lanes whose contact carried a force at the sweep's start; a contact
+// without one whose gap is not negative stays as it is, and its visit ends at
+// once.  safe: lanes whose record allows the fast slip passes.  slip: lanes
+// that slipped.  open: lanes with a gap that is not negative, taken at the end
+// of the last visit.
+struct ChainMasks {
+  unsigned long long nz, safe, slip, open;
+};
+__device__ __forceinline__ unsigned lds_addr(const void *p) {
+  return (unsigned)(unsigned long long)(__attribute__((address_space(3))) const void *)p;
 }
-
-// Contacts 64K .. 64K+63 of the sweep; blocks of the next two contacts and the
-// record of the next one are in flight while the current one is solved.
-// Loads past the end re-read the last contact (unused).  The set's records,
-// statuses and gaps start at contact o of the LDS arrays.  PUB: after every
-// two contacts lane 0 publishes how many are done in L.cprog (LDS operations
-// of one wave complete in order, so a reader that sees the count sees the
-// forces; the compiler fence keeps the stores in that order).
-template <int K, int NS, int J, bool PUB>
-__device__ inline void chain_slot(int nS, const double *__restrict__ Wb, PgsLds &L, int j_inner, int ln, int o,
-                                  double (&g)[NS][3], double2 (&A)[NS][PGS_BLK / 2], double2 (&B)[NS][PGS_BLK / 2],
-                                  ChainRec &rA, ChainRec &rB) {
-  const int last = nS - 1, end = min(nS, 64 * K + 64);
-  for (int i = 64 * K; i < end; i += 2) {
-    chain_rec(rB, L, min(i + 1, last) + o);
-    chain_step<K, NS, J>(i, A, rA, g, L, j_inner, ln, o);
-    chain_load<NS>(A, Wb, min(i + 2, last), ln);
-    if (i + 1 < end) {
-      chain_rec(rA, L, min(i + 2, last) + o);
-      chain_step<K, NS, J>(i + 1, B, rB, g, L, j_inner, ln, o);
+// l to L.lamS (its byte address in at) and, with PUB, prog to L.cprog (pat), from
+// the lane of `bit`; its change d as uniform values.  All lanes are active.
+template <bool PUB>
+__device__ __forceinline__ void chain_commit(double l0, double l1, double l2, double (&d)[3], unsigned at,
+                                             unsigned pat, int prog, unsigned long long bit) {
+  unsigned s0, s1, s2, s3, s4, s5;
+  const unsigned long long x0 = __builtin_bit_cast(unsigned long long, d[0]),
+                           x1 = __builtin_bit_cast(unsigned long long, d[1]),
+                           x2 = __builtin_bit_cast(unsigned long long, d[2]);
+#define ICR_RFL6                     \
+  "v_readfirstlane_b32 %0, %7\n\t"   \
+  "v_readfirstlane_b32 %1, %8\n\t"   \
+  "v_readfirstlane_b32 %2, %9\n\t"   \
+  "v_readfirstlane_b32 %3, %10\n\t"  \
+  "v_readfirstlane_b32 %4, %11\n\t"  \
+  "v_readfirstlane_b32 %5, %12\n\t"  \
+  "s_mov_b64 exec, -1"
+#define ICR_RFL6_OPS                                                                                          \
+  "=&s"(s0), "=&s"(s1), "=&s"(s2), "=&s"(s3), "=&s"(s4), "=&s"(s5)                                            \
+      : "s"(bit), "v"((unsigned)x0), "v"((unsigned)(x0 >> 32)), "v"((unsigned)x1), "v"((unsigned)(x1 >> 32)), \
+        "v"((unsigned)x2), "v"((unsigned)(x2 >> 32)), "v"(at), "v"(l0), "v"(l1), "v"(l2)
+  if constexpr (PUB)
+    asm volatile(
+        "s_mov_b64 exec, %6\n\t"
+        "ds_write2_b64 %13, %14, %15 offset1:1\n\t"
+        "ds_write_b64 %13, %16 offset:16\n\t"
+        "ds_write_b32 %17, %18\n\t" ICR_RFL6
+        : ICR_RFL6_OPS, "v"(pat), "v"(prog)
+        : "memory");
+  else
+    asm volatile(
+        "s_mov_b64 exec, %6\n\t"
+        "ds_write2_b64 %13, %14, %15 offset1:1\n\t"
+        "ds_write_b64 %13, %16 offset:16\n\t" ICR_RFL6
+        : ICR_RFL6_OPS
+        : "memory");
+#undef ICR_RFL6
+#undef ICR_RFL6_OPS
+  d[0] = __builtin_bit_cast(double, (unsigned long long)s1 << 32 | s0);
+  d[1] = __builtin_bit_cast(double, (unsigned long long)s3 << 32 | s2);
+  d[2] = __builtin_bit_cast(double, (unsigned long long)s5 << 32 | s4);
+}
+// e += X d for uniform d, in place (left to itself, the compiler moves e to new
+// registers and back around the branch of the visit).
+__device__ __forceinline__ void blk_apply_uniform(double (&e)[3], const BlkCol &X, const double (&d)[3]) {
+  asm("v_fmac_f64_e32 %0, %3, %6\n\t"
+      "v_fmac_f64_e32 %1, %3, %9\n\t"
+      "v_fmac_f64_e32 %2, %3, %12\n\t"
+      "v_fmac_f64_e32 %0, %4, %7\n\t"
+      "v_fmac_f64_e32 %1, %4, %10\n\t"
+      "v_fmac_f64_e32 %2, %4, %13\n\t"
+      "v_fmac_f64_e32 %0, %5, %8\n\t"
+      "v_fmac_f64_e32 %1, %5, %11\n\t"
+      "v_fmac_f64_e32 %2, %5, %14"
+      : "+v"(e[0]), "+v"(e[1]), "+v"(e[2])
+      : "s"(d[0]), "s"(d[1]), "s"(d[2]), "v"(X.x[0].x), "v"(X.x[0].y), "v"(X.x[1].x), "v"(X.x[1].y), "v"(X.x[2].x),
+        "v"(X.x[2].y), "v"(X.x[3].x), "v"(X.x[3].y), "v"(X.y));
+}
+template <int J, bool PUB>
+__device__ __forceinline__ void chain_visit(ChainLane &c, const BlkCol &X, int li, unsigned at, unsigned pat, int prog,
+                                            int j_inner, ChainMasks &k) {
+  const unsigned long long bit = 1ull << li;
+  if (lane_in(~k.open | k.nz, bit)) {
+    const Trial t = stick_trial(c.rc, c.e[0], c.e[1], c.e[2]);
+    double l[3] = {t.ln, t.lt1, t.lt2};
+    if (!lane_in(t.stick & ~k.open, bit)) {
+      if (!lane_in(k.open, bit)) {
+        slip_solve<J>(c.rc, t, c.e[0], c.e[1], c.e[2], j_inner, bit, k.safe, l);
+        k.slip |= bit;
+      } else {
+        l[0] = l[1] = l[2] = 0.0;
+      }
     }
-    chain_load<NS>(B, Wb, min(i + 3, last), ln);
-    if constexpr (PUB) {
-      __atomic_signal_fence(__ATOMIC_SEQ_CST);
-      if (ln == 0) __hip_atomic_store(&L.cprog, min(i + 2, end), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    }
+    double d[3] = {l[0] - c.l[0], l[1] - c.l[1], l[2] - c.l[2]};
+    chain_commit<PUB>(l[0], l[1], l[2], d, at, pat, prog, bit);
+    blk_apply_uniform(c.e, X, d);
   }
 }
 
-// Sequential sweep over S by wave 0 alone: gaps of S (without own term) live
-// in the lanes' registers, forces, records and statuses in LDS; no barrier is
-// taken inside the sweep.
-template <int NS, int J, bool PUB = false>
-__device__ __forceinline__ void chain_wave(int nS, const double *__restrict__ Wb, PgsLds &L, int j_inner,
-                                           int o = 0) {
-  const int ln = threadIdx.x & 63;
-  double g[NS][3];
+// The n contacts of this wave's lanes 0 .. n-1 in order (and, up to a
+// multiple of PGS_AHEAD, lanes beyond them, whose gap and force are zero);
+// off: byte offset of their first column's group of this wave's rows, stride
+// between columns.  prog: the count of solved contacts after this lane's.
+template <int J, bool PUB>
+__device__ __forceinline__ void chain_solve(ChainLane &c, int n, const BlkBuf &B, unsigned off, unsigned stride,
+                                            int me, int prog, PgsLds &L, int j_inner, int ln) {
+  ChainMasks k{__ballot((c.l[0] != 0.0) | (c.l[1] != 0.0) | (c.l[2] != 0.0)), __ballot(c.rc.it00 > 0.0), 0ull,
+               __ballot(c.e[0] >= 0.0)};
+  const unsigned at = lds_addr(L.lamS + 3 * me), pat = lds_addr(&L.cprog);
+  BlkCol X[PGS_AHEAD];
 #pragma unroll
-  for (int k = 0; k < NS; ++k) {
-    const int c = ln + 64 * k;
-#pragma unroll
-    for (int q = 0; q < 3; ++q) g[k][q] = c < nS ? L.gS[3 * (c + o) + q] : 0.0;
+  for (int u = 0; u < PGS_AHEAD; ++u) {
+    blk_load(X[u], B, off, ln);
+    off += stride;
+    __builtin_amdgcn_sched_barrier(0);   // in column order: the first use waits for the first column only
   }
-  const int last = nS - 1;
-  double2 A[NS][PGS_BLK / 2], B[NS][PGS_BLK / 2];
-  ChainRec rA, rB;
-  chain_load<NS>(A, Wb, 0, ln);
-  chain_load<NS>(B, Wb, min(1, last), ln);
-  chain_rec(rA, L, o);
-  chain_slot<0, NS, J, PUB>(nS, Wb, L, j_inner, ln, o, g, A, B, rA, rB);
-  if constexpr (NS > 1) chain_slot<1, NS, J, PUB>(nS, Wb, L, j_inner, ln, o, g, A, B, rA, rB);
+  for (int i = 0; i < n; i += PGS_AHEAD) {
 #pragma unroll
-  for (int k = 0; k < NS; ++k) {
-    const int c = ln + 64 * k;
-    if (c < nS) {
-#pragma unroll
-      for (int q = 0; q < 3; ++q) L.gS[3 * (c + o) + q] = g[k][q];
+    for (int u = 0; u < PGS_AHEAD; ++u) {
+      chain_visit<J, PUB>(c, X[u], i + u, at, pat, prog, j_inner, k);
+      // the mask of the comparison is ready behind the loads
+      k.open = __ballot(c.e[0] >= 0.0);
+      __builtin_amdgcn_sched_barrier(0);
+      blk_load(X[u], B, off, ln);
+      off += stride;
     }
   }
+  // visits that ended at once have published nothing: the whole count
+  if (PUB && ln == n - 1) __hip_atomic_store(&L.cprog, prog, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  __atomic_signal_fence(__ATOMIC_SEQ_CST);
+  // a contact that sticks has a positive normal force
+  c.st = ((k.slip >> ln) & 1ull) ? ICR_SLIP : L.lamS[3 * (ln < n ? me : me - ln)] != 0.0 ? ICR_STICK : ICR_SEPARATE;
 }
 
-// Sweep over a set of 65..512 contacts by R = ceil(nS / 64) waves: wave w
-// keeps the gaps of contacts 64 w .. 64 w + 63 (one register slot; blocked
-// W~_SS columns of nsp contacts).  The contacts are solved in order, each
-// 64-contact block by the wave that keeps its gaps, while every other wave
-// applies each solved contact's force change to its own gaps as soon as it
-// is published; no wave applies another block's updates on the solving
-// chain, and no barrier is taken.  The solving wave publishes how many
-// contacts are done in L.cprog after the force's stores (LDS operations of
-// one wave complete in order); an applying wave takes the change as the
-// published force minus the force at the sweep's start (each contact is
-// solved once per sweep), so every gap receives the same products in the
-// same order as in the one-wave sweep.  A wave solves its block only after
-// it has applied every earlier block, so each wait is on a wave that is
-// making progress.  A wait that runs out (a broken count, not an input)
-// sets L.perr.
-// NSP: the padded set size when fixed at compile time (128: two waves), else 0.
+// A set of up to 512 contacts is swept by R = ceil(nS / 64) waves: wave w
+// keeps the gaps of contacts 64 w .. 64 w + 63.  The contacts are solved in
+// order, each 64-contact block by the wave that keeps its gaps, while every
+// other wave applies each force change to its own gaps as soon as it is
+// published; no wave applies another block's updates on the solving chain,
+// and no barrier is taken.  Every gap receives the same products in the same
+// order as in a one-wave sweep.  A wave solves its block only after it has
+// applied every earlier block, so each wait is on a wave that is making
+// progress.  A wait that runs out (a broken count, not an input) sets L.perr.
 constexpr int RING_SPIN = 1 << 24;
-template <int NSP>
-__device__ inline void ring_load(double2 (&X)[1][PGS_BLK / 2], const double *__restrict__ Wb, int i, int nsp,
-                                 int ln, int w) {
-  const double2 *base = reinterpret_cast<const double2 *>(Wb + (long)i * (NSP ? NSP : nsp) * PGS_BLK);
-  const int lo = (64 * w + ln) * (PGS_BLK / 2);
-#pragma unroll
-  for (int j = 0; j < PGS_BLK / 2; ++j) X[0][j] = base[lo + j];
-}
-
-// The solving part: contacts b .. e-1 (this wave's gaps).
-template <int J, int NSP>
-__device__ inline void ring_solve(int b, int e, int nsp, const double *__restrict__ Wb, PgsLds &L, int j_inner,
-                                  int ln, int w, double (&g)[1][3]) {
-  if (b >= e) return;
-  const int last = e - 1;
-  double2 A[1][PGS_BLK / 2], B[1][PGS_BLK / 2];
-  ChainRec rA, rB;
-  ring_load<NSP>(A, Wb, b, nsp, ln, w);
-  ring_load<NSP>(B, Wb, min(b + 1, last), nsp, ln, w);
-  chain_rec(rA, L, b);
-  for (int i = b; i < e; i += 2) {
-    chain_rec(rB, L, min(i + 1, last));
-    chain_step<0, 1, J>(i, A, rA, g, L, j_inner, ln, 0);
-    __atomic_signal_fence(__ATOMIC_SEQ_CST);
-    if (ln == 0) __hip_atomic_store(&L.cprog, i + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    ring_load<NSP>(A, Wb, min(i + 2, last), nsp, ln, w);
-    if (i + 1 < e) {
-      chain_rec(rA, L, min(i + 2, last));
-      chain_step<0, 1, J>(i + 1, B, rB, g, L, j_inner, ln, 0);
-      __atomic_signal_fence(__ATOMIC_SEQ_CST);
-      if (ln == 0) __hip_atomic_store(&L.cprog, i + 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    }
-    ring_load<NSP>(B, Wb, min(i + 3, last), nsp, ln, w);
-  }
-}
-
-// The applying part: the changes of contacts b .. e-1, solved by another
-// wave, added to this wave's gaps in contact order.
-__device__ inline void ring_apply_one(int i, const double2 (&X)[1][PGS_BLK / 2], PgsLds &L, double (&g)[1][3]) {
-  for (int spin = 0; __hip_atomic_load(&L.cprog, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) <= i; ++spin) {
+__device__ __forceinline__ void ring_wait(PgsLds &L, int prog, int &seen) {
+  if (seen >= prog) return;
+  for (int spin = 0;; ++spin) {
+    seen = __builtin_amdgcn_readfirstlane(
+        __hip_atomic_load(&L.cprog, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
+    if (seen >= prog) break;
     if (spin == RING_SPIN) {
       __hip_atomic_store(&L.perr, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
       break;
@@ -1235,69 +1330,85 @@ __device__ inline void ring_apply_one(int i, const double2 (&X)[1][PGS_BLK / 2],
     __builtin_amdgcn_s_sleep(1);
   }
   __atomic_signal_fence(__ATOMIC_SEQ_CST);
-  const double *rp = L.rec + PGS_RW * i + 19;
-  const double d0 = rp[0] - L.lamS0[3 * i], d1 = rp[1] - L.lamS0[3 * i + 1], d2 = rp[2] - L.lamS0[3 * i + 2];
-  const double bb[9] = {X[0][0].x, X[0][0].y, X[0][1].x, X[0][1].y, X[0][2].x,
-                        X[0][2].y, X[0][3].x, X[0][3].y, X[0][4].x};
-#pragma unroll
-  for (int a = 0; a < 3; ++a) g[0][a] = fma(bb[3 * a + 2], d2, fma(bb[3 * a + 1], d1, fma(bb[3 * a], d0, g[0][a])));
 }
-template <int NSP>
-__device__ inline void ring_apply(int b, int e, int nsp, const double *__restrict__ Wb, PgsLds &L, int ln, int w,
-                                  double (&g)[1][3]) {
-  if (b >= e) return;
-  const int last = e - 1;
-  double2 A[1][PGS_BLK / 2], B[1][PGS_BLK / 2];
-  ring_load<NSP>(A, Wb, b, nsp, ln, w);
-  ring_load<NSP>(B, Wb, min(b + 1, last), nsp, ln, w);
-  for (int i = b; i < e; i += 2) {
-    ring_apply_one(i, A, L, g);
-    ring_load<NSP>(A, Wb, min(i + 2, last), nsp, ln, w);
-    if (i + 1 < e) ring_apply_one(i + 1, B, L, g);
-    ring_load<NSP>(B, Wb, min(i + 3, last), nsp, ln, w);
+// The applying part: the changes of contacts b .. b + n - 1 of the LDS arrays,
+// solved by another wave, added to this wave's gaps in contact order.  prog0:
+// the count before the first one.
+__device__ __forceinline__ void ring_apply(ChainLane &c, int n, const BlkBuf &B, unsigned off, unsigned stride, int b,
+                                           int prog0, PgsLds &L, int ln) {
+  BlkCol X[PGS_AHEAD];
+#pragma unroll
+  for (int u = 0; u < PGS_AHEAD; ++u) {
+    blk_load(X[u], B, off, ln);
+    off += stride;
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  int seen = prog0;
+  for (int i = 0; i < n; i += PGS_AHEAD) {
+#pragma unroll
+    for (int u = 0; u < PGS_AHEAD; ++u) {
+      if (i + u < n) {
+        ring_wait(L, prog0 + i + u + 1, seen);
+        const double *l = L.lamS + 3 * (b + i + u), *l0 = L.lamS0 + 3 * (b + i + u);
+        blk_apply(c.e, X[u], l[0] - l0[0], l[1] - l0[1], l[2] - l0[2]);
+        blk_load(X[u], B, off, ln);
+        off += stride;
+      }
+    }
   }
 }
 
-template <int J, int NSP>
-__device__ __forceinline__ void chain_ring(int nS, int nsp, const double *__restrict__ Wb, PgsLds &L, int j_inner,
-                                           int w) {
-  const int ln = threadIdx.x & 63, c = 64 * w + ln, R = (nS + 63) / 64;
-  double g[1][3];
-#pragma unroll
-  for (int q = 0; q < 3; ++q) g[0][q] = c < nS ? L.gS[3 * c + q] : 0.0;
-  if constexpr (NSP == 128) {   // two waves: one block each
-    const int h = min(64, nS);
-    if (w == 0) {
-      ring_solve<J, NSP>(0, h, nsp, Wb, L, j_inner, ln, w, g);
-      ring_apply<NSP>(h, nS, nsp, Wb, L, ln, w, g);
-    } else {
-      ring_apply<NSP>(0, h, nsp, Wb, L, ln, w, g);
-      ring_solve<J, NSP>(h, nS, nsp, Wb, L, j_inner, ln, w, g);
-    }
-  } else {
-    for (int b = 0; b < R; ++b) {
-      const int lo = 64 * b, hi = min(lo + 64, nS);
-      if (b == w)
-        ring_solve<J, NSP>(lo, hi, nsp, Wb, L, j_inner, ln, w, g);
-      else
-        ring_apply<NSP>(lo, hi, nsp, Wb, L, ln, w, g);
-    }
+// One sweep over nS contacts, padded to nsp, by wave w < nsp / 64; o: first
+// contact of the set in the LDS arrays (L.lamS = L.lamS0 = the forces at the
+// sweep's start), prog0: the count of solved contacts before the sweep, which
+// adds nsp.
+template <int J, bool PUB>
+__device__ __forceinline__ void chain_sweep(ChainLane &c, int nS, int nsp, const BlkBuf &B, int o, int prog0,
+                                            PgsLds &L, int j_inner, int w, int ln) {
+  const unsigned stride = 8u * PGS_BLK * (unsigned)nsp, col = 8u * BLK_GROUP * (unsigned)w;
+  const int me = o + 64 * w + ln, prog = prog0 + 64 * w + ln + 1;
+  if (!PUB) {
+    chain_solve<J, false>(c, nS, B, col, stride, me, prog, L, j_inner, ln);
+    return;
   }
-  if (c < nS) {
-#pragma unroll
-    for (int q = 0; q < 3; ++q) L.gS[3 * c + q] = g[0][q];
+  for (int b = 0; b < nS; b += 64) {
+    const int n = min(64, nS - b);
+    if (b == 64 * w) {
+      __builtin_amdgcn_s_setprio(3);   // the solving wave first on its SIMD
+      chain_solve<J, true>(c, n, B, col + stride * (unsigned)b, stride, me, prog, L, j_inner, ln);
+      __builtin_amdgcn_s_setprio(0);
+    } else {
+      ring_apply(c, n, B, col + stride * (unsigned)b, stride, o + b, prog0 + b, L, ln);
+    }
   }
 }
 
 // The active set of the first sweep, its compact couplings and records are
 // prepared by a wide kernel before the sequential kernel starts (a set that
 // grows later is rebuilt inside k_pgs_active).
+// Entry e of the blocked couplings of the set Sidx (nS contacts padded to
+// nsp): h^2 W of the block, zero diagonal blocks and padding.  The rows of
+// contact i stand for its columns (W is exactly symmetric), so consecutive
+// lanes read neighbouring columns of one row.
+template <class TW>
+__device__ __forceinline__ double blk_value(long e, int nS, int nsp, const int *Sidx, const TW *__restrict__ W, int m,
+                                            double h2) {
+  const int per = nsp * PGS_BLK;
+  const int i = (int)(e / per), r = (int)(e % per);
+  int l, j;
+  blk_index(r % BLK_GROUP, l, j);
+  const int c = 64 * (r / BLK_GROUP) + l;
+  if (c >= nS || c == i) return 0.0;
+  return h2 * (double)W[(3L * Sidx[i] + j % 3) * m + 3L * Sidx[c] + j / 3];
+}
+
 // k_pgs_gather (any grid): the normal gaps at the set's start and sqrt(W~_nn)
 // of every contact; every block forms the set S = {c : lambda_c != 0 or
 // g0_n(c) < 0} in ascending order (64-contact ballots, window prefix) and
 // block 0 writes S and |S|.  For a set of at most PGS_WAVE_MAX contacts the blocks then
 // write the blocked W~_SS with zero diagonal blocks, the per-contact records
-// and the gaps without the own term, e = g0 - W~_cc lambda_c.
+// (row q of contact i at q |S| + i: PgsRec, then the square roots of the
+// block's diagonal) and the gaps without the own term, e = g0 - W~_cc lambda_c.
 template <class TW>
 __global__ __launch_bounds__(256) void k_pgs_gather(int nc, const TW *__restrict__ W,
                                                     const double *__restrict__ g0, const double *__restrict__ lam,
@@ -1350,22 +1461,16 @@ __global__ __launch_bounds__(256) void k_pgs_gather(int nc, const TW *__restrict
   if (nS == 0 || nS > PGS_WAVE_MAX) return;
   const int nsp = pgs_wave_pad(nS);
   const long nel = (long)nS * nsp * PGS_BLK;
-  for (long e = t0; e < nel; e += stride) {
-    const int j = (int)(e % PGS_BLK);
-    const long ic = e / PGS_BLK;
-    const int c = (int)(ic % nsp), i = (int)(ic / nsp);
-    double v = 0.0;
-    if (j < 9 && c < nS && c != i) v = h2 * (double)W[(3L * Sidx[c] + j / 3) * m + 3L * Sidx[i] + j % 3];
-    Wss[e] = v;
-  }
+  for (long e = t0; e < nel; e += stride) Wss[e] = blk_value(e, nS, nsp, Sidx, W, m, h2);
   for (long i = t0; i < nS; i += stride) {
     double wb[3][3];
     const long ci = 3L * Sidx[i];
     for (int p = 0; p < 3; ++p)
       for (int q = 0; q < 3; ++q) wb[p][q] = h2 * (double)W[(ci + p) * m + ci + q];
-    double tmp[19];
-    make_record(wb, mu[Sidx[i]], tmp);
-    for (int q = 0; q < 19; ++q) rec[PGS_RW * i + q] = tmp[q];
+    const PgsRec tmp = make_record(wb, mu[Sidx[i]]);
+    const double *x = reinterpret_cast<const double *>(&tmp);
+    for (int q = 0; q < PGS_RC; ++q) rec[(long)q * nS + i] = x[q];
+    for (int q = 0; q < 3; ++q) rec[(long)(PGS_RC + q) * nS + i] = sqrt(wb[q][q]);
   }
   for (long r = t0; r < 3L * nS; r += stride) {
     const long cr = 3L * Sidx[r / 3];
@@ -1398,24 +1503,26 @@ __device__ __forceinline__ void pgs_active_body(PgsLds &L, int nc, const TW *__r
     L.inS[c] = (nzc || g0[3 * c] < 0.0) ? 1 : 0;
   }
   if (tid == 0) {
-    L.stop = 0;
     L.zflag = 0;
     L.perr = 0;
+    L.cprog = 0;
     ctl[0] = 0;
     ctl[1] = 0;
   }
   __syncthreads();
+  const int wu = __builtin_amdgcn_readfirstlane(wv);
   int sweep = 0, nS = 0, ldS = 0, nsp = 0;
+  int nsweep = 0, prog = 0;   // sweeps run and contacts solved, restarted sweeps included
   double eps = 0.0;
   bool need_build = true, first_build = true, built = false;
   while (sweep < max_sweeps) {
     if (need_build && first_build && npre <= PGS_WAVE_MAX) {
       // ---- the prepared first set: copy it in
-      nS = npre;
+      nS = __builtin_amdgcn_readfirstlane(npre);
       ldS = 3 * nS;
       nsp = pgs_wave_pad(nS);
       for (int i = tid; i < nS; i += PGS_NT) L.Sidx[i] = preSidx[i];
-      for (int e = tid; e < nS * 19; e += PGS_NT) L.rec[PGS_RW * (e / 19) + e % 19] = preRec[PGS_RW * (e / 19) + e % 19];
+      for (int e = tid; e < nS * (PGS_RC + 3); e += PGS_NT) L.rec[PGS_SMAX * (e / nS) + e % nS] = preRec[e];
       for (int r = tid; r < ldS; r += PGS_NT) L.gS[r] = preGS[r];
       __syncthreads();
       for (int r = tid; r < ldS; r += PGS_NT) {
@@ -1446,7 +1553,7 @@ __device__ __forceinline__ void pgs_active_body(PgsLds &L, int nc, const TW *__r
         L.nS = acc;
       }
       __syncthreads();
-      nS = L.nS;
+      nS = __builtin_amdgcn_readfirstlane(L.nS);
       if (nS > PGS_SMAX) {   // hand over: global lambda holds the sweep-start state
         if (tid == 0) {
           ctl[0] = 1;
@@ -1467,18 +1574,10 @@ __device__ __forceinline__ void pgs_active_body(PgsLds &L, int nc, const TW *__r
         L.lamS[r] = lam[3 * L.Sidx[r / 3] + r % 3];
         L.lamSet[r] = L.lamS[r];
       }
-      // ---- compact couplings W~_SS: blocked [i][c] 3x3 blocks of rows c,
-      // columns i (padded to nsp contacts), zero diagonal blocks
+      // ---- compact couplings W~_SS (padded to nsp contacts) and records
       {
         const long nel = (long)nS * nsp * PGS_BLK;
-        for (long e = tid; e < nel; e += PGS_NT) {
-          const int j = (int)(e % PGS_BLK);
-          const long ic = e / PGS_BLK;
-          const int c = (int)(ic % nsp), i = (int)(ic / nsp);
-          double v = 0.0;
-          if (j < 9 && c < nS && c != i) v = h2 * (double)W[(3L * L.Sidx[c] + j / 3) * m + 3L * L.Sidx[i] + j % 3];
-          Wss[e] = v;
-        }
+        for (long e = tid; e < nel; e += PGS_NT) Wss[e] = blk_value(e, nS, nsp, L.Sidx, W, m, h2);
       }
       __threadfence_block();
       __syncthreads();
@@ -1487,10 +1586,10 @@ __device__ __forceinline__ void pgs_active_body(PgsLds &L, int nc, const TW *__r
         const long ci = 3L * L.Sidx[i];
         for (int p = 0; p < 3; ++p)
           for (int q = 0; q < 3; ++q) wb[p][q] = h2 * (double)W[(ci + p) * m + ci + q];
-        double *rc = L.rec + PGS_RW * i;
-        double tmp[19];
-        make_record(wb, mu[L.Sidx[i]], tmp);
-        for (int q = 0; q < 19; ++q) rc[q] = tmp[q];
+        const PgsRec tmp = make_record(wb, mu[L.Sidx[i]]);
+        const double *x = reinterpret_cast<const double *>(&tmp);
+        for (int q = 0; q < PGS_RC; ++q) L.rec[q * PGS_SMAX + i] = x[q];
+        for (int q = 0; q < 3; ++q) L.rec[(PGS_RC + q) * PGS_SMAX + i] = sqrt(wb[q][q]);
       }
       // ---- gaps at the set's start state (lambda is zero outside S)
       if (first_build) {
@@ -1506,7 +1605,10 @@ __device__ __forceinline__ void pgs_active_body(PgsLds &L, int nc, const TW *__r
         for (int c = wv; c < nS; c += PGS_NW) {
           double a0 = 0.0, a1 = 0.0, a2 = 0.0;
           for (int i = ln; i < nS; i += 64) {
-            const double *b = Wss + ((long)i * nsp + c) * PGS_BLK;
+            const double *g = Wss + (long)i * nsp * PGS_BLK + (long)BLK_GROUP * (c / 64);
+            double b[9];
+#pragma unroll
+            for (int j = 0; j < 9; ++j) b[j] = g[blk_entry(c % 64, j)];
             const double l0 = L.lamS[3 * i], l1 = L.lamS[3 * i + 1], l2 = L.lamS[3 * i + 2];
             a0 += b[0] * l0 + b[1] * l1 + b[2] * l2;
             a1 += b[3] * l0 + b[4] * l1 + b[5] * l2;
@@ -1561,72 +1663,90 @@ __device__ __forceinline__ void pgs_active_body(PgsLds &L, int nc, const TW *__r
       __syncthreads();
       built = false;
     }
-    // ---- sweep over S from its start state (forces into the records)
-    for (int r = tid; r < ldS; r += PGS_NT) {
-      L.lamS0[r] = L.lamS[r];
-      L.rec[PGS_RW * (r / 3) + 19 + r % 3] = L.lamS[r];
-    }
-    if (tid == 0) {
-      L.flag = 0;
-      L.nu = 0;
-      L.cprog = 0;
-    }
-    __syncthreads();
-    if (nS > 0) {
+    // ---- sweep over S from its start state, by the waves that hold its
+    // contacts, and their part of the sweep's sums: squared changes,
+    // |lambda|^2, and the bound factor of the skipped contacts' gaps
+    // B = sum_q sqrt(W~_qq) max(|lamS - lamSet|, |lamS0 - lamSet|)
+    double *red = L.red + 24 * (nsweep & 1);   // double-buffered: one barrier per sweep
+    if (64 * wu < nS) {
+      const int me = 64 * wu + ln;
+      const bool on = me < nS;
+      const BlkBuf buf(Wss, 8u * PGS_BLK * (unsigned)nsp * (unsigned)nS);
+      ChainLane c;
+      c.rc = pgs_rec_load(L, on ? me : 0);
+#pragma unroll
+      for (int q = 0; q < 3; ++q) {
+        c.e[q] = on ? L.gS[3 * me + q] : 0.0;
+        c.l[q] = on ? L.lamS[3 * me + q] : 0.0;
+        if (on) L.lamS0[3 * me + q] = c.l[q];
+      }
       if (nS <= 64) {
-        if (wv == 0) {
-          if (j_inner == 8)
-            chain_wave<1, 8>(nS, Wss, L, j_inner);
-          else
-            chain_wave<1, 0>(nS, Wss, L, j_inner);
-        }
-      } else if (nS <= 128) {
-        if (wv < 2) {
-          if (j_inner == 8)
-            chain_ring<8, 128>(nS, nsp, Wss, L, j_inner, wv);
-          else
-            chain_ring<0, 128>(nS, nsp, Wss, L, j_inner, wv);
-        }
-      } else if (wv < (nS + 63) / 64) {
         if (j_inner == 8)
-          chain_ring<8, 0>(nS, nsp, Wss, L, j_inner, wv);
+          chain_sweep<8, false>(c, nS, nsp, buf, 0, prog, L, j_inner, 0, ln);
         else
-          chain_ring<0, 0>(nS, nsp, Wss, L, j_inner, wv);
+          chain_sweep<0, false>(c, nS, nsp, buf, 0, prog, L, j_inner, 0, ln);
+      } else {
+        if (j_inner == 8)
+          chain_sweep<8, true>(c, nS, nsp, buf, 0, prog, L, j_inner, wu, ln);
+        else
+          chain_sweep<0, true>(c, nS, nsp, buf, 0, prog, L, j_inner, wu, ln);
+      }
+      double dpart = 0.0, bpart = 0.0, npart = 0.0;
+      if (on) {
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+          const double ls = L.lamS[3 * me + q], lset = L.lamSet[3 * me + q], dv = ls - c.l[q];
+          L.gS[3 * me + q] = c.e[q];
+          dpart += dv * dv;
+          bpart += L.rec[(PGS_RC + q) * PGS_SMAX + me] * fmax(fabs(ls - lset), fabs(c.l[q] - lset));
+          npart += ls * ls;
+        }
+        L.stS[me] = (unsigned char)c.st;
+      }
+      for (int o = 32; o > 0; o >>= 1) {
+        dpart += __shfl_xor(dpart, o, 64);
+        bpart += __shfl_xor(bpart, o, 64);
+        npart += __shfl_xor(npart, o, 64);
+      }
+      if (ln == 0) {
+        red[3 * wu] = dpart;
+        red[3 * wu + 1] = bpart;
+        red[3 * wu + 2] = npart;
       }
     }
+    prog += nsp;
+    ++nsweep;
     __syncthreads();
-    // ---- one pass over S: sum of squared changes of the sweep, |lambda|^2,
-    // and the bound factor of the skipped contacts' gaps
-    // B = sum_q sqrt(W~_qq) max(|lamS - lamSet|, |lamS0 - lamSet|)
-    // (the forces come back from the records in the same pass)
-    double dpart = 0.0, bpart = 0.0, npart = 0.0;
-    for (int r = tid; r < ldS; r += PGS_NT) {
-      const double *rc = L.rec + PGS_RW * (r / 3);
-      const double wqq = (r % 3 == 0) ? rc[0] : ((r % 3 == 1) ? rc[3] : rc[5]);
-      const double ls = rc[19 + r % 3], l0 = L.lamS0[r], lset = L.lamSet[r];
-      L.lamS[r] = ls;
-      const double dv = ls - l0;
-      dpart += dv * dv;
-      bpart += sqrt(wqq) * fmax(fabs(ls - lset), fabs(l0 - lset));
-      npart += ls * ls;
+    if (prog > (1 << 30)) {   // the count of solved contacts starts over
+      prog = 0;
+      __syncthreads();
+      if (tid == 0) L.cprog = 0;
+      __syncthreads();
     }
-    block_sum3(dpart, bpart, npart, L.red);
-    if (tid == 0) {
-      const double diff = sqrt(dpart), nl = sqrt(npart);
-      eps = nl > 0.0 ? diff / nl : (diff == 0.0 ? 0.0 : INFINITY);
-      if (L.perr) eps = NAN;   // the ring sweep lost its count: stop and report eps = NaN
-      L.stop = (eps <= tol || L.perr) ? 1 : 0;
-      L.red[0] = bpart * (1.0 + 1e-12);
-      L.settled = (L.zflag == 0 && L.red[0] < L.Rmin) ? 1 : 0;
+    double dsum = 0.0, B = 0.0, nsum = 0.0;   // every thread takes the same sums
+    for (int w = 0; 64 * w < nS; ++w) {
+      dsum += red[3 * w];
+      B += red[3 * w + 1];
+      nsum += red[3 * w + 2];
     }
-    __syncthreads();
-    const double B = L.red[0];
+    const double diff = sqrt(dsum), nl = sqrt(nsum);
+    eps = nl > 0.0 ? diff / nl : (diff == 0.0 ? 0.0 : INFINITY);
+    const bool perr = L.perr != 0;
+    if (perr) eps = NAN;   // the ring sweep lost its count: stop and report eps = NaN
+    const bool stop = eps <= tol || perr;
+    B *= 1.0 + 1e-12;
     // ---- verify the skipped contacts (all settled at once when B < Rmin)
-    if (!L.settled) {
+    bool grow = false;
+    if (L.zflag != 0 || !(B < L.Rmin)) {
+      if (tid == 0) {
+        L.nu = 0;
+        L.flag = 0;
+      }
+      __syncthreads();
       for (int c = tid; c < nc; c += PGS_NT) {
         if (L.inS[c]) continue;
         const double g = gnSet[c], rb = swn[c] * B;
-        if (!(g - rb > 1e-13 * (fabs(g) + rb))) L.ulist[atomicAdd(&L.nu, 1)] = c;
+        if (!(g - rb > 1e-13 * (fabs(g) + rb))) L.ulist[atomicAdd(&L.nu, 1)] = (unsigned short)c;
       }
       __syncthreads();
       const int nu = L.nu;
@@ -1644,8 +1764,9 @@ __device__ __forceinline__ void pgs_active_body(PgsLds &L, int nc, const TW *__r
         }
       }
       __syncthreads();
+      grow = L.flag != 0 && !perr;
     }
-    if (L.flag && !L.perr) {
+    if (grow) {
       // a skipped contact was not a no-op: restart the sweep with a larger S
       for (int r = tid; r < ldS; r += PGS_NT) lam[3 * L.Sidx[r / 3] + r % 3] = L.lamS0[r];
       need_build = true;
@@ -1654,7 +1775,7 @@ __device__ __forceinline__ void pgs_active_body(PgsLds &L, int nc, const TW *__r
       continue;
     }
     ++sweep;
-    if (L.stop) break;
+    if (stop) break;
   }
   for (int r = tid; r < ldS; r += PGS_NT) lam[3 * L.Sidx[r / 3] + r % 3] = L.lamS[r];
   for (int i = tid; i < nS; i += PGS_NT) status[L.Sidx[i]] = (int8_t)L.stS[i];
@@ -1695,7 +1816,7 @@ __global__ __launch_bounds__(PGS_NT) void k_pgs_active(int nc, const TW *__restr
 template <class TM>
 __device__ void wg_sym_gemv_sparse(int nc, const TM *__restrict__ M, const double *__restrict__ x0,
                                    const double *__restrict__ v, const double *__restrict__ nzv, double h2,
-                                   double *__restrict__ y, int *list, int *count, double *part) {
+                                   double *__restrict__ y, unsigned short *list, int *count, double *part) {
   static_assert(PGS_NT == SG_NT, "the per-scene kernel's wave count");
   const int tid = threadIdx.x, wv = tid >> 6, ln = tid & 63;
   const long m = 3L * nc;
@@ -1705,7 +1826,7 @@ __device__ void wg_sym_gemv_sparse(int nc, const TM *__restrict__ M, const doubl
       const int c = c0 + ln;
       const bool nz = c < nc && block_nonzero(nzv, c);
       const unsigned long long bal = __ballot(nz);
-      if (nz) list[cnt + __popcll(bal & ((1ull << ln) - 1ull))] = c;
+      if (nz) list[cnt + __popcll(bal & ((1ull << ln) - 1ull))] = (unsigned short)c;
       cnt += __popcll(bal);
     }
     if (ln == 0) *count = cnt;
@@ -1861,7 +1982,7 @@ struct PcaLds {
   int Sidx[PCA_MAX];
   unsigned char stS[PCA_MAX];
   int wcount[64];
-  int ulist[PGS_MAX_NC];
+  unsigned short ulist[PGS_MAX_NC];
   unsigned char inS[PGS_MAX_NC];
   int nS, flag, stop, nu;
   int cprog, perr;   // two-wave sweep: contacts done by the solving wave; a wait ran out
@@ -1933,13 +2054,12 @@ __device__ inline void contact_frame_rcp(const icr_obstacle &obs, double t0, dou
   delta[2] = tb[0] * rel[0] + tb[1] * rel[1] + tb[2] * rel[2];
 }
 
-// One visit of the chain: contact i, its proximity in lane i % 64, slot K.
-template <int K, int NS, int J>
-__device__ inline void pca_step(int i, const double2 (&X)[NS][PGS_BLK / 2], const PcaRec &c, double (&g)[NS][3],
-                                PcaLds &L, int j_inner, int ln, const icr_obstacle &obs, double t0, double t1,
-                                double h2) {
+// One visit of the chain: contact i, its proximity in lane i % 64.
+template <int J>
+__device__ inline void pca_step(int i, const BlkCol &X, const PcaRec &c, double (&g)[3], PcaLds &L, int j_inner,
+                                int ln, const icr_obstacle &obs, double t0, double t1, double h2) {
   const int li = i & 63;
-  const double pa[3] = {readlane_f64(g[K][0], li), readlane_f64(g[K][1], li), readlane_f64(g[K][2], li)};
+  const double pa[3] = {readlane_f64(g[0], li), readlane_f64(g[1], li), readlane_f64(g[2], li)};
   const double ps[3] = {c[7], c[8], c[9]};
   double F[3][3], delta[3];
   contact_frame_rcp(obs, t0, t1, pa, ps, F, delta);
@@ -1956,8 +2076,7 @@ __device__ inline void pca_step(int i, const double2 (&X)[NS][PGS_BLK / 2], cons
   double lr[3], dd[3];
   for (int a = 0; a < 3; ++a) lr[a] = F[a][0] * fo[0] + F[a][1] * fo[1] + F[a][2] * fo[2];
   for (int a = 0; a < 3; ++a) dd[a] = delta[a] - (w[a][0] * lr[0] + w[a][1] * lr[1] + w[a][2] * lr[2]);
-  double rc[PGS_RW];
-  make_record<true>(w, c[6], rc);
+  const PgsRec rc = make_record<true>(w, c[6]);
   const Local r = local_solve_rec<J>(rc, dd, j_inner);
   double fn[3], df[3];
   for (int q = 0; q < 3; ++q) {
@@ -1973,62 +2092,44 @@ __device__ inline void pca_step(int i, const double2 (&X)[NS][PGS_BLK / 2], cons
     }
     L.stS[i] = (unsigned char)r.st;
   }
-#pragma unroll
-  for (int k = 0; k < NS; ++k) {
-    const double b[9] = {X[k][0].x, X[k][0].y, X[k][1].x, X[k][1].y, X[k][2].x,
-                         X[k][2].y, X[k][3].x, X[k][3].y, X[k][4].x};
-#pragma unroll
-    for (int a = 0; a < 3; ++a) g[k][a] = fma(b[3 * a + 2], df[2], fma(b[3 * a + 1], df[1], fma(b[3 * a], df[0], g[k][a])));
-  }
+  blk_apply(g, X, df[0], df[1], df[2]);
 }
 
-template <int K, int NS, int J>
-__device__ inline void pca_slot(int nS, const double *__restrict__ Wb, PcaLds &L, int j_inner, int ln,
-                                double (&g)[NS][3], double2 (&A)[NS][PGS_BLK / 2], double2 (&B)[NS][PGS_BLK / 2],
-                                PcaRec &rA, PcaRec &rB, const icr_obstacle &obs, double t0, double t1, double h2) {
-  const int last = nS - 1, end = min(nS, 64 * K + 64);
-  for (int i = 64 * K; i < end; i += 2) {
-    pca_rec(rB, L, min(i + 1, last));
-    pca_step<K, NS, J>(i, A, rA, g, L, j_inner, ln, obs, t0, t1, h2);
-    chain_load<NS>(A, Wb, min(i + 2, last), ln);
-    if (i + 1 < end) {
-      pca_rec(rA, L, min(i + 2, last));
-      pca_step<K, NS, J>(i + 1, B, rB, g, L, j_inner, ln, obs, t0, t1, h2);
-    }
-    chain_load<NS>(B, Wb, min(i + 3, last), ln);
-  }
+// Column i's blocks of the rows of wave w (h^2 W_H,SS padded to nsp contacts).
+__device__ __forceinline__ void pca_load(BlkCol &X, const BlkBuf &B, int i, int nsp, int w, int ln) {
+  blk_load(X, B, 8u * (unsigned)(i * (nsp * PGS_BLK) + BLK_GROUP * w), ln);
 }
 
-template <int NS, int J>
-__device__ __forceinline__ void pca_chain(int nS, const double *__restrict__ Wb, PcaLds &L, int j_inner,
+template <int J>
+__device__ __forceinline__ void pca_chain(int nS, const BlkBuf &Wb, PcaLds &L, int j_inner,
                                           const icr_obstacle &obs, double t0, double t1, double h2) {
   const int ln = threadIdx.x & 63;
-  double g[NS][3];
+  double g[3];
 #pragma unroll
-  for (int k = 0; k < NS; ++k) {
-    const int c = ln + 64 * k;
-#pragma unroll
-    for (int q = 0; q < 3; ++q) g[k][q] = c < nS ? L.P[3 * c + q] : 0.0;
-  }
+  for (int q = 0; q < 3; ++q) g[q] = ln < nS ? L.P[3 * ln + q] : 0.0;
   const int last = nS - 1;
-  double2 A[NS][PGS_BLK / 2], B[NS][PGS_BLK / 2];
+  BlkCol A, B;
   PcaRec rA, rB;
-  chain_load<NS>(A, Wb, 0, ln);
-  chain_load<NS>(B, Wb, min(1, last), ln);
+  pca_load(A, Wb, 0, 64, 0, ln);
+  pca_load(B, Wb, min(1, last), 64, 0, ln);
   pca_rec(rA, L, 0);
-  pca_slot<0, NS, J>(nS, Wb, L, j_inner, ln, g, A, B, rA, rB, obs, t0, t1, h2);
-  if constexpr (NS > 1) pca_slot<1, NS, J>(nS, Wb, L, j_inner, ln, g, A, B, rA, rB, obs, t0, t1, h2);
-#pragma unroll
-  for (int k = 0; k < NS; ++k) {
-    const int c = ln + 64 * k;
-    if (c < nS) {
-#pragma unroll
-      for (int q = 0; q < 3; ++q) L.P[3 * c + q] = g[k][q];
+  for (int i = 0; i < nS; i += 2) {
+    pca_rec(rB, L, min(i + 1, last));
+    pca_step<J>(i, A, rA, g, L, j_inner, ln, obs, t0, t1, h2);
+    pca_load(A, Wb, min(i + 2, last), 64, 0, ln);
+    if (i + 1 < nS) {
+      pca_rec(rA, L, min(i + 2, last));
+      pca_step<J>(i + 1, B, rB, g, L, j_inner, ln, obs, t0, t1, h2);
     }
+    pca_load(B, Wb, min(i + 3, last), 64, 0, ln);
+  }
+  if (ln < nS) {
+#pragma unroll
+    for (int q = 0; q < 3; ++q) L.P[3 * ln + q] = g[q];
   }
 }
 
-// A set of 65..128 contacts is swept by two waves as in chain_ring: wave w
+// A set of 65..128 contacts is swept by two waves as in chain_sweep: wave w
 // keeps the proximities of contacts 64 w .. 64 w + 63, solves those
 // contacts while the other wave adds each published force change to its own
 // proximities, then applies the other half's changes.  The applying wave
@@ -2036,32 +2137,32 @@ __device__ __forceinline__ void pca_chain(int nS, const double *__restrict__ Wb,
 // sweep's start, so every proximity receives the same products in the same
 // order as in the one-wave sweep.
 template <int J>
-__device__ inline void pca_pair_solve(int b, int e, const double *__restrict__ Wb, PcaLds &L, int j_inner, int ln,
-                                      int w, double (&g)[1][3], const icr_obstacle &obs, double t0, double t1,
+__device__ inline void pca_pair_solve(int b, int e, const BlkBuf &Wb, PcaLds &L, int j_inner, int ln,
+                                      int w, double (&g)[3], const icr_obstacle &obs, double t0, double t1,
                                       double h2) {
   if (b >= e) return;
   const int last = e - 1;
-  double2 A[1][PGS_BLK / 2], B[1][PGS_BLK / 2];
+  BlkCol A, B;
   PcaRec rA, rB;
-  ring_load<128>(A, Wb, b, 128, ln, w);
-  ring_load<128>(B, Wb, min(b + 1, last), 128, ln, w);
+  pca_load(A, Wb, b, 128, w, ln);
+  pca_load(B, Wb, min(b + 1, last), 128, w, ln);
   pca_rec(rA, L, b);
   for (int i = b; i < e; i += 2) {
     pca_rec(rB, L, min(i + 1, last));
-    pca_step<0, 1, J>(i, A, rA, g, L, j_inner, ln, obs, t0, t1, h2);
+    pca_step<J>(i, A, rA, g, L, j_inner, ln, obs, t0, t1, h2);
     __atomic_signal_fence(__ATOMIC_SEQ_CST);
     if (ln == 0) __hip_atomic_store(&L.cprog, i + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    ring_load<128>(A, Wb, min(i + 2, last), 128, ln, w);
+    pca_load(A, Wb, min(i + 2, last), 128, w, ln);
     if (i + 1 < e) {
       pca_rec(rA, L, min(i + 2, last));
-      pca_step<0, 1, J>(i + 1, B, rB, g, L, j_inner, ln, obs, t0, t1, h2);
+      pca_step<J>(i + 1, B, rB, g, L, j_inner, ln, obs, t0, t1, h2);
       __atomic_signal_fence(__ATOMIC_SEQ_CST);
       if (ln == 0) __hip_atomic_store(&L.cprog, i + 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
-    ring_load<128>(B, Wb, min(i + 3, last), 128, ln, w);
+    pca_load(B, Wb, min(i + 3, last), 128, w, ln);
   }
 }
-__device__ inline void pca_pair_apply_one(int i, const double2 (&X)[1][PGS_BLK / 2], PcaLds &L, double (&g)[1][3]) {
+__device__ inline void pca_pair_apply_one(int i, const BlkCol &X, PcaLds &L, double (&g)[3]) {
   for (int spin = 0; __hip_atomic_load(&L.cprog, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) <= i; ++spin) {
     if (spin == RING_SPIN) {
       __hip_atomic_store(&L.perr, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -2074,32 +2175,29 @@ __device__ inline void pca_pair_apply_one(int i, const double2 (&X)[1][PGS_BLK /
   __atomic_signal_fence(__ATOMIC_SEQ_CST);
   const double *rp = L.rec + PCA_RW * i + 22;
   const double d0 = rp[0] - L.f0[3 * i], d1 = rp[1] - L.f0[3 * i + 1], d2 = rp[2] - L.f0[3 * i + 2];
-  const double bb[9] = {X[0][0].x, X[0][0].y, X[0][1].x, X[0][1].y, X[0][2].x,
-                        X[0][2].y, X[0][3].x, X[0][3].y, X[0][4].x};
-#pragma unroll
-  for (int a = 0; a < 3; ++a) g[0][a] = fma(bb[3 * a + 2], d2, fma(bb[3 * a + 1], d1, fma(bb[3 * a], d0, g[0][a])));
+  blk_apply(g, X, d0, d1, d2);
 }
-__device__ inline void pca_pair_apply(int b, int e, const double *__restrict__ Wb, PcaLds &L, int ln, int w,
-                                      double (&g)[1][3]) {
+__device__ inline void pca_pair_apply(int b, int e, const BlkBuf &Wb, PcaLds &L, int ln, int w,
+                                      double (&g)[3]) {
   if (b >= e) return;
   const int last = e - 1;
-  double2 A[1][PGS_BLK / 2], B[1][PGS_BLK / 2];
-  ring_load<128>(A, Wb, b, 128, ln, w);
-  ring_load<128>(B, Wb, min(b + 1, last), 128, ln, w);
+  BlkCol A, B;
+  pca_load(A, Wb, b, 128, w, ln);
+  pca_load(B, Wb, min(b + 1, last), 128, w, ln);
   for (int i = b; i < e; i += 2) {
     pca_pair_apply_one(i, A, L, g);
-    ring_load<128>(A, Wb, min(i + 2, last), 128, ln, w);
+    pca_load(A, Wb, min(i + 2, last), 128, w, ln);
     if (i + 1 < e) pca_pair_apply_one(i + 1, B, L, g);
-    ring_load<128>(B, Wb, min(i + 3, last), 128, ln, w);
+    pca_load(B, Wb, min(i + 3, last), 128, w, ln);
   }
 }
 template <int J>
-__device__ __forceinline__ void pca_pair(int nS, const double *__restrict__ Wb, PcaLds &L, int j_inner,
+__device__ __forceinline__ void pca_pair(int nS, const BlkBuf &Wb, PcaLds &L, int j_inner,
                                          const icr_obstacle &obs, double t0, double t1, double h2, int w) {
   const int ln = threadIdx.x & 63, c = 64 * w + ln, h = min(64, nS);
-  double g[1][3];
+  double g[3];
 #pragma unroll
-  for (int q = 0; q < 3; ++q) g[0][q] = c < nS ? L.P[3 * c + q] : 0.0;
+  for (int q = 0; q < 3; ++q) g[q] = c < nS ? L.P[3 * c + q] : 0.0;
   if (w == 0) {
     pca_pair_solve<J>(0, h, Wb, L, j_inner, ln, w, g, obs, t0, t1, h2);
     pca_pair_apply(h, nS, Wb, L, ln, w, g);
@@ -2109,7 +2207,7 @@ __device__ __forceinline__ void pca_pair(int nS, const double *__restrict__ Wb, 
   }
   if (c < nS) {
 #pragma unroll
-    for (int q = 0; q < 3; ++q) L.P[3 * c + q] = g[0][q];
+    for (int q = 0; q < 3; ++q) L.P[3 * c + q] = g[q];
   }
 }
 
@@ -2198,7 +2296,7 @@ __global__ __launch_bounds__(PGS_NT) void k_pgs_pca(int nc, const StepCtx *__res
         L.nS = acc;
       }
       __syncthreads();
-      nS = L.nS;
+      nS = __builtin_amdgcn_readfirstlane(L.nS);
       if (nS > PCA_MAX) {   // hand over: f and Pset hold the sweep-start state
         if (tid == 0) {
           ctl[0] = 1;
@@ -2238,11 +2336,12 @@ __global__ __launch_bounds__(PGS_NT) void k_pgs_pca(int nc, const StepCtx *__res
       // diagonal blocks included
       const long nel = (long)nS * nsp * PGS_BLK;
       for (long e = tid; e < nel; e += PGS_NT) {
-        const int j = (int)(e % PGS_BLK);
-        const long ic = e / PGS_BLK;
-        const int cc = (int)(ic % nsp), i = (int)(ic / nsp);
+        const int per = nsp * PGS_BLK, i = (int)(e / per), r = (int)(e % per);
+        int l, j;
+        blk_index(r % BLK_GROUP, l, j);
+        const int cc = 64 * (r / BLK_GROUP) + l;
         double v = 0.0;
-        if (j < 9 && cc < nS) v = h2 * WH[(3L * L.Sidx[cc] + j / 3) * m + 3L * L.Sidx[i] + j % 3];
+        if (cc < nS) v = h2 * WH[(3L * L.Sidx[i] + j % 3) * m + 3L * L.Sidx[cc] + j / 3];
         Wss[e] = v;
       }
       __threadfence_block();
@@ -2259,18 +2358,20 @@ __global__ __launch_bounds__(PGS_NT) void k_pgs_pca(int nc, const StepCtx *__res
     }
     __syncthreads();
     if (nS > 0) {
+      const BlkBuf buf(Wss, 8u * PGS_BLK * (unsigned)nsp * (unsigned)nS);
+      const int wu = __builtin_amdgcn_readfirstlane(wv);
       if (nsp == 64) {
         if (wv == 0) {
           if (j_inner == 8)
-            pca_chain<1, 8>(nS, Wss, L, j_inner, obs, t0, t1, h2);
+            pca_chain<8>(nS, buf, L, j_inner, obs, t0, t1, h2);
           else
-            pca_chain<1, 0>(nS, Wss, L, j_inner, obs, t0, t1, h2);
+            pca_chain<0>(nS, buf, L, j_inner, obs, t0, t1, h2);
         }
       } else if (wv < 2) {
         if (j_inner == 8)
-          pca_pair<8>(nS, Wss, L, j_inner, obs, t0, t1, h2, wv);
+          pca_pair<8>(nS, buf, L, j_inner, obs, t0, t1, h2, wu);
         else
-          pca_pair<0>(nS, Wss, L, j_inner, obs, t0, t1, h2, wv);
+          pca_pair<0>(nS, buf, L, j_inner, obs, t0, t1, h2, wu);
       }
     }
     __syncthreads();
@@ -2302,7 +2403,7 @@ __global__ __launch_bounds__(PGS_NT) void k_pgs_pca(int nc, const StepCtx *__res
     for (int c = tid; c < nc; c += PGS_NT) {
       if (L.inS[c]) continue;
       const double g = gnSet[c], rb = swn[c] * Bb;
-      if (!(g - rb > 1e-13 * (fabs(g) + rb))) L.ulist[atomicAdd(&L.nu, 1)] = c;
+      if (!(g - rb > 1e-13 * (fabs(g) + rb))) L.ulist[atomicAdd(&L.nu, 1)] = (unsigned short)c;
     }
     __syncthreads();
     const int nu = L.nu;
@@ -2375,13 +2476,13 @@ __global__ __launch_bounds__(PGS_NT) void k_pgs_pca(int nc, const StepCtx *__res
 // reach the gaps of all contacts, g += W~[:, block] dlambda (rows of the
 // exactly symmetric W stand for its columns), before those contacts' turn.
 // One cooperative launch with no grid barrier inside the sweeps:
-//  - workgroup 0 (the lead) runs the chain of a block in wave 0 (the register
-//    chain of the active-set kernel, which skips nothing: separated contacts
-//    are solved and stay at zero); meanwhile waves 1-3 and 5-7 add the
+//  - workgroup 0 (the lead) runs the chain of a block in waves 0 and 1 (the
+//    chains of the active-set kernel, 64 contacts each; contacts that stay
+//    separated are passed over); meanwhile waves 2-7 stage the next block's
+//    records and forces in the other half of the LDS arrays and add the
 //    block's force changes to the gaps of the NEXT block as the chain
-//    publishes them, and wave 4 stages the next block's records and forces
-//    in the other half of the LDS arrays.  So the next chain starts without
-//    waiting for the rest of the GPU.
+//    publishes them.  So the next chain starts without waiting for the rest
+//    of the GPU.
 //  - the other workgroups push each published block's changes into all other
 //    gap rows (64-row chunks, each chunk always owned by the same workgroup),
 //    one block behind the lead, and report the last block they finished.
@@ -2393,7 +2494,7 @@ constexpr int COOP_B = kPgsCoopB;   // contacts per block
 constexpr int COOP_NT = PGS_NT;     // threads per workgroup
 constexpr int COOP_MAXG = 128;      // workgroups of the launch at most
 static_assert(3 * COOP_B == 6 * 64, "a block's gap rows are six 64-row chunks");
-static_assert(COOP_NT == 512, "lead workgroup: chain wave, staging wave, six follower waves");
+static_assert(COOP_NT == 512, "lead workgroup: two chain waves, six follower waves");
 // sync words: [0] last published block, [1] stop, [2..3] changed contacts per
 // list buffer, [4] a wait gave up, [8 + w] last block pushed by workgroup w
 constexpr int COOP_SYNC_PUB = 0, COOP_SYNC_STOP = 1, COOP_SYNC_CNT = 2, COOP_SYNC_ERR = 4, COOP_SYNC_PROG = 8;
@@ -2416,7 +2517,7 @@ struct CoopArgs {
   double *eps_out;
   const int *ctl;    // [0] handover, [1] first sweep
   double *g;         // [3 nc] gaps with the own term
-  double *recAll;    // [nc * PGS_RW] records
+  double *recAll;    // [PGS_RW][nc] records, then the entries w00 w01 w02 w11 w12 w22 of the blocks
   double *Wblk;      // [nblocks * COOP_B * COOP_B * PGS_BLK] blocked diagonal couplings
   double *dl;        // [2][3 COOP_B] force changes of the last two blocks
   int *chg;          // [2][COOP_B] their changed contacts (block-local)
@@ -2440,7 +2541,7 @@ __device__ inline void st_wg(int *p, int v) { __hip_atomic_store(p, v, __ATOMIC_
 // through with non-temporal loads, so that it does not evict the blocked
 // couplings the chain reads.
 template <class TW>
-__device__ void coop_rows(int m, const TW *__restrict__ M, const int *list, int nlist, const double *vals,
+__device__ void coop_rows(int m, const TW *__restrict__ M, const unsigned short *list, int nlist, const double *vals,
                           int cbase, const double *base, double h2, double *y, double *part, int first, int stride,
                           int skip_lo, int skip_hi) {
   const int tid = threadIdx.x, wv = tid >> 6, ln = tid & 63;
@@ -2484,15 +2585,15 @@ __device__ void coop_rows(int m, const TW *__restrict__ M, const int *list, int 
 }
 
 // Own-term-free gap of row e of the block staged at contact o of the LDS
-// arrays: g - w lambda, w the contact's 3x3 block (record entries 0-5 =
-// w00 w01 w02 w11 w12 w22), lambda its current force (entries 19-21).
+// arrays: g - w lambda, w the contact's 3x3 block (the record's last six rows,
+// w00 w01 w02 w11 w12 w22), lambda its current force.
 __device__ inline double coop_own_free(const PgsLds &L, int o, int e, double g) {
-  const double *rc = L.rec + PGS_RW * (o + e / 3);
-  const int r = e % 3;
-  const double w0 = r == 0 ? rc[0] : (r == 1 ? rc[1] : rc[2]);
-  const double w1 = r == 0 ? rc[1] : (r == 1 ? rc[3] : rc[4]);
-  const double w2 = r == 0 ? rc[2] : (r == 1 ? rc[4] : rc[5]);
-  return g - (w0 * rc[19] + w1 * rc[20] + w2 * rc[21]);
+  const int c = o + e / 3, r = e % 3;
+  const double *w = L.rec + PGS_RC * PGS_SMAX + c;
+  const double w0 = w[(r == 0 ? 0 : r == 1 ? 1 : 2) * PGS_SMAX];
+  const double w1 = w[(r == 0 ? 1 : r == 1 ? 3 : 4) * PGS_SMAX];
+  const double w2 = w[(r == 0 ? 2 : r == 1 ? 4 : 5) * PGS_SMAX];
+  return g - (w0 * L.lamS[3 * c] + w1 * L.lamS[3 * c + 1] + w2 * L.lamS[3 * c + 2]);
 }
 
 // Lead workgroup (see above).
@@ -2511,97 +2612,108 @@ __device__ void coop_lead(const CoopArgs &a, PgsLds &L, int sweep0) {
     // block 0 staged at contact 0 of the LDS arrays
     {
       const int nB = min(COOP_B, nc);
-      for (int e = tid; e < nB * 19; e += COOP_NT) L.rec[PGS_RW * (e / 19) + e % 19] = a.recAll[PGS_RW * (e / 19) + e % 19];
-      for (int e = tid; e < 3 * nB; e += COOP_NT) {
-        const double v = a.lam[e];
-        L.rec[PGS_RW * (e / 3) + 19 + e % 3] = v;
-        L.lamS0[e] = v;
-      }
+      for (int e = tid; e < nB * PGS_RW; e += COOP_NT)
+        L.rec[PGS_SMAX * (e / nB) + e % nB] = a.recAll[(long)nc * (e / nB) + e % nB];
+      for (int e = tid; e < 3 * nB; e += COOP_NT) L.lamS[e] = L.lamS0[e] = a.lam[e];
       __syncthreads();
       for (int e = tid; e < 3 * nB; e += COOP_NT) L.gS[e] = coop_own_free(L, 0, e, ld_dev(a.g + e));
       if (tid == 0) {
         L.cprog = 0;
         L.cflag = 0;
         L.stop = 0;
+        L.perr = 0;
       }
       __syncthreads();
     }
+    const int wu = __builtin_amdgcn_readfirstlane(wv);
     double dsum = 0.0, nl2 = 0.0;   // wave 0: sums of the sweep
     for (int s = 0; s < total; ++s) {
       const int b = s % nb, bn = (b + 1) % nb, p = s & 1;
       const int o = p ? COOP_B : 0, o1 = COOP_B - o;
       const int c0 = COOP_B * b, nB = min(COOP_B, nc - c0), nsp = pgs_wave_pad(nB);
       const int cn0 = COOP_B * bn, nBn = min(COOP_B, nc - cn0);
-      if (wv == 0) {
-        const double *Wb = a.Wblk + (long)b * blk_elems;
-        if (a.j_inner == 8) {
-          if (nsp == 64)
-            chain_wave<1, 8, true>(nB, Wb, L, a.j_inner, o);
-          else
-            chain_wave<2, 8, true>(nB, Wb, L, a.j_inner, o);
-        } else {
-          if (nsp == 64)
-            chain_wave<1, 0, true>(nB, Wb, L, a.j_inner, o);
-          else
-            chain_wave<2, 0, true>(nB, Wb, L, a.j_inner, o);
+      // waves 0-1: the chain of this block, each over its 64 contacts
+      if (64 * wu < min(nB, 128)) {
+        const BlkBuf buf(a.Wblk + (long)b * blk_elems, 8u * PGS_BLK * (unsigned)nsp * (unsigned)nB);
+        const int me = o + 64 * wu + ln;
+        const bool on = 64 * wu + ln < nB;
+        ChainLane c;
+        c.rc = pgs_rec_load(L, on ? me : o);
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+          c.e[q] = on ? L.gS[3 * me + q] : 0.0;
+          c.l[q] = on ? L.lamS[3 * me + q] : 0.0;
         }
-      } else if (wv == 4) {
-        // stage the next block's records and forces (unchanged by this chain)
-        for (int e = ln; e < nBn * 19; e += 64)
-          L.rec[PGS_RW * (o1 + e / 19) + e % 19] = a.recAll[PGS_RW * (long)(cn0 + e / 19) + e % 19];
-        for (int e = ln; e < 3 * nBn; e += 64) {
-          const double v = a.lam[3 * cn0 + e];
-          L.rec[PGS_RW * (o1 + e / 3) + 19 + e % 3] = v;
-          L.lamS0[3 * o1 + e] = v;
-        }
-        // every pushing workgroup finished block s - 1: the next block's gap
-        // rows hold all earlier changes, and list buffer p ^ 1 is free
-        for (int spin = 0;; ++spin) {
-          bool ok = true;
-          for (int w = 1 + ln; w < G; w += 64) ok &= ld_dev(a.sync + COOP_SYNC_PROG + w) >= s - 1;
-          if (__ballot(!ok) == 0ull) break;
-          if (spin == COOP_SPIN_DEV) {
-            if (ln == 0) st_dev(a.sync + COOP_SYNC_ERR, 1);
-            break;
-          }
-          __builtin_amdgcn_s_sleep(2);
-        }
-        __atomic_signal_fence(__ATOMIC_SEQ_CST);
-        if (ln == 0) st_wg(&L.cflag, 1);
+        if (a.j_inner == 8)
+          chain_sweep<8, true>(c, nB, nsp, buf, o, 0, L, a.j_inner, wu, ln);
+        else
+          chain_sweep<0, true>(c, nB, nsp, buf, o, 0, L, a.j_inner, wu, ln);
+        if (on) L.stS[me] = (unsigned char)c.st;
       }
-      // waves 1-3, 5-7: row f of the next block, f < 3 nBn
-      const bool follower = wv != 0 && wv != 4;
-      const int f = (wv < 4 ? wv - 1 : wv - 2) * 64 + ln;
+      // waves 2-7: row f of the next block, f < 3 nBn
+      const bool follower = wv >= 2;
+      const int f = 64 * (wv - 2) + ln;
       double acc = 0.0, gold = 0.0;
       bool have_g = false;
       if (follower) {
         const bool act = f < 3 * nBn;
         const long row = 3L * cn0 + (act ? f : 0);
-        for (int i = 0; i < nB; i += 4) {
-          double x[4][3];
+        // W~ rows of four contacts at a time, the next four in flight
+        auto load = [&](double (&x)[4][3], int i) {
 #pragma unroll
           for (int q = 0; q < 4; ++q) {
             const long c3 = 3L * (c0 + min(i + q, nB - 1));
 #pragma unroll
             for (int t = 0; t < 3; ++t) x[q][t] = (double)__builtin_nontemporal_load(W + (c3 + t) * m + row);
           }
-          const int need = min(i + 4, nB);
-          for (int spin = 0; ld_wg(&L.cprog) < need; ++spin) {
-            if (spin == COOP_SPIN_LDS) {
-              st_dev(a.sync + COOP_SYNC_ERR, 1);
+        };
+        double x[2][4][3];
+        load(x[0], 0);
+        load(x[1], 4);
+        // stage the next block's records and forces (unchanged by this chain)
+        for (int e = f; e < nBn * PGS_RW; e += COOP_NT - 128)
+          L.rec[PGS_SMAX * (e / nBn) + o1 + e % nBn] = a.recAll[(long)nc * (e / nBn) + cn0 + e % nBn];
+        if (act) L.lamS[3 * o1 + f] = L.lamS0[3 * o1 + f] = a.lam[3 * cn0 + f];
+        if (wv == 7) {
+          // every pushing workgroup finished block s - 1: the next block's gap
+          // rows hold all earlier changes, and list buffer p ^ 1 is free
+          for (int spin = 0;; ++spin) {
+            bool ok = true;
+            for (int w = 1 + ln; w < G; w += 64) ok &= ld_dev(a.sync + COOP_SYNC_PROG + w) >= s - 1;
+            if (__ballot(!ok) == 0ull) break;
+            if (spin == COOP_SPIN_DEV) {
+              if (ln == 0) st_dev(a.sync + COOP_SYNC_ERR, 1);
               break;
             }
-            __builtin_amdgcn_s_sleep(1);
+            __builtin_amdgcn_s_sleep(2);
           }
           __atomic_signal_fence(__ATOMIC_SEQ_CST);
+          if (ln == 0) st_wg(&L.cflag, 1);
+        }
+        for (int i = 0; i < nB; i += 8) {
 #pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            if (i + q < nB) {
-              const double *rc = L.rec + PGS_RW * (o + i + q) + 19;
-              const double *l0 = L.lamS0 + 3 * (o + i + q);
-              acc = fma(x[q][0], rc[0] - l0[0], acc);
-              acc = fma(x[q][1], rc[1] - l0[1], acc);
-              acc = fma(x[q][2], rc[2] - l0[2], acc);
+          for (int h = 0; h < 2; ++h) {
+            const int ih = i + 4 * h;
+            if (ih < nB) {
+              const int need = min(ih + 4, nB);
+              for (int spin = 0; ld_wg(&L.cprog) < need; ++spin) {
+                if (spin == COOP_SPIN_LDS) {
+                  st_dev(a.sync + COOP_SYNC_ERR, 1);
+                  break;
+                }
+                __builtin_amdgcn_s_sleep(1);
+              }
+              __atomic_signal_fence(__ATOMIC_SEQ_CST);
+#pragma unroll
+              for (int q = 0; q < 4; ++q) {
+                if (ih + q < nB) {
+                  const double *l = L.lamS + 3 * (o + ih + q), *l0 = L.lamS0 + 3 * (o + ih + q);
+                  acc = fma(x[h][q][0], l[0] - l0[0], acc);
+                  acc = fma(x[h][q][1], l[1] - l0[1], acc);
+                  acc = fma(x[h][q][2], l[2] - l0[2], acc);
+                }
+              }
+              load(x[h], ih + 8);
             }
           }
           if (!have_g && ld_wg(&L.cflag) != 0) {
@@ -2630,14 +2742,14 @@ __device__ void coop_lead(const CoopArgs &a, PgsLds &L, int sweep0) {
           const int i = i0 + ln;
           double d0 = 0.0, d1 = 0.0, d2 = 0.0, q2 = 0.0;
           if (i < nB) {
-            const double *rc = L.rec + PGS_RW * (o + i);
-            d0 = rc[19] - L.lamS0[3 * (o + i)];
-            d1 = rc[20] - L.lamS0[3 * (o + i) + 1];
-            d2 = rc[21] - L.lamS0[3 * (o + i) + 2];
-            q2 = rc[19] * rc[19] + rc[20] * rc[20] + rc[21] * rc[21];
-            a.lam[3 * (c0 + i)] = rc[19];
-            a.lam[3 * (c0 + i) + 1] = rc[20];
-            a.lam[3 * (c0 + i) + 2] = rc[21];
+            const double *l = L.lamS + 3 * (o + i), *l0 = L.lamS0 + 3 * (o + i);
+            d0 = l[0] - l0[0];
+            d1 = l[1] - l0[1];
+            d2 = l[2] - l0[2];
+            q2 = l[0] * l[0] + l[1] * l[1] + l[2] * l[2];
+            a.lam[3 * (c0 + i)] = l[0];
+            a.lam[3 * (c0 + i) + 1] = l[1];
+            a.lam[3 * (c0 + i) + 2] = l[2];
             a.status[c0 + i] = (int8_t)L.stS[o + i];
           }
           const bool ch = (d0 != 0.0) | (d1 != 0.0) | (d2 != 0.0);
@@ -2668,7 +2780,8 @@ __device__ void coop_lead(const CoopArgs &a, PgsLds &L, int sweep0) {
           stop = (eps <= a.tol || sweep >= a.max_sweeps) ? 1 : 0;
           dsum = nl2 = 0.0;
         }
-        if (ld_dev(a.sync + COOP_SYNC_ERR) != 0) stop = 1;
+        if (L.perr && ln == 0) st_dev(a.sync + COOP_SYNC_ERR, 1);   // the chain's waves lost their count
+        if (L.perr || ld_dev(a.sync + COOP_SYNC_ERR) != 0) stop = 1;
         if (ln == 0) {
           L.stop = stop;
           if (stop) a.sync[COOP_SYNC_STOP] = 1;
@@ -2727,7 +2840,7 @@ __device__ void coop_push(const CoopArgs &a, PgsLds &L) {
     if (L.stop) break;
     const int b = s % nb, bn = (b + 1) % nb, p = s & 1;
     const int nchg = ld_dev(a.sync + COOP_SYNC_CNT + p);
-    for (int e = tid; e < nchg; e += COOP_NT) L.ulist[e] = ld_dev(a.chg + COOP_B * p + e);
+    for (int e = tid; e < nchg; e += COOP_NT) L.ulist[e] = (unsigned short)ld_dev(a.chg + COOP_B * p + e);
     for (int e = tid; e < 3 * nchg; e += COOP_NT) L.lamSet[e] = ld_dev(a.dl + 3 * COOP_B * p + e);
     __syncthreads();
     if (nchg > 0)
@@ -2762,20 +2875,24 @@ __global__ __launch_bounds__(COOP_NT) void k_pgs_coop(CoopArgs a) {
     double wb[3][3];
     for (int p = 0; p < 3; ++p)
       for (int q = 0; q < 3; ++q) wb[p][q] = h2 * (double)W[(3 * c + p) * m + 3 * c + q];
-    double tmp[19];
-    make_record(wb, a.mu[c], tmp);
-    for (int q = 0; q < 19; ++q) a.recAll[PGS_RW * c + q] = tmp[q];
+    const PgsRec tmp = make_record(wb, a.mu[c]);
+    const double *x = reinterpret_cast<const double *>(&tmp);
+    for (int q = 0; q < PGS_RC; ++q) a.recAll[(long)q * nc + c] = x[q];
+    const double bw[6] = {wb[0][0], wb[0][1], wb[0][2], wb[1][1], wb[1][2], wb[2][2]};
+    for (int q = 0; q < 6; ++q) a.recAll[(long)(PGS_RC + q) * nc + c] = bw[q];
   }
   for (long e = gt; e < (long)nb * blk_elems; e += gthreads) {
     const int b = (int)(e / blk_elems);
     const long r = e % blk_elems;
     const int c0 = COOP_B * b, nB = min(COOP_B, nc - c0), nsp = pgs_wave_pad(nB);
-    const int j = (int)(r % PGS_BLK);
-    const long ic = r / PGS_BLK;
-    const int c = (int)(ic % nsp), i = (int)(ic / nsp);
+    const int per = nsp * PGS_BLK, i = (int)(r / per), rr = (int)(r % per);
+    int l, j;
+    blk_index(rr % BLK_GROUP, l, j);
+    const int c = 64 * (rr / BLK_GROUP) + l;
+    if (i >= nB) continue;
     double v = 0.0;
-    if (i < nB && j < 9 && c < nB && c != i) v = h2 * (double)W[(3L * (c0 + c) + j / 3) * m + 3L * (c0 + i) + j % 3];
-    if (i < nB) a.Wblk[(long)b * blk_elems + ((long)i * nsp + c) * PGS_BLK + j] = v;
+    if (c < nB && c != i) v = h2 * (double)W[(3L * (c0 + i) + j % 3) * m + 3L * (c0 + c) + j / 3];
+    a.Wblk[e] = v;
   }
   {
     // contacts with a force, in every workgroup's LDS (order is fixed); the
@@ -2786,7 +2903,7 @@ __global__ __launch_bounds__(COOP_NT) void k_pgs_coop(CoopArgs a) {
         const int c = c0 + ln;
         const bool nz = c < nc && (a.lam[3 * c] != 0.0 || a.lam[3 * c + 1] != 0.0 || a.lam[3 * c + 2] != 0.0);
         const unsigned long long bal = __ballot(nz);
-        if (nz) L.ulist[cnt + __popcll(bal & ((1ull << ln) - 1ull))] = c;
+        if (nz) L.ulist[cnt + __popcll(bal & ((1ull << ln) - 1ull))] = (unsigned short)c;
         cnt += __popcll(bal);
       }
       if (ln == 0) L.nu = cnt;

@@ -307,14 +307,14 @@ template <class TW>
 void launch_update_W(hipStream_t st, int nc, const TW *WH, const double *C, TW *W);
 constexpr int kPgsMaxContacts = 4096;
 constexpr int kMaxNewton = 256;   // Newton iterations per step (per-iteration sweeps, eps, stamps)
-// Layout of the PGS work buffers: per-contact records of kPgsRecWidth
-// doubles, the blocked coupling matrix of an active set of up to kPgsWaveMax
-// contacts in 3x3 blocks of kPgsBlk doubles, padded to pgs_wave_pad contacts.
-constexpr int kPgsRecWidth = 22;
+// Layout of the PGS work buffers: per-contact records of kPgsRecWidth rows,
+// the blocked coupling matrix of an active set of up to kPgsWaveMax contacts
+// in 3x3 blocks of kPgsBlk doubles, padded to pgs_wave_pad contacts.
+constexpr int kPgsRecWidth = 20;
 constexpr int kPgsWaveMax = 512;
-constexpr int kPgsBlk = 10;
-// 64 contacts per register slot, two slots per chain wave beyond 64 contacts
-__host__ __device__ constexpr inline int pgs_wave_pad(int nS) { return nS <= 64 ? 64 : 128 * ((nS + 127) / 128); }
+constexpr int kPgsBlk = 9;
+constexpr int kPgsAhead = 4;   // columns of it in flight ahead of a sweep
+__host__ __device__ constexpr inline int pgs_wave_pad(int nS) { return 64 * ((nS + 63) / 64); }
 // doubles of the blocked coupling matrix of an active set (n_c contacts)
 constexpr inline size_t pgs_wss_elems(int nc) {
   return (size_t)(nc < kPgsWaveMax ? nc : kPgsWaveMax) * pgs_wave_pad(nc < kPgsWaveMax ? nc : kPgsWaveMax) * kPgsBlk;
