@@ -237,9 +237,6 @@ void prepare_factor(icr_scene *s) {
       L.max_n3 = std::max(L.max_n3, n3);
       L.max_f3 = std::max(L.max_f3, f);
       L.max_b3 = std::max(L.max_b3, b3);
-      L.max_f2 = std::max<long long>(L.max_f2, (long long)f * f);
-      L.max_rows_tiles = std::max(L.max_rows_tiles, cdiv(n3, TILE));
-      L.max_below_tiles = std::max(L.max_below_tiles, cdiv(b3, TILE));
     }
   }
   // single-RHS task lists: every (supernode, block) of a level that exists;
@@ -272,6 +269,14 @@ void prepare_factor(icr_scene *s) {
   for (int s_ = 0; s_ < ns; ++s_)
     for (int p = sym.col0[s_]; p < sym.col0[s_] + sym.ncol[s_]; ++p) sup_of_node[sym.perm[p]] = s_;
 
+  std::vector<int> by_tiles(ns);
+  std::iota(by_tiles.begin(), by_tiles.end(), 0);
+  auto tiles = [&](int s_) { return cdiv(3 * F.sup[s_].ncol, TILE); };
+  std::stable_sort(by_tiles.begin(), by_tiles.end(), [&](int u, int v) { return tiles(u) > tiles(v); });
+  F.tiles_desc.resize(ns);
+  for (int q = 0; q < ns; ++q) F.tiles_desc[q] = tiles(by_tiles[q]);
+  F.max_tiles = F.tiles_desc[0];
+
   s->fac_arena.release();
   F.rhs_arena.release();
   F.nc_cap = 0;
@@ -287,6 +292,7 @@ void prepare_factor(icr_scene *s) {
   F.d_invmap_off = A.upload(invmap_off, st);
   F.d_invmap = A.upload(invmap, st);
   F.d_level_sup = A.upload(sym.level_sup, st);
+  F.d_sup_by_tiles = A.upload(by_tiles, st);
   F.d_perm = A.upload(sym.perm, st);
   F.d_iperm = A.upload(sym.iperm, st);
   F.d_sup_of_node = A.upload(sup_of_node, st);

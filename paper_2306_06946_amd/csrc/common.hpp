@@ -29,128 +29,7 @@ struct HipError : std::runtime_error {
 constexpr int TILE = 64;   // output tile edge of the FP64 GEMM tiles
 constexpr int KT = 16;     // K-chunk staged in LDS per iteration
 
-// ---------------------------------------------------------------------------
-// 64x64 FP64 MFMA tile accumulators.  Each exposes for_each(f) visiting the
-// tile-local (i, j) of every value the calling thread owns.
-// ---------------------------------------------------------------------------
-
 typedef double mfma_d4 __attribute__((ext_vector_type(4)));
-
-// MFMA layout (v_mfma_f64_16x16x4f64, checked on gfx950): A(i, k) comes from
-// lane i + 16 k, B(k, j) from lane j + 16 k, and D(i, j) lands in lane
-// j + 16 (i % 4), register i / 4.  Wave w owns the 32x32 quadrant
-// (32 (w >> 1), 32 (w & 1)) as 2x2 blocks of 16x16.
-struct AccM {
-  mfma_d4 c[2][2];
-  __device__ void zero() {
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-      for (int b = 0; b < 2; ++b) c[a][b] = mfma_d4{0.0, 0.0, 0.0, 0.0};
-  }
-  __device__ void acc(const double *A, long ars, long acs, const double *B, long brs, long bcs, int M, int N, int k0,
-                      int k1, double *sA, double *sB);
-  template <class F>
-  __device__ void for_each(F &&f) {
-    const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-    const int r0 = 32 * (w >> 1), c0 = 32 * (w & 1);
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-      for (int b = 0; b < 2; ++b)
-#pragma unroll
-        for (int t = 0; t < 4; ++t) f(r0 + 16 * a + 4 * t + (l >> 4), c0 + 16 * b + (l & 15), c[a][b][t]);
-  }
-};
-
-// Register-prefetched staging: the next K-chunk is fetched from global memory
-// into registers while the MFMAs of the current chunk run from LDS.
-__device__ inline void load_chunk_regs(const double *__restrict__ A, long ars, long acs, const double *__restrict__ B,
-                                       long brs, long bcs, int M, int N, int kb, int k1, double ra[4],
-                                       double rb[4]) {
-  const int tid = threadIdx.x;
-  const bool a_rowfast = (ars == 1);
-  const bool b_colfast = (bcs == 1);
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    int e = tid + 256 * q;
-    int i, k;
-    if (a_rowfast) {
-      i = e & 63;
-      k = e >> 6;
-    } else {
-      k = e & 15;
-      i = e >> 4;
-    }
-    int kk = kb + k;
-    ra[q] = (i < M && kk < k1) ? A[(long)i * ars + (long)kk * acs] : 0.0;
-    int j;
-    if (b_colfast) {
-      j = e & 63;
-      k = e >> 6;
-    } else {
-      k = e & 15;
-      j = e >> 4;
-    }
-    kk = kb + k;
-    rb[q] = (j < N && kk < k1) ? B[(long)kk * brs + (long)j * bcs] : 0.0;
-  }
-}
-
-__device__ inline void store_chunk_lds(bool a_rowfast, bool b_colfast, const double ra[4], const double rb[4],
-                                       double *sA, double *sB) {
-  const int tid = threadIdx.x;
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    int e = tid + 256 * q;
-    int i, k;
-    if (a_rowfast) {
-      i = e & 63;
-      k = e >> 6;
-    } else {
-      k = e & 15;
-      i = e >> 4;
-    }
-    sA[k * TILE + i] = ra[q];
-    int j;
-    if (b_colfast) {
-      j = e & 63;
-      k = e >> 6;
-    } else {
-      k = e & 15;
-      j = e >> 4;
-    }
-    sB[k * TILE + j] = rb[q];
-  }
-}
-
-__device__ inline void AccM::acc(const double *A, long ars, long acs, const double *B, long brs, long bcs, int M,
-                                 int N, int k0, int k1, double *sA, double *sB) {
-  const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-  const int r0 = 32 * (w >> 1), c0 = 32 * (w & 1);
-  const int li = l & 15, lk = l >> 4;
-  const bool a_rowfast = (ars == 1), b_colfast = (bcs == 1);
-  if (k0 >= k1) return;
-  double ra[4], rb[4];
-  load_chunk_regs(A, ars, acs, B, brs, bcs, M, N, k0, k1, ra, rb);
-  for (int kb = k0; kb < k1; kb += KT) {
-    store_chunk_lds(a_rowfast, b_colfast, ra, rb, sA, sB);
-    __syncthreads();
-    if (kb + KT < k1) load_chunk_regs(A, ars, acs, B, brs, bcs, M, N, kb + KT, k1, ra, rb);
-#pragma unroll
-    for (int kk = 0; kk < KT; kk += 4) {
-      const int k = kk + lk;
-      double a0 = sA[k * TILE + r0 + li], a1 = sA[k * TILE + r0 + 16 + li];
-      double b0 = sB[k * TILE + c0 + li], b1 = sB[k * TILE + c0 + 16 + li];
-      c[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b0, c[0][0], 0, 0, 0);
-      c[0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b1, c[0][1], 0, 0, 0);
-      c[1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b0, c[1][0], 0, 0, 0);
-      c[1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b1, c[1][1], 0, 0, 0);
-    }
-    __syncthreads();
-  }
-}
-
 typedef float mfma_f4 __attribute__((ext_vector_type(4)));
 
 // One 16x16x4 MFMA per element type: FP64 (v_mfma_f64_16x16x4f64) or FP32
@@ -271,10 +150,6 @@ struct AccMT {
 };
 typedef AccMT<2, 32> AccS;          // 64 x 64 FP64, K-chunk 32
 typedef AccMT<2, 32, float> AccS32;  // 64 x 64 FP32, K-chunk 32
-
-// The tile accumulator of the factor kernels.
-typedef AccM Acc;
-
 
 // Lower-triangle tile index x -> (I, J), I >= J, row-major over the triangle.
 __device__ inline void tri_index(int x, int &I, int &J) {

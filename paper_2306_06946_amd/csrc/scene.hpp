@@ -44,9 +44,6 @@ struct LevelInfo {
   int max_n3 = 0;             // max DOF columns of a supernode
   int max_f3 = 0;             // max front order
   int max_b3 = 0;             // max below rows (DOF)
-  long long max_f2 = 0;       // max f^2
-  int max_rows_tiles = 0;     // max ceil(n3/64)
-  int max_below_tiles = 0;    // max ceil(b3/64)
   int a_first = 0, a_count = 0;   // A-scatter entries of the level
   int child_rank_max = 0;
   int fwd_split_diag = 1, fwd_split_off = 1;   // k-chunks of the split single-RHS forward products
@@ -81,6 +78,9 @@ struct Factor {
   std::vector<LevelInfo> levels;
   SupDev *d_sup = nullptr;
   int *d_rows = nullptr, *d_child = nullptr, *d_invmap_off = nullptr, *d_invmap = nullptr;
+  int *d_sup_by_tiles = nullptr;   // supernodes by descending number of 64-column tiles
+  std::vector<int> tiles_desc;     // those numbers
+  int max_tiles = 0;
   int *d_level_sup = nullptr, *d_perm = nullptr, *d_iperm = nullptr, *d_sup_of_node = nullptr;
   AScatter *d_ascat = nullptr;
   double *d_front = nullptr, *d_linv = nullptr, *d_x1 = nullptr;
