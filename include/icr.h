@@ -17,7 +17,8 @@
  *   - "host" pointers are read during the call and copied; "device" pointers
  *     are caller-owned GPU buffers (e.g. torch tensors) that the library never
  *     frees.  Library-owned device memory (mesh, factor, work arenas, state)
- *     lives until icr_destroy.
+ *     lives until icr_destroy; up to 4 GiB of it then stays with the process
+ *     for the next scene (icr_release_idle gives it back).
  *   - Device work is enqueued on the scene's stream (icr_create).  Calls that
  *     return host values (sweeps, eps, reports) synchronise that stream.
  *   - Arrays are row-major, float64 unless stated; node ids are int32,
@@ -66,6 +67,10 @@ icr_status icr_create(icr_scene **out, void *stream);
 
 /* Free every library-owned buffer.  Safe on NULL. */
 void icr_destroy(icr_scene *s);
+/* Frees the device memory that destroyed scenes left for the next ones (any
+ * thread; scenes in use are not touched).  An allocation that fails does the
+ * same for its device by itself. */
+void icr_release_idle(void);
 
 /* Last error message of this scene ("" if none); valid until the next call. */
 const char *icr_last_error(const icr_scene *s);

@@ -2,8 +2,8 @@
 // node graph of the tetrahedral mesh, nested-dissection ordering and the
 // supernodal elimination structure that the dissection tree implies.
 //
-// Ordering: recursive coordinate bisection.  At each region the nodes are
-// sorted along the axis of largest extent and cut near the median at the
+// Ordering: recursive coordinate bisection.  At each region the nodes, kept
+// sorted along every axis, are taken along the axis of largest extent and cut near the median at the
 // widest coordinate gap (between grid layers for the jittered grids); the
 // vertex separator is the smaller of the two one-sided boundaries of the cut.
 // Regions are numbered children first, separator last, so every supernode's
@@ -15,6 +15,7 @@
 // supernode; explicit zeros are stored and computed, which keeps the factor
 // exact (relaxed supernodes = dissection tree nodes).
 #include <algorithm>
+#include <array>
 #include <cmath>
 #include <numeric>
 #include <sstream>
@@ -27,21 +28,35 @@ namespace icr {
 MeshGraph build_graph(int N, const int32_t *tets, int T) {
   MeshGraph g;
   g.N = N;
-  std::vector<std::vector<int>> nb(N);
-  for (int i = 0; i < N; ++i) nb[i].push_back(i);
-  for (int t = 0; t < T; ++t)
-    for (int a = 0; a < 4; ++a)
-      for (int b = 0; b < 4; ++b)
-        if (a != b) nb[tets[4 * t + a]].push_back(tets[4 * t + b]);
-  g.ptr.assign(N + 1, 0);
-  for (int i = 0; i < N; ++i) {
-    auto &v = nb[i];
-    std::sort(v.begin(), v.end());
-    v.erase(std::unique(v.begin(), v.end()), v.end());
-    g.ptr[i + 1] = g.ptr[i] + (int)v.size();
+  // incidences by counting, ascending element order per node
+  g.inc_ptr.assign(N + 1, 0);
+  for (long e = 0; e < 4L * T; ++e) g.inc_ptr[tets[e] + 1]++;
+  for (int i = 0; i < N; ++i) g.inc_ptr[i + 1] += g.inc_ptr[i];
+  g.inc.resize(4L * T);
+  {
+    std::vector<int> at(g.inc_ptr.begin(), g.inc_ptr.end() - 1);
+    for (long e = 0; e < 4L * T; ++e) g.inc[at[tets[e]]++] = (int)e;
   }
-  g.adj.resize(g.ptr[N]);
-  for (int i = 0; i < N; ++i) std::copy(nb[i].begin(), nb[i].end(), g.adj.begin() + g.ptr[i]);
+  // neighbours of a node: the distinct nodes of its elements (a stamp per
+  // node tells which were met)
+  g.ptr.assign(N + 1, 0);
+  g.adj.reserve(16L * N);
+  std::vector<int> met(N, -1);
+  for (int i = 0; i < N; ++i) {
+    const size_t first = g.adj.size();
+    g.adj.push_back(i);
+    met[i] = i;
+    for (int e = g.inc_ptr[i]; e < g.inc_ptr[i + 1]; ++e) {
+      const int32_t *tet = tets + 4L * (g.inc[e] / 4);
+      for (int b = 0; b < 4; ++b)
+        if (met[tet[b]] != i) {
+          met[tet[b]] = i;
+          g.adj.push_back(tet[b]);
+        }
+    }
+    std::sort(g.adj.begin() + first, g.adj.end());
+    g.ptr[i + 1] = (int)g.adj.size();
+  }
   return g;
 }
 
@@ -51,6 +66,7 @@ struct ND {
   const double *xyz;
   const MeshGraph *g;
   int leaf_max;
+  double reach[3] = {0.0, 0.0, 0.0};   // longest edge along each axis
   std::vector<int> stamp;   // region marker
   int cur = 0;
   Symbolic *sym;
@@ -69,25 +85,26 @@ struct ND {
     return s;
   }
 
-  int rec(std::vector<int> nodes) {
-    const int n = (int)nodes.size();
+  // The region's nodes sorted along each axis (coordinate, then id): the lists
+  // of the root are sorted once and split stably on the way down.
+  typedef std::array<std::vector<int>, 3> Sorted;
+
+  int rec(Sorted by) {
+    const int n = (int)by[0].size();
     if (n <= leaf_max) {
-      std::sort(nodes.begin(), nodes.end());
-      return make_sup(nodes, {});
+      std::sort(by[0].begin(), by[0].end());
+      return make_sup(by[0], {});
     }
-    double lo[3] = {1e300, 1e300, 1e300}, hi[3] = {-1e300, -1e300, -1e300};
-    for (int v : nodes)
-      for (int a = 0; a < 3; ++a) {
-        lo[a] = std::min(lo[a], xyz[3 * v + a]);
-        hi[a] = std::max(hi[a], xyz[3 * v + a]);
-      }
     int ax = 0;
-    for (int a = 1; a < 3; ++a)
-      if (hi[a] - lo[a] > hi[ax] - lo[ax]) ax = a;
-    std::stable_sort(nodes.begin(), nodes.end(), [&](int u, int v) {
-      double cu = xyz[3 * u + ax], cv = xyz[3 * v + ax];
-      return cu < cv || (cu == cv && u < v);
-    });
+    double ext = -1.0;
+    for (int a = 0; a < 3; ++a) {
+      const double e = xyz[3 * by[a].back() + a] - xyz[3 * by[a].front() + a];
+      if (a == 0 || e > ext) {
+        ax = a;
+        ext = e;
+      }
+    }
+    const std::vector<int> &nodes = by[ax];
     int k0 = std::max(1, (int)(0.35 * n)), k1 = std::min(n - 1, (int)(0.65 * n));
     int best = n / 2;
     double bgap = -1.0;
@@ -99,57 +116,44 @@ struct ND {
         best = k;
       }
     }
-    // mark right side
-    ++cur;
-    const int right = cur;
-    for (int k = best; k < n; ++k) stamp[nodes[k]] = right;
+    // sides of the cut; the separator is the smaller one-sided boundary
+    const int left = ++cur, right = ++cur;
+    for (int k = 0; k < n; ++k) stamp[nodes[k]] = k < best ? left : right;
+    // (no edge is longer along the axis than reach, so only nodes that close to
+    // the other side can have a neighbour there)
+    auto at_cut = [&](int v, int other, std::vector<int> &sep) {
+      for (int e = g->ptr[v]; e < g->ptr[v + 1]; ++e)
+        if (stamp[g->adj[e]] == other) {
+          sep.push_back(v);
+          return;
+        }
+    };
     std::vector<int> sepL, sepR;
-    ++cur;
-    const int left = cur;
-    for (int k = 0; k < best; ++k) stamp[nodes[k]] = left;
-    for (int k = 0; k < best; ++k) {
-      int v = nodes[k];
-      for (int e = g->ptr[v]; e < g->ptr[v + 1]; ++e)
-        if (stamp[g->adj[e]] == right) {
-          sepL.push_back(v);
-          break;
-        }
+    const double xl = xyz[3 * nodes[best - 1] + ax], xr = xyz[3 * nodes[best] + ax];
+    for (int k = best - 1; k >= 0 && xr - xyz[3 * nodes[k] + ax] <= reach[ax]; --k) at_cut(nodes[k], right, sepL);
+    for (int k = best; k < n && xyz[3 * nodes[k] + ax] - xl <= reach[ax]; ++k) at_cut(nodes[k], left, sepR);
+    std::vector<int> S = sepL.size() <= sepR.size() ? std::move(sepL) : std::move(sepR);
+    const int sepmark = ++cur;
+    if (S.empty()) {   // disconnected halves: any single node separates them
+      S.push_back(best > 0 ? nodes[best - 1] : nodes[n - 1]);
     }
-    for (int k = best; k < n; ++k) {
-      int v = nodes[k];
-      for (int e = g->ptr[v]; e < g->ptr[v + 1]; ++e)
-        if (stamp[g->adj[e]] == left) {
-          sepR.push_back(v);
-          break;
-        }
-    }
-    std::vector<int> A, B, S;
-    bool useL = sepL.size() <= sepR.size();
-    ++cur;
-    const int sepmark = cur;
-    for (int v : (useL ? sepL : sepR)) stamp[v] = sepmark;
-    for (int k = 0; k < n; ++k) {
-      int v = nodes[k];
-      if (stamp[v] == sepmark)
-        S.push_back(v);
-      else if (k < best)
-        A.push_back(v);
-      else
-        B.push_back(v);
-    }
-    if (S.empty()) {  // disconnected halves: any single node separates them
-      if (!A.empty()) {
-        S.push_back(A.back());
-        A.pop_back();
-      } else {
-        S.push_back(B.back());
-        B.pop_back();
+    for (int v : S) stamp[v] = sepmark;
+    Sorted A, B;
+    for (int a = 0; a < 3; ++a) {
+      A[a].reserve(best);
+      B[a].reserve(n - best);
+      for (int v : by[a]) {
+        if (stamp[v] == left)
+          A[a].push_back(v);
+        else if (stamp[v] == right)
+          B[a].push_back(v);
       }
+      std::vector<int>().swap(by[a]);
     }
     std::sort(S.begin(), S.end());
     std::vector<int> children;
-    if (!A.empty()) children.push_back(rec(std::move(A)));
-    if (!B.empty()) children.push_back(rec(std::move(B)));
+    if (!A[0].empty()) children.push_back(rec(std::move(A)));
+    if (!B[0].empty()) children.push_back(rec(std::move(B)));
     return make_sup(S, children);
   }
 };
@@ -166,6 +170,10 @@ void analyze(const double *xyz, const MeshGraph &g, int leaf_max, Symbolic &sym)
   nd.g = &g;
   nd.leaf_max = leaf_max;
   nd.stamp.assign(N, 0);
+  for (int v = 0; v < N; ++v)
+    for (int e = g.ptr[v]; e < g.ptr[v + 1]; ++e)
+      for (int a = 0; a < 3; ++a)
+        nd.reach[a] = std::max(nd.reach[a], std::fabs(xyz[3 * v + a] - xyz[3 * g.adj[e] + a]));
   nd.sym = &sym;
   // connected components are dissected separately and become sibling roots
   std::vector<int> comp(N, -1);
@@ -188,7 +196,18 @@ void analyze(const double *xyz, const MeshGraph &g, int leaf_max, Symbolic &sym)
     }
     comps.push_back(std::move(members));
   }
-  for (auto &c : comps) nd.rec(c);
+  std::vector<std::pair<double, int>> key;
+  for (auto &c : comps) {
+    ND::Sorted by;
+    for (int a = 0; a < 3; ++a) {
+      key.clear();
+      for (int v : c) key.emplace_back(xyz[3 * v + a], v);
+      std::sort(key.begin(), key.end());
+      by[a].reserve(c.size());
+      for (const auto &k : key) by[a].push_back(k.second);
+    }
+    nd.rec(std::move(by));
+  }
   sym.iperm.assign(N, -1);
   for (int p = 0; p < N; ++p) sym.iperm[sym.perm[p]] = p;
 
@@ -199,26 +218,37 @@ void analyze(const double *xyz, const MeshGraph &g, int leaf_max, Symbolic &sym)
   for (int s = 0; s < ns; ++s)
     for (int c : nd.kids[s]) sym.child.push_back(c);
 
-  // below rows: nodes outside the region adjacent to it (all later in the order)
+  // below rows: nodes outside the region adjacent to it (all later in the
+  // order): those of the children that lie outside, and the outside neighbours
+  // of the own columns
   sym.rows_ptr.assign(ns + 1, 0);
   sym.rows.clear();
   std::vector<int> mark(N, -1);
   for (int s = 0; s < ns; ++s) {
-    int rlo = sym.col0[sym.first_desc[s]], rhi = sym.col0[s] + sym.ncol[s];
-    std::vector<int> r;
-    for (int p = rlo; p < rhi; ++p) {
-      int v = sym.perm[p];
-      for (int e = g.ptr[v]; e < g.ptr[v + 1]; ++e) {
-        int q = sym.iperm[g.adj[e]];
+    const int rlo = sym.col0[sym.first_desc[s]], c0 = sym.col0[s], rhi = c0 + sym.ncol[s];
+    const size_t first = sym.rows.size();
+    for (int e = sym.child_ptr[s]; e < sym.child_ptr[s + 1]; ++e) {
+      const int c = sym.child[e];
+      for (int i = sym.rows_ptr[c]; i < sym.rows_ptr[c + 1]; ++i) {
+        const int q = sym.rows[i];
         if (q >= rhi && mark[q] != s) {
           mark[q] = s;
-          r.push_back(q);
+          sym.rows.push_back(q);
+        }
+      }
+    }
+    for (int p = c0; p < rhi; ++p) {
+      const int v = sym.perm[p];
+      for (int e = g.ptr[v]; e < g.ptr[v + 1]; ++e) {
+        const int q = sym.iperm[g.adj[e]];
+        if (q >= rhi && mark[q] != s) {
+          mark[q] = s;
+          sym.rows.push_back(q);
         }
         if (q < rlo) throw std::runtime_error("dissection: region adjacent to an earlier node");
       }
     }
-    std::sort(r.begin(), r.end());
-    sym.rows.insert(sym.rows.end(), r.begin(), r.end());
+    std::sort(sym.rows.begin() + first, sym.rows.end());
     sym.rows_ptr[s + 1] = (int)sym.rows.size();
   }
   // heights and levels
@@ -265,10 +295,11 @@ std::string check_symbolic(const MeshGraph &g, const Symbolic &sym) {
     if (p >= 0) {
       // child's below rows must be columns or below rows of the parent
       int pc0 = sym.col0[p], pc1 = pc0 + sym.ncol[p];
+      int at = sym.rows_ptr[p];   // both row lists ascend
       for (int e = sym.rows_ptr[s]; e < sym.rows_ptr[s + 1]; ++e) {
         int r = sym.rows[e];
-        bool ok = (r >= pc0 && r < pc1) ||
-                  std::binary_search(sym.rows.begin() + sym.rows_ptr[p], sym.rows.begin() + sym.rows_ptr[p + 1], r);
+        while (at < sym.rows_ptr[p + 1] && sym.rows[at] < r) ++at;
+        bool ok = (r >= pc0 && r < pc1) || (at < sym.rows_ptr[p + 1] && sym.rows[at] == r);
         if (!ok) {
           err << "row " << r << " of supernode " << s << " missing in parent " << p;
           return err.str();

@@ -1,15 +1,123 @@
 // C ABI entry points (include/icr.h): argument checks, host planning, and the
 // launch sequence of each call on the scene's stream.
 #include <algorithm>
+#include <chrono>
 #include <cmath>
 #include <cstring>
 #include <exception>
+#include <mutex>
 #include <numeric>
 
 #include "scene.hpp"
 #include "server_hooks.hpp"
 
 using namespace icr;
+
+namespace icr {
+
+// Idle device blocks.  A program that loads scene after scene asks for the
+// same few gigabytes each time, and the driver clears what is freed before it
+// hands it out again: set-ups of 28 ms each at 61 236 DOF (3.5 GB) fell to
+// 96 ms once the cleared memory was used up.  At most kIdleBytes per device
+// stay idle, the oldest go first, a block idle for kIdleSeconds goes with the
+// next allocation or release, and all of a device's go when an allocation
+// fails.  A block is kept only if its scene waited for its own streams and was
+// never moved to another (a wait for the device would end any stream capture
+// of the process); so every stream may use it next.  Others are freed.
+namespace {
+constexpr size_t kIdleBytes = size_t(4) << 30;
+constexpr double kIdleSeconds = 10.0;
+struct IdleBlock {
+  DeviceBlock b;
+  std::chrono::steady_clock::time_point since;
+};
+struct Idle {
+  std::mutex mtx;
+  std::vector<IdleBlock> blocks;   // oldest first
+  template <class F>
+  void drop(F &&which) {   // frees the blocks for which which(block) holds
+    size_t k = 0;
+    for (size_t i = 0; i < blocks.size(); ++i) {
+      if (which(blocks[i]))
+        (void)hipFree(blocks[i].b.p);
+      else
+        blocks[k++] = blocks[i];
+    }
+    blocks.resize(k, IdleBlock{});
+  }
+  void drop_old() {
+    const auto now = std::chrono::steady_clock::now();
+    drop([&](const IdleBlock &i) { return std::chrono::duration<double>(now - i.since).count() > kIdleSeconds; });
+  }
+};
+Idle &idle() {   // lives as long as the process: the runtime may be gone before static destructors
+  static Idle *i = new Idle;
+  return *i;
+}
+}  // namespace
+
+DeviceBlock device_alloc(size_t bytes) {
+  int dev = 0;
+  ICR_HIP(hipGetDevice(&dev));
+  const size_t grain = bytes < (size_t(1) << 20) ? 4096 : size_t(65536);
+  const size_t size = (bytes + grain - 1) / grain * grain;
+  Idle &I = idle();
+  {
+    std::lock_guard<std::mutex> lock(I.mtx);
+    I.drop_old();
+    size_t best = I.blocks.size();   // the smallest that fits, an eighth too large at most
+    for (size_t i = 0; i < I.blocks.size(); ++i) {
+      const DeviceBlock &b = I.blocks[i].b;
+      if (b.dev == dev && b.size >= size && b.size <= size + size / 8 &&
+          (best == I.blocks.size() || b.size < I.blocks[best].b.size))
+        best = i;
+    }
+    if (best < I.blocks.size()) {
+      const DeviceBlock b = I.blocks[best].b;
+      I.blocks.erase(I.blocks.begin() + best);
+      return b;
+    }
+  }
+  void *p = nullptr;
+  hipError_t e = hipMalloc(&p, size);
+  if (e != hipSuccess) {
+    (void)hipGetLastError();
+    std::lock_guard<std::mutex> lock(I.mtx);
+    I.drop([&](const IdleBlock &i) { return i.b.dev == dev; });
+    e = hipMalloc(&p, size);
+  }
+  if (e != hipSuccess) throw HipError(e, "hipMalloc(" + std::to_string(size) + " bytes)");
+  return DeviceBlock{p, size, dev};
+}
+
+void device_release(const std::vector<DeviceBlock> &blocks, bool settled) {
+  Idle &I = idle();
+  std::lock_guard<std::mutex> lock(I.mtx);
+  I.drop_old();
+  const auto now = std::chrono::steady_clock::now();
+  for (const DeviceBlock &b : blocks) {
+    bool kept = false;
+    if (settled && b.size <= kIdleBytes) {
+      size_t held = 0;
+      for (const IdleBlock &i : I.blocks) held += i.b.dev == b.dev ? i.b.size : 0;
+      size_t over = held + b.size > kIdleBytes ? held + b.size - kIdleBytes : 0;
+      if (over)
+        I.drop([&](const IdleBlock &i) {
+          if (over == 0 || i.b.dev != b.dev) return false;
+          over -= std::min(over, i.b.size);
+          return true;
+        });
+      try {
+        I.blocks.push_back(IdleBlock{b, now});
+        kept = true;
+      } catch (...) {
+      }
+    }
+    if (!kept) (void)hipFree(b.p);
+  }
+}
+
+}  // namespace icr
 
 namespace {
 
@@ -60,7 +168,7 @@ void ensure_contact_buffers(icr_scene *s, int nc) {
   if (nc <= C.nc_cap) return;
   s->epoch++;
   ICR_HIP(hipStreamSynchronize(s->stream));
-  C.arena.release();
+  C.arena.release(s->settle());
   const long m = 3L * nc;
   C.d_nodes_c = C.arena.alloc<int>(nc);
   C.d_mu = C.arena.alloc<double>(nc);
@@ -110,7 +218,7 @@ void ensure_pair_step(icr_scene *s, int nc) {
   if (Pr.count == 0 || Pr.step_nc == nc) return;
   ICR_HIP(hipStreamSynchronize(s->stream));
   s->epoch++;
-  Pr.step_arena.release();
+  Pr.step_arena.release(s->settle());
   const int P = Pr.count, nu = Pr.nu + nc - P;
   std::vector<int> idx(4L * nc, -1);
   std::vector<double> w(4L * nc, 0.0);
@@ -166,61 +274,57 @@ void prepare_factor(icr_scene *s) {
     lo += n3 * n3;
     xo += f;
     F.nnzL += n3 * (n3 + 1) / 2 + (f - n3) * n3;
-    for (long long c = 0; c < n3; ++c) F.flops += (double)(f - c) * (double)(f - c);
+    // sum over the columns of (f - c)^2
+    auto squares = [](double k) { return k * (k + 1.0) * (2.0 * k + 1.0) / 6.0; };
+    F.flops += squares((double)f) - squares((double)(f - n3));
     F.max_front = std::max<int>(F.max_front, (int)f);
   }
   F.front_elems = fo;
   F.linv_elems = lo;
   F.x1_elems = xo;
-  // child index maps (parent local node -> child below-row index, or -1)
-  std::vector<int> invmap_off(sym.child.size()), invmap;
-  for (int p = 0; p < ns; ++p) {
-    const SupDev &P = F.sup[p];
-    const int np = P.ncol + P.nb;
-    for (int e = sym.child_ptr[p]; e < sym.child_ptr[p + 1]; ++e) {
-      const int c = sym.child[e];
-      invmap_off[e] = (int)invmap.size();
-      invmap.resize(invmap.size() + np, -1);
-      int *inv = invmap.data() + invmap_off[e];
-      for (int i = sym.rows_ptr[c]; i < sym.rows_ptr[c + 1]; ++i) {
-        int r = sym.rows[i];
-        int L;
-        if (r >= P.col0 && r < P.col0 + P.ncol)
-          L = r - P.col0;
-        else {
-          auto it = std::lower_bound(sym.rows.begin() + sym.rows_ptr[p], sym.rows.begin() + sym.rows_ptr[p + 1], r);
-          L = P.ncol + (int)(it - (sym.rows.begin() + sym.rows_ptr[p]));
-        }
-        inv[L] = i - sym.rows_ptr[c];
-      }
-    }
+  // child index maps (parent local node -> child below-row index, or -1), and
+  // the A -> front scatter entries, grouped by level; local[q]: index of
+  // permuted node q in the front of the supernode at hand
+  std::vector<int> invmap_off(sym.child.size()), invmap, local(m.N, -1);
+  {
+    size_t total = 0;
+    for (int p = 0; p < ns; ++p) total += (size_t)(F.sup[p].ncol + F.sup[p].nb) * F.sup[p].nchild;
+    invmap.assign(total, -1);
   }
-  // A -> front scatter entries, grouped by level
+  // block (u, v) of the BSR matrix for entry (v, u): the pattern is symmetric,
+  // so walking the rows in order meets row u's entries in column order
+  std::vector<int> mirror(g.ptr[g.N]);
+  {
+    std::vector<int> at(g.ptr.begin(), g.ptr.end() - 1);
+    for (int v = 0; v < g.N; ++v)
+      for (int e = g.ptr[v]; e < g.ptr[v + 1]; ++e) mirror[e] = at[g.adj[e]]++;
+  }
   std::vector<std::vector<AScatter>> per_level(sym.nlevels);
-  std::vector<int> bsr_ptr(g.ptr.begin(), g.ptr.end());
+  int next_map = 0;
   for (int s_ = 0; s_ < ns; ++s_) {
     const SupDev &S = F.sup[s_];
+    const int np = S.ncol + S.nb;
+    for (int i = 0; i < S.ncol; ++i) local[S.col0 + i] = i;
+    for (int i = 0; i < S.nb; ++i) local[sym.rows[S.rows_off + i]] = S.ncol + i;
+    for (int e = sym.child_ptr[s_]; e < sym.child_ptr[s_ + 1]; ++e) {
+      const int c = sym.child[e];
+      invmap_off[e] = next_map;
+      int *inv = invmap.data() + next_map;
+      for (int i = sym.rows_ptr[c]; i < sym.rows_ptr[c + 1]; ++i) inv[local[sym.rows[i]]] = i - sym.rows_ptr[c];
+      next_map += np;
+    }
+    auto &out = per_level[sym.height[s_]];
     for (int p = S.col0; p < S.col0 + S.ncol; ++p) {
       const int v = sym.perm[p];
       for (int e = g.ptr[v]; e < g.ptr[v + 1]; ++e) {
-        const int u = g.adj[e];
-        const int q = sym.iperm[u];
+        const int q = sym.iperm[g.adj[e]];
         if (q < p) continue;
-        int lr;
-        if (q < S.col0 + S.ncol)
-          lr = q - S.col0;
-        else {
-          auto it = std::lower_bound(sym.rows.begin() + S.rows_off, sym.rows.begin() + S.rows_off + S.nb, q);
-          if (it == sym.rows.begin() + S.rows_off + S.nb || *it != q)
-            throw std::runtime_error("A entry outside the supernodal structure");
-          lr = S.ncol + (int)(it - (sym.rows.begin() + S.rows_off));
-        }
-        // block (row u, col v) of the BSR matrix
-        auto jt = std::lower_bound(g.adj.begin() + g.ptr[u], g.adj.begin() + g.ptr[u + 1], v);
-        int blk = (int)(jt - g.adj.begin());
-        per_level[sym.height[s_]].push_back(AScatter{s_, lr, p - S.col0, blk});
+        if (local[q] < 0) throw std::runtime_error("A entry outside the supernodal structure");
+        out.push_back(AScatter{s_, local[q], p - S.col0, mirror[e]});
       }
     }
+    for (int i = 0; i < S.ncol; ++i) local[S.col0 + i] = -1;
+    for (int i = 0; i < S.nb; ++i) local[sym.rows[S.rows_off + i]] = -1;
   }
   std::vector<AScatter> ascat;
   F.levels.assign(sym.nlevels, LevelInfo{});
@@ -277,12 +381,13 @@ void prepare_factor(icr_scene *s) {
   for (int q = 0; q < ns; ++q) F.tiles_desc[q] = tiles(by_tiles[q]);
   F.max_tiles = F.tiles_desc[0];
 
-  s->fac_arena.release();
-  F.rhs_arena.release();
+  const bool settled = s->settle();
+  s->fac_arena.release(settled);
+  F.rhs_arena.release(settled);
   F.nc_cap = 0;
-  F.fac32_arena.release();
+  F.fac32_arena.release(settled);
   F.have32 = false;
-  F.mixed_arena.release();
+  F.mixed_arena.release(settled);
   F.mixed_cap = 0;
   hipStream_t st = s->stream;
   auto &A = s->fac_arena;
@@ -337,25 +442,30 @@ icr_status icr_create(icr_scene **out, void *stream) {
   return ICR_OK;
 }
 
+void icr_release_idle(void) {
+  Idle &I = idle();
+  std::lock_guard<std::mutex> lock(I.mtx);
+  I.drop([](const IdleBlock &) { return true; });
+}
+
 void icr_destroy(icr_scene *s) {
   if (!s) return;
-  (void)hipStreamSynchronize(s->stream);
-  if (s->side) (void)hipStreamSynchronize(s->side);
+  const bool settled = s->settle();
   s->sg.reset();
   if (s->sg.cap) (void)hipStreamDestroy(s->sg.cap);
   if (s->ev_fork) (void)hipEventDestroy(s->ev_fork);
   if (s->ev_join) (void)hipEventDestroy(s->ev_join);
   if (s->side) (void)hipStreamDestroy(s->side);
-  s->con.arena.release();
-  s->map_arena.release();
-  s->pairs.arena.release();
-  s->pairs.step_arena.release();
-  s->fac.rhs_arena.release();
-  s->fac.fac32_arena.release();
-  s->fac.mixed_arena.release();
-  s->fac_arena.release();
-  s->mesh_arena.release();
-  s->state_arena.release();
+  s->con.arena.release(settled);
+  s->map_arena.release(settled);
+  s->pairs.arena.release(settled);
+  s->pairs.step_arena.release(settled);
+  s->fac.rhs_arena.release(settled);
+  s->fac.fac32_arena.release(settled);
+  s->fac.mixed_arena.release(settled);
+  s->fac_arena.release(settled);
+  s->mesh_arena.release(settled);
+  s->state_arena.release(settled);
   delete s;
 }
 
@@ -363,6 +473,7 @@ const char *icr_last_error(const icr_scene *s) { return s ? s->err.c_str() : "nu
 
 icr_status icr_set_stream(icr_scene *s, void *stream) {
   return guarded(s, [&] {
+    s->moved |= s->stream != (hipStream_t)stream;
     s->stream = (hipStream_t)stream;
     return ICR_OK;
   });
@@ -396,23 +507,24 @@ icr_status icr_assemble(icr_scene *s, const double *nodes, int32_t N, const int3
     ICR_HIP(hipStreamSynchronize(s->stream));
     s->epoch++;
     s->sg.reset();
+    const bool settled = s->settle();
     s->assembled = s->factored = s->has_candidates = s->stepped = false;
-    s->con.arena.release();
+    s->con.arena.release(settled);
     s->con.nc_cap = 0;
-    s->map_arena.release();
+    s->map_arena.release(settled);
     s->map_nc_cap = s->map_nu_cap = 0;
-    s->pairs.arena.release();
-    s->pairs.step_arena.release();
+    s->pairs.arena.release(settled);
+    s->pairs.step_arena.release(settled);
     s->pairs = Pairs();
-    s->fac.rhs_arena.release();
+    s->fac.rhs_arena.release(settled);
     s->fac.nc_cap = 0;
-    s->fac.fac32_arena.release();
+    s->fac.fac32_arena.release(settled);
     s->fac.have32 = false;
-    s->fac.mixed_arena.release();
+    s->fac.mixed_arena.release(settled);
     s->fac.mixed_cap = 0;
-    s->fac_arena.release();
-    s->mesh_arena.release();
-    s->state_arena.release();
+    s->fac_arena.release(settled);
+    s->mesh_arena.release(settled);
+    s->state_arena.release(settled);
     auto &m = s->mesh;
     m.N = N;
     m.T = T;
@@ -431,26 +543,26 @@ icr_status icr_assemble(icr_scene *s, const double *nodes, int32_t N, const int3
     std::vector<int> bsr_row(m.nnzb);
     for (int i = 0; i < N; ++i)
       for (int e = g.ptr[i]; e < g.ptr[i + 1]; ++e) bsr_row[e] = i;
-    // element contributions per block, ascending element order
-    std::vector<int> cnt(m.nnzb + 1, 0), nt_cnt(N + 1, 0);
-    auto block_of = [&](int u, int v) {
-      auto it = std::lower_bound(g.adj.begin() + g.ptr[u], g.adj.begin() + g.ptr[u + 1], v);
-      return (int)(it - g.adj.begin());
-    };
-    for (int t = 0; t < T; ++t)
-      for (int a = 0; a < 4; ++a) {
-        nt_cnt[tets[4 * t + a] + 1]++;
-        for (int b = 0; b < 4; ++b) cnt[block_of(tets[4 * t + a], tets[4 * t + b]) + 1]++;
+    // element contributions per block, ascending element order: those of a
+    // block row come from the row node's elements (four each), and a table
+    // gives every neighbour's block in the row
+    std::vector<int> cnt(m.nnzb + 1), cursor(m.nnzb, 0), contrib(16L * T), block(N), nt(4L * T);
+    for (int i = 0; i < N; ++i) {
+      for (int e = g.ptr[i]; e < g.ptr[i + 1]; ++e) block[g.adj[e]] = e;
+      for (int q = g.inc_ptr[i]; q < g.inc_ptr[i + 1]; ++q) {
+        nt[q] = g.inc[q] / 4;
+        for (int b = 0; b < 4; ++b) cursor[block[tets[4L * nt[q] + b]]]++;
       }
-    for (int i = 0; i < m.nnzb; ++i) cnt[i + 1] += cnt[i];
-    for (int i = 0; i < N; ++i) nt_cnt[i + 1] += nt_cnt[i];
-    std::vector<int> contrib(cnt[m.nnzb]), fillp(cnt.begin(), cnt.end() - 1);
-    std::vector<int> nt(nt_cnt[N]), filln(nt_cnt.begin(), nt_cnt.end() - 1);
-    for (int t = 0; t < T; ++t)
-      for (int a = 0; a < 4; ++a) {
-        nt[filln[tets[4 * t + a]]++] = t;
-        for (int b = 0; b < 4; ++b) contrib[fillp[block_of(tets[4 * t + a], tets[4 * t + b])]++] = t * 16 + a * 4 + b;
+      int at = 4 * g.inc_ptr[i];
+      for (int e = g.ptr[i]; e < g.ptr[i + 1]; ++e) {
+        cnt[e] = at;
+        at += cursor[e];
+        cursor[e] = cnt[e];
       }
+      for (int q = g.inc_ptr[i]; q < g.inc_ptr[i + 1]; ++q)
+        for (int b = 0; b < 4; ++b) contrib[cursor[block[tets[4L * nt[q] + b]]]++] = 4 * g.inc[q] + b;
+    }
+    cnt[m.nnzb] = 16 * T;
     hipStream_t st = s->stream;
     auto &A = s->mesh_arena;
     m.d_nodes = A.upload(m.nodes, st);
@@ -463,7 +575,7 @@ icr_status icr_assemble(icr_scene *s, const double *nodes, int32_t N, const int3
     m.d_bsr_row = A.upload(bsr_row, st);
     m.d_contrib_ptr = A.upload(cnt, st);
     m.d_contrib = A.upload(contrib, st);
-    m.d_nt_ptr = A.upload(nt_cnt, st);
+    m.d_nt_ptr = A.upload(g.inc_ptr, st);
     m.d_nt = A.upload(nt, st);
     m.d_Ke = A.alloc<double>(144L * T);
     m.d_vol = A.alloc<double>(T);
@@ -596,7 +708,7 @@ icr_status icr_build_WH(icr_scene *s, int32_t n_c, const int32_t *node_ids, cons
       if (ids[e] >= 0) idx[e] = (int)(std::lower_bound(nodes.begin(), nodes.end(), ids[e]) - nodes.begin());
     if (n_c > s->map_nc_cap || nu > s->map_nu_cap) {
       ICR_HIP(hipStreamSynchronize(st));
-      s->map_arena.release();
+      s->map_arena.release(s->settle());
       s->map_nc_cap = std::max(n_c, s->map_nc_cap);
       s->map_nu_cap = std::max(nu, s->map_nu_cap);
       s->d_map_nodes = s->map_arena.alloc<int>(s->map_nu_cap);
@@ -695,8 +807,9 @@ icr_status icr_set_pairs(icr_scene *s, int32_t count, const int32_t *node_ids, c
     ICR_HIP(hipStreamSynchronize(s->stream));
     s->epoch++;
     auto &Pr = s->pairs;
-    Pr.arena.release();
-    Pr.step_arena.release();
+    const bool settled = s->settle();
+    Pr.arena.release(settled);
+    Pr.step_arena.release(settled);
     Pr = Pairs();
     if (count == 0) return ICR_OK;
     Pr.count = count;

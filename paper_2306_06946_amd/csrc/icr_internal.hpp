@@ -18,6 +18,7 @@ struct MeshGraph {
   int N = 0;
   std::vector<int> ptr;  // N+1
   std::vector<int> adj;  // sorted neighbours, self included
+  std::vector<int> inc_ptr, inc;   // node -> incidences 4 tet + vertex, ascending
 };
 
 // Per supernode, in postorder (children before parents).  Columns of a

@@ -915,7 +915,8 @@ void ensure_rhs_capacity(icr_scene *s, int nc) {
   if (nc <= F.nc_cap) return;
   s->epoch++;
   ICR_HIP(hipStreamSynchronize(s->stream));
-  F.rhs_arena.release();
+  const bool settled = s->settle();
+  F.rhs_arena.release(settled);
   long long xo = 0, zo = 0;
   for (int i = 0; i < (int)F.sup.size(); ++i) {
     SupDev &d = F.sup[i];
@@ -930,7 +931,7 @@ void ensure_rhs_capacity(icr_scene *s, int nc) {
   F.d_Z = F.rhs_arena.alloc<double>(zo);
   F.x_elems = xo;
   F.z_elems = zo;
-  F.mixed_arena.release();   // sized for the previous offsets
+  F.mixed_arena.release(settled);   // sized for the previous offsets
   F.mixed_cap = 0;
   {
     // task-list capacities per (level, kind): the counts at r = rmax
@@ -1073,7 +1074,7 @@ void ensure_mixed(icr_scene *s) {
   auto &F = s->fac;
   hipStream_t st = s->stream;
   if (!F.have32) {
-    F.fac32_arena.release();
+    F.fac32_arena.release(s->settle());
     F.d_front32 = F.fac32_arena.alloc<float>(F.front_elems);
     F.d_linv32 = F.fac32_arena.alloc<float>(F.linv_elems);
     k_to_float<<<2048, 256, 0, st>>>(F.front_elems, F.d_front, F.d_front32);
@@ -1084,7 +1085,7 @@ void ensure_mixed(icr_scene *s) {
   }
   if (F.mixed_cap != F.nc_cap) {
     ICR_HIP(hipStreamSynchronize(st));
-    F.mixed_arena.release();
+    F.mixed_arena.release(s->settle());
     F.d_X32 = F.mixed_arena.alloc<float>(F.x_elems);
     F.d_Z32 = F.mixed_arena.alloc<float>(F.z_elems);
     F.d_R = F.mixed_arena.alloc<double>(F.z_elems);

@@ -11,19 +11,28 @@
 
 namespace icr {
 
+// Device memory blocks of released arenas are kept for the next ones (api.hip).
+struct DeviceBlock {
+  void *p;
+  size_t size;
+  int dev;
+};
+DeviceBlock device_alloc(size_t bytes);   // throws HipError
+// settled: no work that touches the blocks is pending, so they may be handed
+// out again at once; else they go back to the driver.  Never throws.
+void device_release(const std::vector<DeviceBlock> &blocks, bool settled);
+
 // Device allocations owned by a scene; freed together.
 struct Arena {
-  std::vector<void *> ptrs;
+  std::vector<DeviceBlock> blocks;
   size_t bytes = 0;
   template <class T>
   T *alloc(size_t count) {
     if (count == 0) count = 1;
-    void *p = nullptr;
-    hipError_t e = hipMalloc(&p, count * sizeof(T));
-    if (e != hipSuccess) throw HipError(e, "hipMalloc(" + std::to_string(count * sizeof(T)) + " bytes)");
-    ptrs.push_back(p);
+    blocks.reserve(blocks.size() + 1);
+    blocks.push_back(device_alloc(count * sizeof(T)));
     bytes += count * sizeof(T);
-    return static_cast<T *>(p);
+    return static_cast<T *>(blocks.back().p);
   }
   template <class T>
   T *upload(const std::vector<T> &v, hipStream_t st) {
@@ -31,9 +40,9 @@ struct Arena {
     if (!v.empty()) ICR_HIP(hipMemcpyAsync(p, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice, st));
     return p;
   }
-  void release() {
-    for (void *p : ptrs) (void)hipFree(p);
-    ptrs.clear();
+  void release(bool settled) {
+    if (!blocks.empty()) device_release(blocks, settled);
+    blocks.clear();
     bytes = 0;
   }
 };
@@ -261,6 +270,15 @@ struct icr_scene {
   bool overlap = true;
   hipStream_t side = nullptr;
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
+  bool moved = false;   // icr_set_stream changed the stream: work may be pending on the one before
+  // Waits for the scene's own streams; true if nothing that touches its
+  // buffers is pending.
+  bool settle() const {
+    const bool a = hipStreamSynchronize(stream) == hipSuccess;
+    const bool b = !side || hipStreamSynchronize(side) == hipSuccess;
+    if (!(a && b)) (void)hipGetLastError();
+    return a && b && !moved;
+  }
 };
 
 namespace icr {

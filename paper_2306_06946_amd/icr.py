@@ -64,6 +64,7 @@ _D = C.c_double
 _SIGS = {
     "icr_create": (C.c_int, [C.POINTER(_P), _P]),
     "icr_destroy": (None, [_P]),
+    "icr_release_idle": (None, []),
     "icr_last_error": (C.c_char_p, [_P]),
     "icr_set_stream": (C.c_int, [_P, _P]),
     "icr_set_overlap": (C.c_int, [_P, C.c_int32]),
@@ -130,6 +131,11 @@ def _dptr(t, dtype=None, numel=None):
     if numel is not None and t.numel() < numel:
         raise ValueError(f"tensor has {t.numel()} elements, need {numel}")
     return C.c_void_p(t.data_ptr())
+
+
+def release_idle():
+    """Give back the device memory that closed scenes left for the next ones."""
+    lib().icr_release_idle()
 
 
 def analyze(nodes, tets):
