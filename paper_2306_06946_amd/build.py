@@ -22,8 +22,10 @@ SOURCES = ["analysis.cpp", "k_fem.hip", "k_factor.hip", "k_solve.hip", "k_contac
            "server.cpp"]
 
 COMMON = ["-O3", "-fPIC", "-std=c++17", "-Wall", "-Wno-unused-function", "-I" + os.path.join(ROOT, "include")]
+# MFMA results in vector registers: with them in accumulation registers every
+# K-chunk of a product moved its 32 accumulator registers there and back
 HIP_FLAGS = ["--offload-arch=gfx950", "-x", "hip", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-             "-munsafe-fp-atomics"]
+             "-munsafe-fp-atomics", "-mllvm", "-amdgpu-mfma-vgpr-form"]
 
 
 def hipcc() -> str:

@@ -200,13 +200,12 @@ __global__ __launch_bounds__(256) void k_panel_tile(const SupDev *__restrict__ s
   AccS acc;
   acc.zero();
   if (k > kp)
-    acc.acc<true, true>(F + k + (long)kp * f, 1, f, F + i0 + (long)kp * f, f, 1, t, M, 0, k - kp, X);
+    acc.acc<true, true>(F + k + (long)kp * f, f, F + i0 + (long)kp * f, f, t, M, 0, k - kp, X);
   // the accumulator holds the tile transposed: its lanes then run along the
   // rows of the column-major front
   if (blockIdx.x > 0) {
-    acc.for_each([&](int j, int i, double v) {
-      if (i < M && j < t) F[(long)(i0 + i) + (long)(k + j) * f] -= v;
-    });
+    double *P = F + i0 + (long)k * f;
+    acc.update(P, f, P, f, t, M, [](int, int) { return true; }, [](int, int, double v, double old) { return old - v; });
     return;
   }
   // the diagonal tile, padded to 64 by the identity (a row tile holds rows
@@ -286,10 +285,8 @@ __global__ __launch_bounds__(256) void k_trsm_panel(const SupDev *__restrict__ s
   AccS acc;
   acc.zero();
   // out(j, i) = sum_c Dinv(j, c) P(i, c)
-  acc.acc<true, true>(Di, 1, n3, F + i0 + (long)k * f, f, 1, t, M, 0, t, lds);
-  acc.for_each([&](int j, int i, double v) {
-    if (i < M && j < t) F[(long)(i0 + i) + (long)(k + j) * f] = v;
-  });
+  acc.acc<true, true>(Di, n3, F + i0 + (long)k * f, f, t, M, 0, t, lds);
+  acc.put(F + i0 + (long)k * f, f, t, M, [](double v) { return v; });
 }
 
 // Trailing update of the lower triangle by the panel of up to FP_W columns at
@@ -314,10 +311,10 @@ __global__ __launch_bounds__(256) void k_trailing(const SupDev *__restrict__ sup
   double *F = front + S.front_off;
   AccS acc;
   acc.zero();
-  acc.acc<true, true>(F + j0 + (long)kp * f, 1, f, F + i0 + (long)kp * f, f, 1, N, M, 0, w, lds);
-  acc.for_each([&](int j, int i, double v) {
-    if (i < M && j < N && i0 + i >= j0 + j) F[(long)(i0 + i) + (long)(j0 + j) * f] -= v;
-  });
+  acc.acc<true, true>(F + j0 + (long)kp * f, f, F + i0 + (long)kp * f, f, N, M, 0, w, lds);
+  double *C = F + i0 + (long)j0 * f;
+  acc.update(C, f, C, f, N, M, [&](int j, int i) { return i0 + i >= j0 + j; },
+             [](int, int, double v, double old) { return old - v; });
 }
 
 // L_ss^{-1} by doubling, from the inverses of the diagonal tiles: with the
@@ -345,15 +342,11 @@ __global__ __launch_bounds__(256) void k_linv(const SupDev *__restrict__ sup, co
   AccS acc;
   acc.zero();
   if (!second) {
-    acc.acc<true, false>(front + S.front_off + i0, 1, f, X + (long)j0 * n3, 1, n3, M, TILE, j0, m0, lds);
-    acc.for_each([&](int i, int j, double v) {
-      if (i < M) X[(long)(j0 + j) + (long)(i0 + i) * n3] = v;
-    });
+    acc.acc<true, false>(front + S.front_off + i0, f, X + (long)j0 * n3, n3, M, TILE, j0, m0, lds);
+    acc.put(X + j0 + (long)i0 * n3, n3, M, TILE, [](double v) { return v; });
   } else {
-    acc.acc<true, true>(X + j0, 1, n3, X + i0, n3, 1, TILE, M, m0, i0 + M, lds);
-    acc.for_each([&](int j, int i, double v) {
-      if (i < M) X[(long)(i0 + i) + (long)(j0 + j) * n3] = -v;
-    });
+    acc.acc<true, true>(X + j0, n3, X + i0, n3, TILE, M, m0, i0 + M, lds);
+    acc.put(X + i0 + (long)j0 * n3, n3, TILE, M, [](double v) { return -v; });
   }
 }
 

@@ -91,24 +91,61 @@ __device__ inline int lower_bound_i(const int *a, int n, int x) {
   return lo;
 }
 
-constexpr int RHS_T = AccS::T;   // tile order of the multi-RHS products
 enum { RT_ASM = 0, RT_DIAG = 1, RT_SYRK = 2, RT_OFF = 3, RHS_KINDS = 4 };
 
+// Tile edges of the multi-RHS products.  A level's list of one kind is cut
+// into 32 x 32 tiles if it has fewer than RHS_SMALL tiles of 64 x 64 and into
+// 64 x 64 tiles otherwise; every entry is the same sum in the same order of k
+// in both.  A short list leaves compute units idle while a workgroup spends
+// 0.85 us of matrix time on 32 k of a 64 x 64 tile: the product of the root's
+// 630 columns with 600 columns took 38 us in 100 tiles of 64 and takes 18 us in
+// 380 of 32.  Lines at 256 and 1024 were 1 % slower at 1000 and 3000 contacts.
+constexpr int RHS_T = 64, RHS_TS = 32;
+constexpr int RHS_SMALL = 512;
+
 // Tasks of the multi-RHS products of one supernode with r RHS columns, n3
-// DOF columns and b3 below rows (tiles of RHS_T): assemble (4 columns per
-// task), L_ss^{-1} X (row tile x column tile), Z^T Z (lower column-tile
-// pairs), L_21 Z (below-row tile x column tile).  The host evaluates the same
-// counts at r = rmax for the list capacities.
-__host__ __device__ inline void rhs_task_counts(int r, int n3, int b3, int c[RHS_KINDS]) {
+// DOF columns and b3 below rows, for tiles of edge T[kind]: assemble (4
+// columns per task), L_ss^{-1} X (row tile x column tile), Z^T Z (lower
+// column-tile pairs), L_21 Z (below-row tile x column tile).  The host
+// evaluates the same counts at r = rmax for the list capacities.
+__host__ __device__ inline void rhs_task_counts(int r, int n3, int b3, const int T[RHS_KINDS], int c[RHS_KINDS]) {
   if (r <= 0) {
     c[RT_ASM] = c[RT_DIAG] = c[RT_SYRK] = c[RT_OFF] = 0;
     return;
   }
-  const int tr = (r + RHS_T - 1) / RHS_T;
+  auto tiles = [&](int len, int k) { return (len + T[k] - 1) / T[k]; };
+  const int ts = tiles(r, RT_SYRK);
   c[RT_ASM] = (r + 3) / 4;
-  c[RT_DIAG] = ((n3 + RHS_T - 1) / RHS_T) * tr;
-  c[RT_SYRK] = tr * (tr + 1) / 2;
-  c[RT_OFF] = ((b3 + RHS_T - 1) / RHS_T) * tr;
+  c[RT_DIAG] = tiles(n3, RT_DIAG) * tiles(r, RT_DIAG);
+  c[RT_SYRK] = ts * (ts + 1) / 2;
+  c[RT_OFF] = tiles(b3, RT_OFF) * tiles(r, RT_OFF);
+}
+
+// Order of a supernode's tiles in its list: bands of RHS_BAND columns (rows
+// for Z^T Z) of tiles, across the band first, so that tiles that follow one
+// another share panels of both operands.
+constexpr int RHS_BAND = 8;
+// u-th tile of a grid with nr rows and nc columns
+__device__ inline void band_index(int u, int nr, int nc, int &i, int &j) {
+  const int b = u / (RHS_BAND * nr), v = u - b * RHS_BAND * nr;
+  const int w = min(RHS_BAND, nc - RHS_BAND * b);
+  i = v / w;
+  j = RHS_BAND * b + v % w;
+}
+// u-th tile of the lower triangle of an n x n grid
+__device__ inline void band_tri_index(int u, int n, int &i, int &j) {
+  int bi, bj;
+  tri_index(u, bi, bj);
+  const int b = bi / RHS_BAND, r0 = RHS_BAND * b;
+  const int v = u - r0 * (r0 + 1) / 2, h = min(RHS_BAND, n - r0);
+  if (v < h * r0) {
+    i = r0 + v % h;
+    j = v / h;
+  } else {
+    tri_index(v - h * r0, i, j);
+    i += r0;
+    j += r0;
+  }
 }
 
 // k_rhs_plan (one block per height level): the contact range [lo, own, hi)
@@ -116,7 +153,7 @@ __host__ __device__ inline void rhs_task_counts(int r, int n3, int b3, int c[RHS
 // over the supernode's capacity, reachable only with duplicate ids, which are
 // flagged, is emptied), then the level's task lists: one entry (supernode,
 // tile row << 16 | tile column) per tile that has work, in supernode order,
-// and the list lengths.  The products launch one workgroup per entry of the
+// and the list lengths (2 x length + 1 if its tiles are the small ones).  The products launch one workgroup per entry of the
 // list's capacity; those past its length return after one uniform load (a
 // grid laid out by supernode and static column capacity would have most of
 // its workgroups find no columns, each after three dependent loads).
@@ -131,7 +168,7 @@ __global__ __launch_bounds__(PLAN_NT) void k_rhs_plan(int nc, const int *__restr
   __shared__ int pre[RHS_KINDS][PLAN_CHUNK];
   __shared__ int wsum[RHS_KINDS][PLAN_CHUNK / 64];
   __shared__ int wtot[RHS_KINDS];
-  __shared__ int ssup[PLAN_CHUNK], sn3t[PLAN_CHUNK], sb3t[PLAN_CHUNK];
+  __shared__ int ssup[PLAN_CHUNK], sr[PLAN_CHUNK], sn3t[PLAN_CHUNK], sb3t[PLAN_CHUNK];
   __shared__ int skeys[PLAN_KEYS];
   const int l = blockIdx.x, tid = threadIdx.x, ln = tid & 63, wv = tid >> 6;
   const int first = level_first[l], last = level_first[l + 1];
@@ -142,27 +179,46 @@ __global__ __launch_bounds__(PLAN_NT) void k_rhs_plan(int nc, const int *__restr
     __syncthreads();
     kp = skeys;
   }
+  // the ranges, and each kind's number of tiles of 64
+  if (tid < RHS_KINDS) wtot[tid] = 0;
+  __syncthreads();
+  int tile[RHS_KINDS] = {RHS_T, RHS_T, RHS_T, RHS_T};
+  for (int q = first + tid; q < last; q += PLAN_CHUNK) {
+    if (tid >= PLAN_CHUNK) break;
+    const int sn = level_sup[q];
+    const SupDev &S = sup[sn];
+    const int lo = lower_bound_i(kp, nc, S.first_desc);
+    int own = lower_bound_i(kp, nc, sn);
+    int hi = lower_bound_i(kp, nc, sn + 1);
+    if (3 * (hi - lo) > S.rmax) own = hi = lo;
+    lohi[3 * sn + 0] = lo;
+    lohi[3 * sn + 1] = own;
+    lohi[3 * sn + 2] = hi;
+    int c[RHS_KINDS];
+    rhs_task_counts(3 * (hi - lo), 3 * S.ncol, 3 * S.nb, tile, c);
+    for (int k = 0; k < RHS_KINDS; ++k)
+      if (c[k]) atomicAdd(&wtot[k], c[k]);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = RT_DIAG; k < RHS_KINDS; ++k)
+    if (wtot[k] < RHS_SMALL) tile[k] = RHS_TS;
+  __syncthreads();
   int run[RHS_KINDS] = {0, 0, 0, 0};
   for (int base = first; base < last; base += PLAN_CHUNK) {
-    // ranges, task counts and their exclusive prefix over the chunk (waves
+    // task counts and their exclusive prefix over the chunk (waves
     // 0 .. PLAN_CHUNK / 64 - 1)
     const int q = base + tid;
     int c[RHS_KINDS] = {0, 0, 0, 0};
     if (tid < PLAN_CHUNK && q < last) {
       const int sn = level_sup[q];
       const SupDev &S = sup[sn];
-      const int lo = lower_bound_i(kp, nc, S.first_desc);
-      int own = lower_bound_i(kp, nc, sn);
-      int hi = lower_bound_i(kp, nc, sn + 1);
-      if (3 * (hi - lo) > S.rmax) own = hi = lo;
-      lohi[3 * sn + 0] = lo;
-      lohi[3 * sn + 1] = own;
-      lohi[3 * sn + 2] = hi;
-      const int n3 = 3 * S.ncol, b3 = 3 * S.nb;
-      rhs_task_counts(3 * (hi - lo), n3, b3, c);
+      const int r = 3 * (lohi[3 * sn + 2] - lohi[3 * sn]), n3 = 3 * S.ncol, b3 = 3 * S.nb;
+      rhs_task_counts(r, n3, b3, tile, c);
       ssup[tid] = sn;
-      sn3t[tid] = (n3 + RHS_T - 1) / RHS_T;
-      sb3t[tid] = (b3 + RHS_T - 1) / RHS_T;
+      sr[tid] = r;
+      sn3t[tid] = (n3 + tile[RT_DIAG] - 1) / tile[RT_DIAG];
+      sb3t[tid] = (b3 + tile[RT_OFF] - 1) / tile[RT_OFF];
     }
     int v[RHS_KINDS];
 #pragma unroll
@@ -212,14 +268,14 @@ __global__ __launch_bounds__(PLAN_NT) void k_rhs_plan(int nc, const int *__restr
         }
         const int qq = a - 1, u = t - pre[k][qq];
         int ti = u, tj = 0;
-        if (k == RT_DIAG) {   // deepest row tiles first (their product runs over k < i0 + 64)
-          ti = sn3t[qq] - 1 - u % sn3t[qq];
-          tj = u / sn3t[qq];
+        const int tr = (sr[qq] + tile[k] - 1) / tile[k];
+        if (k == RT_DIAG) {   // deepest row tiles first (their product runs over k < i0 + T)
+          band_index(u, sn3t[qq], tr, ti, tj);
+          ti = sn3t[qq] - 1 - ti;
         } else if (k == RT_SYRK) {
-          tri_index(u, ti, tj);
+          band_tri_index(u, tr, ti, tj);
         } else if (k == RT_OFF) {
-          ti = u % sb3t[qq];
-          tj = u / sb3t[qq];
+          band_index(u, sb3t[qq], tr, ti, tj);
         }
         out[t] = make_int2(ssup[qq], (ti << 16) | tj);
       }
@@ -227,7 +283,7 @@ __global__ __launch_bounds__(PLAN_NT) void k_rhs_plan(int nc, const int *__restr
     }
     __syncthreads();
   }
-  if (tid < RHS_KINDS) task_cnt[RHS_KINDS * l + tid] = run[tid];
+  if (tid < RHS_KINDS) task_cnt[RHS_KINDS * l + tid] = 2 * run[tid] + (tile[tid] == RHS_TS ? 1 : 0);
 }
 
 // ---- multi-RHS forward ------------------------------------------------------
@@ -308,30 +364,43 @@ __global__ __launch_bounds__(256) void k_rhs_assemble(const SupDev *__restrict__
                                                       const int *__restrict__ order, const int *__restrict__ node_ids,
                                                       const int *__restrict__ iperm, const double *__restrict__ frames,
                                                       const double *__restrict__ R, E *__restrict__ X) {
-  if ((int)blockIdx.x >= *ntask) return;
+  if ((int)blockIdx.x >= *ntask >> 1) return;
   const int2 tk = tasks[blockIdx.x];
   rhs_assemble_column<E>(sup, tk.x, 4 * (tk.y >> 16) + (threadIdx.x >> 6), threadIdx.x & 63, child, invmap_off,
                          invmap, lohi, order, node_ids, iperm, frames, R, X);
 }
 
-// Z_s = L_ss^{-1} X_s[:n_s], one 64x64 tile per task.  z64 (FP32 solves of
+// The product kernels' tiles hold the transposed product (the accumulator's
+// columns are the rows of the column-major output), so that 16 lanes store 16
+// neighbours.  W_H of 200 contacts at 9 450 DOF: 497 -> 345 us, of 1000 at
+// 61 236: 2.65 -> 2.10 ms, of 3000 at 75 600: 11.8 -> 9.7 ms.
+template <class E>
+struct RhsAcc {
+  typedef AccMT<2, 32, E> Mid;     // 64 x 64, K-chunk 32
+  typedef AccMT<1, 64, E> Small;   // 32 x 32, K-chunk 64
+  static constexpr int LDS = Mid::LDS > Small::LDS ? Mid::LDS : Small::LDS;
+  static_assert(Mid::T == RHS_T && Small::T == RHS_TS, "tile edges of the plan");
+};
+
+// Task of this workgroup (false: none); small: it is a 32 x 32 tile.
+__device__ inline bool rhs_my_task(const int2 *__restrict__ tasks, const int *__restrict__ ntask, int2 &tk,
+                                   bool &small) {
+  const int n = *ntask;
+  if ((int)blockIdx.x >= n >> 1) return false;
+  tk = tasks[blockIdx.x];
+  small = n & 1;
+  return true;
+}
+
+// Z_s = L_ss^{-1} X_s[:n_s], one tile per task.  z64 (FP32 solves of
 // the mixed-precision build): 1 also stores the tile into the FP64 Z,
 // 2 adds it there (a refinement correction).
 template <class Ac>
-__global__ __launch_bounds__(256) void k_rhs_diag(const SupDev *__restrict__ sup, const int2 *__restrict__ tasks,
-                                                  const int *__restrict__ ntask, const int *__restrict__ lohi,
-                                                  const typename Ac::elem *__restrict__ linv,
-                                                  const typename Ac::elem *__restrict__ X,
-                                                  typename Ac::elem *__restrict__ Z, double *__restrict__ Z64,
-                                                  int z64) {
+__device__ void rhs_diag_tile(const SupDev &S, int r, int2 tk, const typename Ac::elem *__restrict__ linv,
+                              const typename Ac::elem *__restrict__ X, typename Ac::elem *__restrict__ Z,
+                              double *__restrict__ Z64, int z64, typename Ac::elem *lds) {
   typedef typename Ac::elem E;
   constexpr int T = Ac::T;
-  __shared__ E lds[Ac::LDS];
-  if ((int)blockIdx.x >= *ntask) return;
-  const int2 tk = tasks[blockIdx.x];
-  const int s = tk.x;
-  const SupDev S = sup[s];
-  const int r = 3 * (lohi[3 * s + 2] - lohi[3 * s]);
   const int n3 = 3 * S.ncol, f = 3 * (S.ncol + S.nb);
   const int i0 = T * (tk.y >> 16), j0 = T * (tk.y & 0xffff);
   if (i0 >= n3 || j0 >= r) return;
@@ -339,47 +408,65 @@ __global__ __launch_bounds__(256) void k_rhs_diag(const SupDev *__restrict__ sup
   const int kend = min(n3, i0 + T);
   Ac acc;
   acc.zero();
-  acc.template acc<true, false>(linv + S.linv_off + i0, 1, n3, X + S.x_off + (long)j0 * f, 1, f, M, N, 0, kend,
-                                lds);
-  E *Zs = Z + S.z_off;
-  double *Z64s = Z64 ? Z64 + S.z_off : nullptr;
-  acc.for_each([&](int i, int j, E v) {
-    if (i < M && j < N) {
-      const long e = (long)(i0 + i) + (long)(j0 + j) * n3;
-      Zs[e] = v;
-      if (z64 == 1) Z64s[e] = (double)v;
-      if (z64 == 2) Z64s[e] += (double)v;
-    }
-  });
+  acc.template acc<false, true>(X + S.x_off + (long)j0 * f, f, linv + S.linv_off + i0, n3, N, M, 0, kend, lds);
+  const long out = S.z_off + i0 + (long)j0 * n3;
+  acc.put(Z + out, n3, N, M, [](E v) { return v; });
+  if (z64 == 1) acc.put(Z64 + out, n3, N, M, [](E v) { return (double)v; });
+  if (z64 == 2)
+    acc.update(Z64 + out, n3, Z64 + out, n3, N, M, [](int, int) { return true; },
+               [](int, int, E v, double old) { return old + (double)v; });
+}
+template <class E>
+__global__ __launch_bounds__(256) void k_rhs_diag(const SupDev *__restrict__ sup, const int2 *__restrict__ tasks,
+                                                  const int *__restrict__ ntask, const int *__restrict__ lohi,
+                                                  const E *__restrict__ linv, const E *__restrict__ X,
+                                                  E *__restrict__ Z, double *__restrict__ Z64, int z64) {
+  __shared__ E lds[RhsAcc<E>::LDS];
+  int2 tk;
+  bool small;
+  if (!rhs_my_task(tasks, ntask, tk, small)) return;
+  const int s = tk.x;
+  const SupDev S = sup[s];
+  const int r = 3 * (lohi[3 * s + 2] - lohi[3 * s]);
+  if (small)
+    rhs_diag_tile<typename RhsAcc<E>::Small>(S, r, tk, linv, X, Z, Z64, z64, lds);
+  else
+    rhs_diag_tile<typename RhsAcc<E>::Mid>(S, r, tk, linv, X, Z, Z64, z64, lds);
 }
 
 // X_s[n_s:] -= L_21 Z_s, one tile per task
 template <class Ac>
-__global__ __launch_bounds__(256) void k_rhs_off(const SupDev *__restrict__ sup, const int2 *__restrict__ tasks,
-                                                 const int *__restrict__ ntask, const int *__restrict__ lohi,
-                                                 const typename Ac::elem *__restrict__ front,
-                                                 const typename Ac::elem *__restrict__ Z,
-                                                 typename Ac::elem *__restrict__ X) {
+__device__ void rhs_off_tile(const SupDev &S, int r, int2 tk, const typename Ac::elem *__restrict__ front,
+                             const typename Ac::elem *__restrict__ Z, typename Ac::elem *__restrict__ X,
+                             typename Ac::elem *lds) {
   typedef typename Ac::elem E;
   constexpr int T = Ac::T;
-  __shared__ E lds[Ac::LDS];
-  if ((int)blockIdx.x >= *ntask) return;
-  const int2 tk = tasks[blockIdx.x];
-  const int s = tk.x;
-  const SupDev S = sup[s];
-  const int r = 3 * (lohi[3 * s + 2] - lohi[3 * s]);
   const int n3 = 3 * S.ncol, b3 = 3 * S.nb, f = n3 + b3;
   const int i0 = T * (tk.y >> 16), j0 = T * (tk.y & 0xffff);
   if (i0 >= b3 || j0 >= r) return;
   const int M = min(T, b3 - i0), N = min(T, r - j0);
   Ac acc;
   acc.zero();
-  acc.template acc<true, false>(front + S.front_off + n3 + i0, 1, f, Z + S.z_off + (long)j0 * n3, 1, n3, M, N, 0,
-                                n3, lds);
-  E *Xs = X + S.x_off;
-  acc.for_each([&](int i, int j, E v) {
-    if (i < M && j < N) Xs[(long)(n3 + i0 + i) + (long)(j0 + j) * f] -= v;
-  });
+  acc.template acc<false, true>(Z + S.z_off + (long)j0 * n3, n3, front + S.front_off + n3 + i0, f, N, M, 0, n3, lds);
+  E *Xs = X + S.x_off + n3 + i0 + (long)j0 * f;
+  acc.update(Xs, f, Xs, f, N, M, [](int, int) { return true; }, [](int, int, E v, E old) { return old - v; });
+}
+template <class E>
+__global__ __launch_bounds__(256) void k_rhs_off(const SupDev *__restrict__ sup, const int2 *__restrict__ tasks,
+                                                 const int *__restrict__ ntask, const int *__restrict__ lohi,
+                                                 const E *__restrict__ front, const E *__restrict__ Z,
+                                                 E *__restrict__ X) {
+  __shared__ E lds[RhsAcc<E>::LDS];
+  int2 tk;
+  bool small;
+  if (!rhs_my_task(tasks, ntask, tk, small)) return;
+  const int s = tk.x;
+  const SupDev S = sup[s];
+  const int r = 3 * (lohi[3 * s + 2] - lohi[3 * s]);
+  if (small)
+    rhs_off_tile<typename RhsAcc<E>::Small>(S, r, tk, front, Z, X, lds);
+  else
+    rhs_off_tile<typename RhsAcc<E>::Mid>(S, r, tk, front, Z, X, lds);
 }
 
 // Residual of the forward solve on a supernode's own rows (FP64, the
@@ -387,17 +474,10 @@ __global__ __launch_bounds__(256) void k_rhs_off(const SupDev *__restrict__ sup,
 // X_s assembled in FP64 from the unit columns and the children's FP64
 // updates; L_ss is the lower triangle of the front's diagonal block.
 template <class Ac>
-__global__ __launch_bounds__(256) void k_rhs_resid(const SupDev *__restrict__ sup, const int2 *__restrict__ tasks,
-                                                   const int *__restrict__ ntask, const int *__restrict__ lohi,
-                                                   const double *__restrict__ front, const double *__restrict__ X,
-                                                   const double *__restrict__ Z, double *__restrict__ R) {
+__device__ void rhs_resid_tile(const SupDev &S, int r, int2 tk, const double *__restrict__ front,
+                               const double *__restrict__ X, const double *__restrict__ Z, double *__restrict__ R,
+                               double *lds) {
   constexpr int T = Ac::T;
-  __shared__ double lds[Ac::LDS];
-  if ((int)blockIdx.x >= *ntask) return;
-  const int2 tk = tasks[blockIdx.x];
-  const int s = tk.x;
-  const SupDev S = sup[s];
-  const int r = 3 * (lohi[3 * s + 2] - lohi[3 * s]);
   const int n3 = 3 * S.ncol, f = 3 * (S.ncol + S.nb);
   const int i0 = T * (tk.y >> 16), j0 = T * (tk.y & 0xffff);
   if (i0 >= n3 || j0 >= r) return;
@@ -405,30 +485,35 @@ __global__ __launch_bounds__(256) void k_rhs_resid(const SupDev *__restrict__ su
   const int kend = min(n3, i0 + T);
   Ac acc;
   acc.zero();
-  // A(i, k) = L_ss(i0 + i, k), zero above the diagonal (k > i0 + i)
-  acc.template acc<true, false, true>(front + S.front_off + i0, 1, f, Z + S.z_off + (long)j0 * n3, 1, n3, M, N, 0,
-                                      kend, lds, i0);
-  const double *Xs = X + S.x_off;
-  double *Rs = R + S.z_off;
-  acc.for_each([&](int i, int j, double v) {
-    if (i < M && j < N) Rs[(long)(i0 + i) + (long)(j0 + j) * n3] = Xs[(long)(i0 + i) + (long)(j0 + j) * f] - v;
-  });
+  // B(k, i) = L_ss(i0 + i, k), zero above the diagonal (k > i0 + i)
+  acc.template acc<false, true, true>(Z + S.z_off + (long)j0 * n3, n3, front + S.front_off + i0, f, N, M, 0, kend, lds,
+                                      i0);
+  acc.update(R + S.z_off + i0 + (long)j0 * n3, n3, X + S.x_off + i0 + (long)j0 * f, f, N, M,
+             [](int, int) { return true; }, [](int, int, double v, double x) { return x - v; });
+}
+__global__ __launch_bounds__(256) void k_rhs_resid(const SupDev *__restrict__ sup, const int2 *__restrict__ tasks,
+                                                   const int *__restrict__ ntask, const int *__restrict__ lohi,
+                                                   const double *__restrict__ front, const double *__restrict__ X,
+                                                   const double *__restrict__ Z, double *__restrict__ R) {
+  __shared__ double lds[RhsAcc<double>::LDS];
+  int2 tk;
+  bool small;
+  if (!rhs_my_task(tasks, ntask, tk, small)) return;
+  const int s = tk.x;
+  const SupDev S = sup[s];
+  const int r = 3 * (lohi[3 * s + 2] - lohi[3 * s]);
+  if (small)
+    rhs_resid_tile<RhsAcc<double>::Small>(S, r, tk, front, X, Z, R, lds);
+  else
+    rhs_resid_tile<RhsAcc<double>::Mid>(S, r, tk, front, X, Z, R, lds);
 }
 
 // Wp[3lo + i][3lo + j] += sum_k Z(k, i) Z(k, j), one lower tile of the r x r
 // block per task
 template <class Ac>
-__global__ __launch_bounds__(256) void k_rhs_syrk(const SupDev *__restrict__ sup, const int2 *__restrict__ tasks,
-                                                  const int *__restrict__ ntask, const int *__restrict__ lohi,
-                                                  const double *__restrict__ Z, int m, double *__restrict__ Wp) {
+__device__ void rhs_syrk_tile(const SupDev &S, int lo, int r, int2 tk, const double *__restrict__ Z, int m,
+                              double *__restrict__ Wp, double *lds) {
   constexpr int T = Ac::T;
-  __shared__ double lds[Ac::LDS];
-  if ((int)blockIdx.x >= *ntask) return;
-  const int2 tk = tasks[blockIdx.x];
-  const int s = tk.x;
-  const SupDev S = sup[s];
-  const int lo = lohi[3 * s];
-  const int r = 3 * (lohi[3 * s + 2] - lo);
   const int i0 = T * (tk.y >> 16), j0 = T * (tk.y & 0xffff);
   if (i0 >= r || j0 > i0) return;
   const int n3 = 3 * S.ncol;
@@ -436,11 +521,25 @@ __global__ __launch_bounds__(256) void k_rhs_syrk(const SupDev *__restrict__ sup
   const double *Zs = Z + S.z_off;
   Ac acc;
   acc.zero();
-  acc.template acc<false, false>(Zs + (long)i0 * n3, n3, 1, Zs + (long)j0 * n3, 1, n3, M, N, 0, n3, lds);
-  const long base = (long)(3 * lo) * m + 3 * lo;
-  acc.for_each([&](int i, int j, double v) {
-    if (i < M && j < N) Wp[base + (long)(i0 + i) * m + (j0 + j)] += v;
-  });
+  acc.template acc<false, false>(Zs + (long)i0 * n3, n3, Zs + (long)j0 * n3, n3, M, N, 0, n3, lds);
+  double *C = Wp + (long)(3 * lo + i0) * m + 3 * lo + j0;
+  acc.update(C, m, C, m, M, N, [](int, int) { return true; }, [](int, int, double v, double old) { return old + v; });
+}
+__global__ __launch_bounds__(256) void k_rhs_syrk(const SupDev *__restrict__ sup, const int2 *__restrict__ tasks,
+                                                  const int *__restrict__ ntask, const int *__restrict__ lohi,
+                                                  const double *__restrict__ Z, int m, double *__restrict__ Wp) {
+  __shared__ double lds[RhsAcc<double>::LDS];
+  int2 tk;
+  bool small;
+  if (!rhs_my_task(tasks, ntask, tk, small)) return;
+  const int s = tk.x;
+  const SupDev S = sup[s];
+  const int lo = lohi[3 * s];
+  const int r = 3 * (lohi[3 * s + 2] - lo);
+  if (small)
+    rhs_syrk_tile<RhsAcc<double>::Small>(S, lo, r, tk, Z, m, Wp, lds);
+  else
+    rhs_syrk_tile<RhsAcc<double>::Mid>(S, lo, r, tk, Z, m, Wp, lds);
 }
 
 __global__ void k_fill(long n, double v, double *__restrict__ x) {
@@ -944,13 +1043,21 @@ void ensure_rhs_capacity(icr_scene *s, int nc) {
       const LevelInfo &L = F.levels[l];
       level_first[l] = L.first;
       level_first[l + 1] = L.first + L.count;
+      const int T[RHS_KINDS] = {RHS_T, RHS_T, RHS_T, RHS_T}, TS[RHS_KINDS] = {RHS_TS, RHS_TS, RHS_TS, RHS_TS};
+      long long mid[RHS_KINDS] = {}, small[RHS_KINDS] = {};
       for (int q = 0; q < L.count; ++q) {
         const SupDev &d = F.sup[F.sym.level_sup[L.first + q]];
         int c[RHS_KINDS];
-        rhs_task_counts(d.rmax, 3 * d.ncol, 3 * d.nb, c);
-        for (int k = 0; k < RHS_KINDS; ++k) F.rhs_cap[RHS_KINDS * l + k] += c[k];
+        rhs_task_counts(d.rmax, 3 * d.ncol, 3 * d.nb, T, c);
+        for (int k = 0; k < RHS_KINDS; ++k) mid[k] += c[k];
+        rhs_task_counts(d.rmax, 3 * d.ncol, 3 * d.nb, TS, c);
+        for (int k = 0; k < RHS_KINDS; ++k) small[k] += c[k];
       }
       for (int k = 0; k < RHS_KINDS; ++k) {
+        // a list of small tiles has fewer than 4 RHS_SMALL entries
+        const long long cap = std::max(mid[k], std::min(small[k], (long long)4 * RHS_SMALL));
+        if (cap > INT32_MAX / 2) throw std::runtime_error("multi-RHS task lists exceed 2^30 entries");
+        F.rhs_cap[RHS_KINDS * l + k] = (int)cap;
         F.rhs_off[RHS_KINDS * l + k] = (int)tot;
         tot += F.rhs_cap[RHS_KINDS * l + k];
       }
@@ -1057,11 +1164,11 @@ void forward_fp32(icr_scene *s, const int *node_ids, const double *R, int z64) {
                                                              F.d_child, F.d_invmap_off, F.d_invmap, F.d_lohi,
                                                              F.d_order, node_ids, F.d_iperm, nullptr, R, F.d_X32);
     ICR_LAUNCH_CHECK();
-    k_rhs_diag<AccS32><<<L.grid(l, RT_DIAG), 256, 0, st>>>(F.d_sup, L.list(l, RT_DIAG), L.count(l, RT_DIAG),
+    k_rhs_diag<float><<<L.grid(l, RT_DIAG), 256, 0, st>>>(F.d_sup, L.list(l, RT_DIAG), L.count(l, RT_DIAG),
                                                            F.d_lohi, F.d_linv32, F.d_X32, F.d_Z32, F.d_Z, z64);
     ICR_LAUNCH_CHECK();
     if (L.any(l, RT_OFF)) {
-      k_rhs_off<AccS32><<<L.grid(l, RT_OFF), 256, 0, st>>>(F.d_sup, L.list(l, RT_OFF), L.count(l, RT_OFF), F.d_lohi,
+      k_rhs_off<float><<<L.grid(l, RT_OFF), 256, 0, st>>>(F.d_sup, L.list(l, RT_OFF), L.count(l, RT_OFF), F.d_lohi,
                                                            F.d_front32, F.d_Z32, F.d_X32);
       ICR_LAUNCH_CHECK();
     }
@@ -1106,7 +1213,7 @@ void build_WH_device(icr_scene *s, int nc, const int *node_ids, double *WH, bool
                                                               F.d_order, node_ids, F.d_iperm, frames, nullptr,
                                                               F.d_X);
     ICR_LAUNCH_CHECK();
-    k_rhs_diag<AccS><<<L.grid(l, RT_DIAG), 256, 0, st>>>(F.d_sup, L.list(l, RT_DIAG), L.count(l, RT_DIAG), F.d_lohi,
+    k_rhs_diag<double><<<L.grid(l, RT_DIAG), 256, 0, st>>>(F.d_sup, L.list(l, RT_DIAG), L.count(l, RT_DIAG), F.d_lohi,
                                                          F.d_linv, F.d_X, F.d_Z, nullptr, 0);
     ICR_LAUNCH_CHECK();
     // Z of this level is final: its W_H products go to the side stream (they
@@ -1118,11 +1225,11 @@ void build_WH_device(icr_scene *s, int nc, const int *node_ids, double *WH, bool
       ICR_HIP(hipStreamWaitEvent(s->side, s->ev_fork, 0));
       sy = s->side;
     }
-    k_rhs_syrk<AccS><<<L.grid(l, RT_SYRK), 256, 0, sy>>>(F.d_sup, L.list(l, RT_SYRK), L.count(l, RT_SYRK), F.d_lohi,
+    k_rhs_syrk<<<L.grid(l, RT_SYRK), 256, 0, sy>>>(F.d_sup, L.list(l, RT_SYRK), L.count(l, RT_SYRK), F.d_lohi,
                                                          F.d_Z, (int)m, F.d_Wp);
     ICR_LAUNCH_CHECK();
     if (L.any(l, RT_OFF)) {
-      k_rhs_off<AccS><<<L.grid(l, RT_OFF), 256, 0, st>>>(F.d_sup, L.list(l, RT_OFF), L.count(l, RT_OFF), F.d_lohi,
+      k_rhs_off<double><<<L.grid(l, RT_OFF), 256, 0, st>>>(F.d_sup, L.list(l, RT_OFF), L.count(l, RT_OFF), F.d_lohi,
                                                          F.d_front, F.d_Z, F.d_X);
       ICR_LAUNCH_CHECK();
     }
@@ -1150,11 +1257,11 @@ void build_WH_mixed(icr_scene *s, int nc, const int *node_ids, int refine, float
                                                                 F.d_order, node_ids, F.d_iperm, nullptr, nullptr,
                                                                 F.d_X);
       ICR_LAUNCH_CHECK();
-      k_rhs_resid<AccS><<<L.grid(l, RT_DIAG), 256, 0, st>>>(F.d_sup, L.list(l, RT_DIAG), L.count(l, RT_DIAG),
+      k_rhs_resid<<<L.grid(l, RT_DIAG), 256, 0, st>>>(F.d_sup, L.list(l, RT_DIAG), L.count(l, RT_DIAG),
                                                             F.d_lohi, F.d_front, F.d_X, F.d_Z, F.d_R);
       ICR_LAUNCH_CHECK();
       if (L.any(l, RT_OFF)) {
-        k_rhs_off<AccS><<<L.grid(l, RT_OFF), 256, 0, st>>>(F.d_sup, L.list(l, RT_OFF), L.count(l, RT_OFF), F.d_lohi,
+        k_rhs_off<double><<<L.grid(l, RT_OFF), 256, 0, st>>>(F.d_sup, L.list(l, RT_OFF), L.count(l, RT_OFF), F.d_lohi,
                                                            F.d_front, F.d_Z, F.d_X);
         ICR_LAUNCH_CHECK();
       }
@@ -1164,7 +1271,7 @@ void build_WH_mixed(icr_scene *s, int nc, const int *node_ids, int refine, float
   // W_H = Z^T Z in FP64 from the refined Z
   for (int l = 0; l < (int)F.levels.size(); ++l) {
     if (!L.any(l, RT_ASM)) continue;
-    k_rhs_syrk<AccS><<<L.grid(l, RT_SYRK), 256, 0, st>>>(F.d_sup, L.list(l, RT_SYRK), L.count(l, RT_SYRK), F.d_lohi,
+    k_rhs_syrk<<<L.grid(l, RT_SYRK), 256, 0, st>>>(F.d_sup, L.list(l, RT_SYRK), L.count(l, RT_SYRK), F.d_lohi,
                                                          F.d_Z, (int)m, F.d_Wp);
     ICR_LAUNCH_CHECK();
   }
