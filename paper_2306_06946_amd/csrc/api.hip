@@ -282,10 +282,11 @@ void prepare_factor(icr_scene *s) {
   F.front_elems = fo;
   F.linv_elems = lo;
   F.x1_elems = xo;
-  // child index maps (parent local node -> child below-row index, or -1), and
+  // child index maps (parent local node -> child below-row index, or -1, and
+  // back), and
   // the A -> front scatter entries, grouped by level; local[q]: index of
   // permuted node q in the front of the supernode at hand
-  std::vector<int> invmap_off(sym.child.size()), invmap, local(m.N, -1);
+  std::vector<int> invmap_off(sym.child.size()), invmap, relmap(sym.rows.size()), local(m.N, -1);
   {
     size_t total = 0;
     for (int p = 0; p < ns; ++p) total += (size_t)(F.sup[p].ncol + F.sup[p].nb) * F.sup[p].nchild;
@@ -310,7 +311,10 @@ void prepare_factor(icr_scene *s) {
       const int c = sym.child[e];
       invmap_off[e] = next_map;
       int *inv = invmap.data() + next_map;
-      for (int i = sym.rows_ptr[c]; i < sym.rows_ptr[c + 1]; ++i) inv[local[sym.rows[i]]] = i - sym.rows_ptr[c];
+      for (int i = sym.rows_ptr[c]; i < sym.rows_ptr[c + 1]; ++i) {
+        relmap[i] = local[sym.rows[i]];
+        inv[relmap[i]] = i - sym.rows_ptr[c];
+      }
       next_map += np;
     }
     auto &out = per_level[sym.height[s_]];
@@ -396,6 +400,7 @@ void prepare_factor(icr_scene *s) {
   F.d_child = A.upload(sym.child, st);
   F.d_invmap_off = A.upload(invmap_off, st);
   F.d_invmap = A.upload(invmap, st);
+  F.d_relmap = A.upload(relmap, st);
   F.d_level_sup = A.upload(sym.level_sup, st);
   F.d_sup_by_tiles = A.upload(by_tiles, st);
   F.d_perm = A.upload(sym.perm, st);

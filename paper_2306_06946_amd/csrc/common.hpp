@@ -231,6 +231,47 @@ struct AccMT {
                     (O)f(i, j, c[a][b][t], old[a][b][t]));
         }
   }
+  // C[i ld + row(j)] = Q[i ldq + j] - v, or the sum of that and what is there
+  // (add), for the tile's i < M, j < N (row(j) < ld, ldq >= N)
+  template <class R>
+  __device__ void push(E *C, long ld, R &&row, const E *Q, long ldq, int M, int N, bool add) {
+    const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
+    const int r0 = (T / 2) * (w >> 1), c0 = (T / 2) * (w & 1) + (l & 15);
+    const __amdgpu_buffer_rsrc_t bc = buf_make(C, (long)sizeof(E) * M * ld);
+    const __amdgpu_buffer_rsrc_t bq = buf_make(Q, (long)sizeof(E) * ((M - 1) * ldq + N));
+    unsigned at[WB];
+    E q[WB][WB][4];
+#pragma unroll
+    for (int b = 0; b < WB; ++b) at[b] = c0 + 16 * b < N ? (unsigned)sizeof(E) * (unsigned)row(c0 + 16 * b) : BUF_OUT;
+#pragma unroll
+    for (int a = 0; a < WB; ++a)
+#pragma unroll
+      for (int b = 0; b < WB; ++b)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          const int i = r0 + 16 * a + Mfma<E>::row(l, t), j = c0 + 16 * b;
+          q[a][b][t] =
+              buf_load<E>(bq, j < N ? (unsigned)sizeof(E) * ((unsigned)i * (unsigned)ldq + (unsigned)j) : BUF_OUT) -
+              c[a][b][t];
+        }
+    if (add)
+#pragma unroll
+      for (int a = 0; a < WB; ++a)
+#pragma unroll
+        for (int b = 0; b < WB; ++b)
+#pragma unroll
+          for (int t = 0; t < 4; ++t)
+            q[a][b][t] += buf_load<E>(
+                bc, (unsigned)sizeof(E) * (unsigned)(r0 + 16 * a + Mfma<E>::row(l, t)) * (unsigned)ld + at[b]);
+#pragma unroll
+    for (int a = 0; a < WB; ++a)
+#pragma unroll
+      for (int b = 0; b < WB; ++b)
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+          buf_store(bc, (unsigned)sizeof(E) * (unsigned)(r0 + 16 * a + Mfma<E>::row(l, t)) * (unsigned)ld + at[b],
+                    q[a][b][t]);
+  }
   // C[i ld + j] = f(v) for the tile's i < M, j < N
   template <class O, class F>
   __device__ void put(O *C, long ld, int M, int N, F &&f) {

@@ -5,9 +5,9 @@
 // holding their node, so the contacts below supernode s form one contiguous
 // range [lo_s, hi_s) and its RHS front X_s has 3 (hi_s - lo_s) columns.  Per
 // height level, bottom-up:
-//   X_s  = unit columns of its own contacts + children's updates (pulled)
+//   X_s  = unit columns of its own contacts, children's updates
 //   Z_s  = L_ss^{-1} X_s[:n_s]                   (triangular dense product)
-//   X_s[n_s:] -= L_21 Z_s                        (update passed to the parent)
+//   X_parent[rows below s] = X_s[n_s:] - L_21 Z_s
 //   Wp[range_s, range_s] += Z_s^T Z_s            (lower tiles; ranges of one
 //                                                 level are disjoint)
 // then W_H is read out of Wp in contact order (exactly symmetric).
@@ -288,34 +288,34 @@ __global__ __launch_bounds__(PLAN_NT) void k_rhs_plan(int nc, const int *__restr
 
 // ---- multi-RHS forward ------------------------------------------------------
 
-// X_s column by column (one wave per column, 4 columns per task): a column
-// of an own contact is a unit vector of H^T (or a column of J^T = H^T C^T
-// when frames are given); a column of a contact below a child is the child's
-// below-row part extended into the front rows (extend-add through invmap).
-// With a residual R (the correction solve of the refinement), the columns
-// carry R_s on the supernode's own rows instead of the unit vectors, plus
-// the children's parts.  Everything that identifies the column is uniform
-// over the wave.
+// What the children's updates leave open of X_s, column by column (one wave
+// per column, 4 columns per task): a column of an own contact is a unit vector
+// of H^T (or a column of J^T = H^T C^T when frames are given); a column of a
+// contact below a child is zero on the front rows that the child does not
+// reach, the others are stored by the child's product.  With a residual R (the
+// correction solve of the refinement) every column holds R_s on the
+// supernode's own rows and zero below, and the children's products add to it.
+// Everything that identifies the column is uniform over the wave.
 template <class E>
-__device__ inline void rhs_assemble_column(const SupDev *__restrict__ sup, int s, int jc, int l,
-                                           const int *__restrict__ child, const int *__restrict__ invmap_off,
-                                           const int *__restrict__ invmap, const int *__restrict__ lohi,
-                                           const int *__restrict__ order, const int *__restrict__ node_ids,
-                                           const int *__restrict__ iperm, const double *__restrict__ frames,
-                                           const double *__restrict__ R, E *__restrict__ X) {
+__device__ inline void rhs_init_column(const SupDev *__restrict__ sup, int s, int jc, int l,
+                                       const int *__restrict__ child, const int *__restrict__ invmap_off,
+                                       const int *__restrict__ invmap, const int *__restrict__ lohi,
+                                       const int *__restrict__ order, const int *__restrict__ node_ids,
+                                       const int *__restrict__ iperm, const double *__restrict__ frames,
+                                       const double *__restrict__ R, E *__restrict__ X) {
   const SupDev S = sup[s];
   const int lo = lohi[3 * s], own = lohi[3 * s + 1], hi = lohi[3 * s + 2];
   const int r = 3 * (hi - lo);
   if (jc >= r) return;
   const int n3 = 3 * S.ncol, f = 3 * (S.ncol + S.nb);
   E *Xc = X + S.x_off + (long)jc * f;
-  const double *Rc = R ? R + S.z_off + (long)jc * n3 : nullptr;
   const int p = lo + jc / 3, a = jc % 3;
+  if (R) {
+    const double *Rc = R + S.z_off + (long)jc * n3;
+    for (int i = l; i < f; i += 64) Xc[i] = (i < n3) ? E(Rc[i]) : E(0);
+    return;
+  }
   if (p >= own) {
-    if (Rc) {
-      for (int i = l; i < f; i += 64) Xc[i] = (i < n3) ? E(Rc[i]) : E(0);
-      return;
-    }
     const int c = order[p];
     const int base = 3 * (iperm[node_ids[c]] - S.col0);
     for (int i = l; i < f; i += 64) {
@@ -328,46 +328,35 @@ __device__ inline void rhs_assemble_column(const SupDev *__restrict__ sup, int s
     }
     return;
   }
-  int cc = -1, clo = 0;
+  const int *im = nullptr;   // null: not below any child (cannot happen for sorted contacts)
   for (int q = 0; q < S.nchild; ++q) {
     const int ch = child[S.child_off + q];
     if (p >= lohi[3 * ch] && p < lohi[3 * ch + 2]) {
-      cc = q;
-      clo = lohi[3 * ch];
+      im = invmap + invmap_off[S.child_off + q];
       break;
     }
   }
-  if (cc < 0) {   // not below any child (cannot happen for sorted contacts)
-    for (int i = l; i < f; i += 64) Xc[i] = E(0);
-    return;
-  }
-  const SupDev C = sup[child[S.child_off + cc]];
-  const int fc = 3 * (C.ncol + C.nb);
-  const int *im = invmap + invmap_off[S.child_off + cc];
-  const E *src = X + C.x_off + (long)(jc - 3 * (clo - lo)) * fc + 3 * C.ncol;
-  for (int i = l; i < f; i += 64) {
-    const int ii = im[i / 3];
-    E v = (ii >= 0) ? src[3 * ii + i % 3] : E(0);
-    if (Rc && i < n3) v += E(Rc[i]);
-    Xc[i] = v;
-  }
+  for (int i = l; i < f; i += 64)
+    if (im == nullptr || im[i / 3] < 0) Xc[i] = E(0);
 }
 
-// The product kernels take task blockIdx.x of their level's list; the grid is
-// the list's capacity and the workgroups past its length return after one
-// uniform load.
+// All levels in one launch: asm_first[l] is the first workgroup of level l.
 template <class E>
-__global__ __launch_bounds__(256) void k_rhs_assemble(const SupDev *__restrict__ sup, const int2 *__restrict__ tasks,
-                                                      const int *__restrict__ ntask, const int *__restrict__ child,
-                                                      const int *__restrict__ invmap_off,
-                                                      const int *__restrict__ invmap, const int *__restrict__ lohi,
-                                                      const int *__restrict__ order, const int *__restrict__ node_ids,
-                                                      const int *__restrict__ iperm, const double *__restrict__ frames,
-                                                      const double *__restrict__ R, E *__restrict__ X) {
-  if ((int)blockIdx.x >= *ntask >> 1) return;
-  const int2 tk = tasks[blockIdx.x];
-  rhs_assemble_column<E>(sup, tk.x, 4 * (tk.y >> 16) + (threadIdx.x >> 6), threadIdx.x & 63, child, invmap_off,
-                         invmap, lohi, order, node_ids, iperm, frames, R, X);
+__global__ __launch_bounds__(256) void k_rhs_init(const SupDev *__restrict__ sup, int nlev,
+                                                  const int *__restrict__ asm_first, const int *__restrict__ task_off,
+                                                  const int *__restrict__ task_cnt, const int2 *__restrict__ tasks,
+                                                  const int *__restrict__ child, const int *__restrict__ invmap_off,
+                                                  const int *__restrict__ invmap, const int *__restrict__ lohi,
+                                                  const int *__restrict__ order, const int *__restrict__ node_ids,
+                                                  const int *__restrict__ iperm, const double *__restrict__ frames,
+                                                  const double *__restrict__ R, E *__restrict__ X) {
+  int l = 0;
+  while (l + 1 < nlev && asm_first[l + 1] <= (int)blockIdx.x) ++l;
+  const int t = blockIdx.x - asm_first[l];
+  if (t >= task_cnt[RHS_KINDS * l + RT_ASM] >> 1) return;
+  const int2 tk = tasks[task_off[RHS_KINDS * l + RT_ASM] + t];
+  rhs_init_column<E>(sup, tk.x, 4 * (tk.y >> 16) + (threadIdx.x >> 6), threadIdx.x & 63, child, invmap_off, invmap,
+                     lohi, order, node_ids, iperm, frames, R, X);
 }
 
 // The product kernels' tiles hold the transposed product (the accumulator's
@@ -434,12 +423,17 @@ __global__ __launch_bounds__(256) void k_rhs_diag(const SupDev *__restrict__ sup
     rhs_diag_tile<typename RhsAcc<E>::Mid>(S, r, tk, linv, X, Z, Z64, z64, lds);
 }
 
-// X_s[n_s:] -= L_21 Z_s, one tile per task
+// X_parent = X_s[n_s:] - L_21 Z_s on the front rows below s, one tile per
+// task; added there when the parents' columns hold a residual.  The store goes
+// straight to the parent's front, in place of a store to X_s and a kernel per
+// level that gathered the children's rows (8 to 24 us a level at 200 to 1000
+// contacts, and three passes over X).  W_H of 1000 contacts at 61 236 DOF:
+// 2.10 -> 1.97 ms, of 400 mapped ones at 12 288: 475 -> 426 us.
 template <class Ac>
 __device__ void rhs_off_tile(const SupDev &S, int r, int2 tk, const typename Ac::elem *__restrict__ front,
-                             const typename Ac::elem *__restrict__ Z, typename Ac::elem *__restrict__ X,
+                             const typename Ac::elem *__restrict__ Z, const typename Ac::elem *__restrict__ X,
+                             const int *__restrict__ rel, typename Ac::elem *__restrict__ Xp, long fp, bool add,
                              typename Ac::elem *lds) {
-  typedef typename Ac::elem E;
   constexpr int T = Ac::T;
   const int n3 = 3 * S.ncol, b3 = 3 * S.nb, f = n3 + b3;
   const int i0 = T * (tk.y >> 16), j0 = T * (tk.y & 0xffff);
@@ -448,30 +442,35 @@ __device__ void rhs_off_tile(const SupDev &S, int r, int2 tk, const typename Ac:
   Ac acc;
   acc.zero();
   acc.template acc<false, true>(Z + S.z_off + (long)j0 * n3, n3, front + S.front_off + n3 + i0, f, N, M, 0, n3, lds);
-  E *Xs = X + S.x_off + n3 + i0 + (long)j0 * f;
-  acc.update(Xs, f, Xs, f, N, M, [](int, int) { return true; }, [](int, int, E v, E old) { return old - v; });
+  acc.push(Xp + (long)j0 * fp, fp, [&](int i) { return 3 * rel[(i0 + i) / 3] + (i0 + i) % 3; },
+           X + S.x_off + n3 + i0 + (long)j0 * f, f, N, M, add);
 }
 template <class E>
 __global__ __launch_bounds__(256) void k_rhs_off(const SupDev *__restrict__ sup, const int2 *__restrict__ tasks,
                                                  const int *__restrict__ ntask, const int *__restrict__ lohi,
-                                                 const E *__restrict__ front, const E *__restrict__ Z,
-                                                 E *__restrict__ X) {
+                                                 const int *__restrict__ relmap, const E *__restrict__ front,
+                                                 const E *__restrict__ Z, E *X, int add) {
   __shared__ E lds[RhsAcc<E>::LDS];
   int2 tk;
   bool small;
   if (!rhs_my_task(tasks, ntask, tk, small)) return;
   const int s = tk.x;
   const SupDev S = sup[s];
-  const int r = 3 * (lohi[3 * s + 2] - lohi[3 * s]);
+  const int lo = lohi[3 * s], hi = lohi[3 * s + 2], r = 3 * (hi - lo);
+  // the parent's columns of these contacts; none if the plan emptied its range
+  const int p = S.parent, plo = lohi[3 * p];
+  if (lo < plo || hi > lohi[3 * p + 1]) return;
+  const long fp = 3L * (sup[p].ncol + sup[p].nb);
+  E *Xp = X + sup[p].x_off + 3L * (lo - plo) * fp;
   if (small)
-    rhs_off_tile<typename RhsAcc<E>::Small>(S, r, tk, front, Z, X, lds);
+    rhs_off_tile<typename RhsAcc<E>::Small>(S, r, tk, front, Z, X, relmap + S.rows_off, Xp, fp, add, lds);
   else
-    rhs_off_tile<typename RhsAcc<E>::Mid>(S, r, tk, front, Z, X, lds);
+    rhs_off_tile<typename RhsAcc<E>::Mid>(S, r, tk, front, Z, X, relmap + S.rows_off, Xp, fp, add, lds);
 }
 
 // Residual of the forward solve on a supernode's own rows (FP64, the
 // refinement of the mixed-precision build): R_s = X_s[:n_s] - L_ss Z_s with
-// X_s assembled in FP64 from the unit columns and the children's FP64
+// X_s in FP64, from the unit columns and the children's FP64
 // updates; L_ss is the lower triangle of the front's diagonal block.
 template <class Ac>
 __device__ void rhs_resid_tile(const SupDev &S, int r, int2 tk, const double *__restrict__ front,
@@ -1063,6 +1062,14 @@ void ensure_rhs_capacity(icr_scene *s, int nc) {
       }
     }
     if (tot > INT32_MAX) throw std::runtime_error("multi-RHS task lists exceed 2^31 entries");
+    std::vector<int> asm_first(nlev);
+    F.asm_cap = 0;
+    for (int l = 0; l < nlev; ++l) {
+      asm_first[l] = F.asm_cap;
+      F.asm_cap += F.rhs_cap[RHS_KINDS * l + RT_ASM];
+    }
+    F.d_asm_first = F.rhs_arena.alloc<int>(nlev);
+    ICR_HIP(hipMemcpyAsync(F.d_asm_first, asm_first.data(), nlev * sizeof(int), hipMemcpyHostToDevice, s->stream));
     F.d_rhs_tasks = F.rhs_arena.alloc<int2>(std::max<long long>(1, tot));
     F.d_rhs_off = F.rhs_arena.alloc<int>(F.rhs_off.size());
     F.d_rhs_cnt = F.rhs_arena.alloc<int>(F.rhs_off.size());
@@ -1150,26 +1157,32 @@ void wh_finish(icr_scene *s, int nc, TW *WH) {
   ICR_LAUNCH_CHECK();
 }
 
+template <class E>
+void rhs_init(icr_scene *s, const int *node_ids, const double *frames, const double *R, E *X) {
+  auto &F = s->fac;
+  k_rhs_init<E><<<std::max(1, F.asm_cap), 256, 0, s->stream>>>(
+      F.d_sup, (int)F.levels.size(), F.d_asm_first, F.d_rhs_off, F.d_rhs_cnt, F.d_rhs_tasks, F.d_child, F.d_invmap_off,
+      F.d_invmap, F.d_lohi, F.d_order, node_ids, F.d_iperm, frames, R, X);
+  ICR_LAUNCH_CHECK();
+}
+
 // One forward sweep over the tree levels in FP32 (the bulk solve of the
-// mixed-precision build): X32 assembled from the unit columns (R null) or
+// mixed-precision build): X32 from the unit columns (R null) or
 // from the residual R and the children, Z32 = L_ss^-1 X32 with its FP64 copy
 // stored (z64 = 1) or added (z64 = 2) into Z, X32 below rows -= L_21 Z32.
 void forward_fp32(icr_scene *s, const int *node_ids, const double *R, int z64) {
   auto &F = s->fac;
   hipStream_t st = s->stream;
   RhsLists L{F};
+  rhs_init<float>(s, node_ids, nullptr, R, F.d_X32);
   for (int l = 0; l < (int)F.levels.size(); ++l) {
     if (!L.any(l, RT_ASM)) continue;
-    k_rhs_assemble<float><<<L.grid(l, RT_ASM), 256, 0, st>>>(F.d_sup, L.list(l, RT_ASM), L.count(l, RT_ASM),
-                                                             F.d_child, F.d_invmap_off, F.d_invmap, F.d_lohi,
-                                                             F.d_order, node_ids, F.d_iperm, nullptr, R, F.d_X32);
-    ICR_LAUNCH_CHECK();
     k_rhs_diag<float><<<L.grid(l, RT_DIAG), 256, 0, st>>>(F.d_sup, L.list(l, RT_DIAG), L.count(l, RT_DIAG),
                                                            F.d_lohi, F.d_linv32, F.d_X32, F.d_Z32, F.d_Z, z64);
     ICR_LAUNCH_CHECK();
     if (L.any(l, RT_OFF)) {
       k_rhs_off<float><<<L.grid(l, RT_OFF), 256, 0, st>>>(F.d_sup, L.list(l, RT_OFF), L.count(l, RT_OFF), F.d_lohi,
-                                                           F.d_front32, F.d_Z32, F.d_X32);
+                                                        F.d_relmap, F.d_front32, F.d_Z32, F.d_X32, R != nullptr);
       ICR_LAUNCH_CHECK();
     }
   }
@@ -1206,13 +1219,9 @@ void build_WH_device(icr_scene *s, int nc, const int *node_ids, double *WH, bool
   const long long m = 3LL * nc;
   rhs_prepare(s, nc, node_ids, validate);
   RhsLists L{F};
+  rhs_init<double>(s, node_ids, frames, nullptr, F.d_X);
   for (int l = 0; l < (int)F.levels.size(); ++l) {
     if (!L.any(l, RT_ASM)) continue;   // no supernode of the level can hold a contact column
-    k_rhs_assemble<double><<<L.grid(l, RT_ASM), 256, 0, st>>>(F.d_sup, L.list(l, RT_ASM), L.count(l, RT_ASM),
-                                                              F.d_child, F.d_invmap_off, F.d_invmap, F.d_lohi,
-                                                              F.d_order, node_ids, F.d_iperm, frames, nullptr,
-                                                              F.d_X);
-    ICR_LAUNCH_CHECK();
     k_rhs_diag<double><<<L.grid(l, RT_DIAG), 256, 0, st>>>(F.d_sup, L.list(l, RT_DIAG), L.count(l, RT_DIAG), F.d_lohi,
                                                          F.d_linv, F.d_X, F.d_Z, nullptr, 0);
     ICR_LAUNCH_CHECK();
@@ -1230,7 +1239,7 @@ void build_WH_device(icr_scene *s, int nc, const int *node_ids, double *WH, bool
     ICR_LAUNCH_CHECK();
     if (L.any(l, RT_OFF)) {
       k_rhs_off<double><<<L.grid(l, RT_OFF), 256, 0, st>>>(F.d_sup, L.list(l, RT_OFF), L.count(l, RT_OFF), F.d_lohi,
-                                                         F.d_front, F.d_Z, F.d_X);
+                                                         F.d_relmap, F.d_front, F.d_Z, F.d_X, 0);
       ICR_LAUNCH_CHECK();
     }
   }
@@ -1250,19 +1259,15 @@ void build_WH_mixed(icr_scene *s, int nc, const int *node_ids, int refine, float
   forward_fp32(s, node_ids, nullptr, 1);   // Z32 and its FP64 copy Z
   for (int it = 0; it < refine; ++it) {
     // FP64 residual of L Z = P H^T on every supernode's rows, level by level
+    rhs_init<double>(s, node_ids, nullptr, nullptr, F.d_X);
     for (int l = 0; l < (int)F.levels.size(); ++l) {
       if (!L.any(l, RT_ASM)) continue;
-      k_rhs_assemble<double><<<L.grid(l, RT_ASM), 256, 0, st>>>(F.d_sup, L.list(l, RT_ASM), L.count(l, RT_ASM),
-                                                                F.d_child, F.d_invmap_off, F.d_invmap, F.d_lohi,
-                                                                F.d_order, node_ids, F.d_iperm, nullptr, nullptr,
-                                                                F.d_X);
-      ICR_LAUNCH_CHECK();
       k_rhs_resid<<<L.grid(l, RT_DIAG), 256, 0, st>>>(F.d_sup, L.list(l, RT_DIAG), L.count(l, RT_DIAG),
                                                             F.d_lohi, F.d_front, F.d_X, F.d_Z, F.d_R);
       ICR_LAUNCH_CHECK();
       if (L.any(l, RT_OFF)) {
         k_rhs_off<double><<<L.grid(l, RT_OFF), 256, 0, st>>>(F.d_sup, L.list(l, RT_OFF), L.count(l, RT_OFF), F.d_lohi,
-                                                           F.d_front, F.d_Z, F.d_X);
+                                                           F.d_relmap, F.d_front, F.d_Z, F.d_X, 0);
         ICR_LAUNCH_CHECK();
       }
     }

@@ -87,6 +87,7 @@ struct Factor {
   std::vector<LevelInfo> levels;
   SupDev *d_sup = nullptr;
   int *d_rows = nullptr, *d_child = nullptr, *d_invmap_off = nullptr, *d_invmap = nullptr;
+  int *d_relmap = nullptr;   // local node in the parent's front of each below-row node (at rows_off)
   int *d_sup_by_tiles = nullptr;   // supernodes by descending number of 64-column tiles
   std::vector<int> tiles_desc;     // those numbers
   int max_tiles = 0;
@@ -106,8 +107,9 @@ struct Factor {
   // multi-RHS product tasks per (height level, kind), built on the device
   // from the contact ranges: (supernode, tile row << 16 | tile column)
   int2 *d_rhs_tasks = nullptr;
-  int *d_rhs_off = nullptr, *d_rhs_cnt = nullptr, *d_level_first = nullptr;
+  int *d_rhs_off = nullptr, *d_rhs_cnt = nullptr, *d_level_first = nullptr, *d_asm_first = nullptr;
   std::vector<int> rhs_off, rhs_cap;   // first entry and capacity of each list
+  int asm_cap = 0;                     // capacity of all levels' first lists together
   int4 *d_zf_tasks = nullptr;
   int n_zf_tasks = 0, n_zf_sum_tasks = 0;   // the first n_zf_sum_tasks tasks have chunk 0
   double *d_zf_part = nullptr;
