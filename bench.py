@@ -269,10 +269,10 @@ def main():
                     help="also time this many steps with the directions updated before every local solve; 0 = skip")
     ap.add_argument("--graph", action="store_true",
                     help="replay the captured step graph instead of launching every step eagerly (eager is about "
-                         "1%% faster here: the graph replay loses part of the overlap of the W_H products)")
+                         "as fast here)")
     ap.add_argument("--no-graph", action="store_true", help="eager launches (the default; kept for old commands)")
     ap.add_argument("--no-overlap", action="store_true",
-                    help="run the W_H products of a tree level on the scene's own stream instead of a second one")
+                    help="call set_overlap(False) (one stream is used either way; kept for old commands)")
     ap.add_argument("--serving", type=int, default=0, metavar="SCENES",
                     help="also run the serving mix: this many independent scenes (node count 500-8000, 10-500 "
                          "contacts) stepped through icr_server; 0 = skip")

@@ -78,13 +78,10 @@ const char *icr_last_error(const icr_scene *s);
 /* Rebind the scene to another stream (e.g. torch's current stream). */
 icr_status icr_set_stream(icr_scene *s, void *stream);
 
-/* enable = 1 (default): the multi-RHS solve of icr_build_WH / icr_step runs
- * the W_H products of each elimination-tree level on a second stream of the
- * scene, overlapping the next level's solve (joined before the call's later
- * work).  enable = 0: everything on the scene's stream -- what many scenes
- * stepped concurrently want, since every extra stream takes a place among
- * the process's few hardware queues.  Same results either way.
- * ICR_E_ARG unless enable is 0 or 1. */
+/* Accepted for callers that chose between one stream and two: the W_H
+ * products of icr_build_WH / icr_step are one launch after the multi-RHS solve
+ * and all work runs on the scene's stream either way.  ICR_E_ARG unless enable
+ * is 0 or 1. */
 icr_status icr_set_overlap(icr_scene *s, int32_t enable);
 
 /*
@@ -408,8 +405,7 @@ icr_status icr_server_set_batching(icr_server *srv, int32_t group, double max_wa
  * budget.  A request runs on a slot's stream; when it completes (or its
  * launch fails) the scene is set back to the stream it had at admission, so
  * that direct calls on the scene after its requests have completed
- * (icr_destroy included) run on its own stream.  Admission also turns the
- * scene's second stream off (icr_set_overlap(scene, 0)). */
+ * (icr_destroy included) run on its own stream. */
 icr_status icr_server_admit(icr_server *srv, icr_scene *scene, int32_t *scene_id);
 /* Remove an idle scene (no request queued or in flight: else ICR_E_STATE);
  * its bytes return to the budget.  The scene itself is not destroyed. */

@@ -377,6 +377,12 @@ void prepare_factor(icr_scene *s) {
   for (int s_ = 0; s_ < ns; ++s_)
     for (int p = sym.col0[s_]; p < sym.col0[s_] + sym.ncol[s_]; ++p) sup_of_node[sym.perm[p]] = s_;
 
+  std::vector<int> anc_ptr(ns + 1, 0), anc;
+  for (int s_ = 0; s_ < ns; ++s_) {
+    for (int a = s_; a >= 0; a = sym.parent[a]) anc.push_back(a);
+    anc_ptr[s_ + 1] = (int)anc.size();
+  }
+
   std::vector<int> by_tiles(ns);
   std::iota(by_tiles.begin(), by_tiles.end(), 0);
   auto tiles = [&](int s_) { return cdiv(3 * F.sup[s_].ncol, TILE); };
@@ -401,6 +407,8 @@ void prepare_factor(icr_scene *s) {
   F.d_invmap_off = A.upload(invmap_off, st);
   F.d_invmap = A.upload(invmap, st);
   F.d_relmap = A.upload(relmap, st);
+  F.d_anc_ptr = A.upload(anc_ptr, st);
+  F.d_anc = A.upload(anc, st);
   F.d_level_sup = A.upload(sym.level_sup, st);
   F.d_sup_by_tiles = A.upload(by_tiles, st);
   F.d_perm = A.upload(sym.perm, st);
@@ -458,9 +466,6 @@ void icr_destroy(icr_scene *s) {
   const bool settled = s->settle();
   s->sg.reset();
   if (s->sg.cap) (void)hipStreamDestroy(s->sg.cap);
-  if (s->ev_fork) (void)hipEventDestroy(s->ev_fork);
-  if (s->ev_join) (void)hipEventDestroy(s->ev_join);
-  if (s->side) (void)hipStreamDestroy(s->side);
   s->con.arena.release(settled);
   s->map_arena.release(settled);
   s->pairs.arena.release(settled);
@@ -487,10 +492,6 @@ icr_status icr_set_stream(icr_scene *s, void *stream) {
 icr_status icr_set_overlap(icr_scene *s, int32_t enable) {
   return guarded(s, [&] {
     REQUIRE(enable == 0 || enable == 1, "enable must be 0 or 1");
-    if (s->overlap != (enable == 1)) {
-      s->overlap = enable == 1;
-      s->epoch++;   // a captured step graph holds the other launch pattern
-    }
     return ICR_OK;
   });
 }

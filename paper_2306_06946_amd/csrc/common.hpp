@@ -115,7 +115,9 @@ struct AccMT {
     int n;              // valid i
     int i, k;           // of q = 0
     unsigned off[NE];   // byte offset of element q from p, BUF_OUT at an i that the buffer's end does not catch
-    __device__ __forceinline__ Stage(const E *P, long ld_, int n_, int k0) : ld(ld_), n(n_) {
+    // i0: the operand's first row is the tile's row i0 (rows before it are
+    // zero: their offsets wrap past every buffer's end; rows not contiguous)
+    __device__ __forceinline__ Stage(const E *P, long ld_, int n_, int k0, int i0 = 0) : ld(ld_), n(n_) {
       const int tid = threadIdx.x;
       i = F ? tid % T : tid / KC;
       k = F ? tid / T : tid % KC;
@@ -123,7 +125,7 @@ struct AccMT {
 #pragma unroll
       for (int q = 0; q < NE; ++q)
         off[q] = (unsigned)sizeof(E) * (F ? (unsigned)i + (unsigned)(k + 256 / T * q) * (unsigned)ld
-                                          : (unsigned)k + (unsigned)(i + 256 / KC * q) * (unsigned)ld);
+                                          : (unsigned)k + (unsigned)(i - i0 + 256 / KC * q) * (unsigned)ld);
       if (F && i >= n)
 #pragma unroll
         for (int q = 0; q < NE; ++q) off[q] = BUF_OUT;
@@ -149,9 +151,6 @@ struct AccMT {
   template <bool AF, bool BF, bool TRI = false>
   __device__ void acc(const E *A, long lda, const E *B, long ldb, int M, int N, int k0, int k1, E *lds, int tri = 0) {
     static_assert(!TRI || BF, "a triangle is staged with its columns contiguous");
-    const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-    const int r0 = (T / 2) * (w >> 1), c0 = (T / 2) * (w & 1);
-    const int li = l & 15, lk = l >> 4;
     if (k0 >= k1) return;
     Stage<AF> sa(A, lda, M, k0);
     Stage<BF> sb(B, ldb, N, k0);
@@ -173,19 +172,63 @@ struct AccMT {
         sa.load(ra, kc);
         sb.load(rb, kc);
       }
+      products(lds, KC);
+      __syncthreads();
+    }
+  }
+  // c += the staged chunk, its first have columns (in sixteens)
+  __device__ __forceinline__ void products(const E *lds, int have) {
+    const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
+    const int r0 = (T / 2) * (w >> 1), c0 = (T / 2) * (w & 1);
+    const int li = l & 15, lk = l >> 4;
 #pragma unroll
-      for (int kk = 0; kk < KC; kk += 4) {
-        const int k = kk + lk;
-        E av[WB], bv[WB];
+    for (int kk = 0; kk < KC; kk += 4) {
+      if (kk % 16 == 0 && kk >= have) break;
+      const int k = kk + lk;
+      E av[WB], bv[WB];
 #pragma unroll
-        for (int a = 0; a < WB; ++a) av[a] = lds[k * TP + r0 + 16 * a + li];
+      for (int a = 0; a < WB; ++a) av[a] = lds[k * TP + r0 + 16 * a + li];
 #pragma unroll
-        for (int b = 0; b < WB; ++b) bv[b] = lds[KC * TP + k * TP + c0 + 16 * b + li];
+      for (int b = 0; b < WB; ++b) bv[b] = lds[KC * TP + k * TP + c0 + 16 * b + li];
 #pragma unroll
-        for (int a = 0; a < WB; ++a)
+      for (int a = 0; a < WB; ++a)
 #pragma unroll
-          for (int b = 0; b < WB; ++b) c[a][b] = Mfma<E>::op(av[a], bv[b], c[a][b]);
+        for (int b = 0; b < WB; ++b) c[a][b] = Mfma<E>::op(av[a], bv[b], c[a][b]);
+    }
+  }
+  // c += sum over q < n of A_q^T B_q; get(q, A, an, as, B, bn, bs, rows) names
+  // the an columns at A, of that many rows, that meet the tile from its row as
+  // on, and the bn at B from its column bs.  The staging runs ahead across q.
+  template <class G>
+  __device__ void chain_product(int n, G &&get, E *lds) {
+    const E *A, *B;
+    int an, as, bn, bs, left, q = 0;
+    get(0, A, an, as, B, bn, bs, left);
+    Stage<false> sa(A, left, an, 0, as), sb(B, left, bn, 0, bs);
+    E ra[NE], rb[NE];
+    int kc = min(KC, left);
+    sa.load(ra, kc);
+    sb.load(rb, kc);
+    while (q < n) {
+      const int have = kc;
+      sa.store(ra, lds);
+      sb.store(rb, lds + KC * TP);
+      __syncthreads();
+      left -= kc;
+      if (left > 0) {
+        sa.next();
+        sb.next();
+      } else if (++q < n) {
+        get(q, A, an, as, B, bn, bs, left);
+        sa = Stage<false>(A, left, an, 0, as);
+        sb = Stage<false>(B, left, bn, 0, bs);
       }
+      if (q < n) {
+        kc = min(KC, left);
+        sa.load(ra, kc);
+        sb.load(rb, kc);
+      }
+      products(lds, have);
       __syncthreads();
     }
   }

@@ -8,9 +8,8 @@
 //   X_s  = unit columns of its own contacts, children's updates
 //   Z_s  = L_ss^{-1} X_s[:n_s]                   (triangular dense product)
 //   X_parent[rows below s] = X_s[n_s:] - L_21 Z_s
-//   Wp[range_s, range_s] += Z_s^T Z_s            (lower tiles; ranges of one
-//                                                 level are disjoint)
-// then W_H is read out of Wp in contact order (exactly symmetric).
+// then Wp = Z^T Z over the supernodes that two contacts share, and W_H is read
+// out of it in contact order (exactly symmetric).
 //
 // Single RHS (free motion, corrective motion): the same forward sweep with one
 // dense column, then the backward sweep top-down
@@ -91,7 +90,7 @@ __device__ inline int lower_bound_i(const int *a, int n, int x) {
   return lo;
 }
 
-enum { RT_ASM = 0, RT_DIAG = 1, RT_SYRK = 2, RT_OFF = 3, RHS_KINDS = 4 };
+enum { RT_ASM = 0, RT_DIAG = 1, RT_OFF = 2, RHS_KINDS = 3 };
 
 // Tile edges of the multi-RHS products.  A level's list of one kind is cut
 // into 32 x 32 tiles if it has fewer than RHS_SMALL tiles of 64 x 64 and into
@@ -104,26 +103,24 @@ constexpr int RHS_T = 64, RHS_TS = 32;
 constexpr int RHS_SMALL = 512;
 
 // Tasks of the multi-RHS products of one supernode with r RHS columns, n3
-// DOF columns and b3 below rows, for tiles of edge T[kind]: assemble (4
-// columns per task), L_ss^{-1} X (row tile x column tile), Z^T Z (lower
-// column-tile pairs), L_21 Z (below-row tile x column tile).  The host
-// evaluates the same counts at r = rmax for the list capacities.
+// DOF columns and b3 below rows, for tiles of edge T[kind]: set X up (4
+// columns per task), L_ss^{-1} X (row tile x column tile), L_21 Z (below-row
+// tile x column tile).  The host evaluates the same counts at r = rmax for the
+// list capacities.
 __host__ __device__ inline void rhs_task_counts(int r, int n3, int b3, const int T[RHS_KINDS], int c[RHS_KINDS]) {
   if (r <= 0) {
-    c[RT_ASM] = c[RT_DIAG] = c[RT_SYRK] = c[RT_OFF] = 0;
+    c[RT_ASM] = c[RT_DIAG] = c[RT_OFF] = 0;
     return;
   }
   auto tiles = [&](int len, int k) { return (len + T[k] - 1) / T[k]; };
-  const int ts = tiles(r, RT_SYRK);
   c[RT_ASM] = (r + 3) / 4;
   c[RT_DIAG] = tiles(n3, RT_DIAG) * tiles(r, RT_DIAG);
-  c[RT_SYRK] = ts * (ts + 1) / 2;
   c[RT_OFF] = tiles(b3, RT_OFF) * tiles(r, RT_OFF);
 }
 
-// Order of a supernode's tiles in its list: bands of RHS_BAND columns (rows
-// for Z^T Z) of tiles, across the band first, so that tiles that follow one
-// another share panels of both operands.
+// Order of tiles: bands of RHS_BAND columns (rows for Z^T Z) of tiles, across
+// the band first, so that tiles that follow one another share panels of both
+// operands.
 constexpr int RHS_BAND = 8;
 // u-th tile of a grid with nr rows and nc columns
 __device__ inline void band_index(int u, int nr, int nc, int &i, int &j) {
@@ -153,8 +150,8 @@ __device__ inline void band_tri_index(int u, int n, int &i, int &j) {
 // over the supernode's capacity, reachable only with duplicate ids, which are
 // flagged, is emptied), then the level's task lists: one entry (supernode,
 // tile row << 16 | tile column) per tile that has work, in supernode order,
-// and the list lengths (2 x length + 1 if its tiles are the small ones).  The products launch one workgroup per entry of the
-// list's capacity; those past its length return after one uniform load (a
+// and the list lengths (2 x length + 1 if its tiles are the small ones).  The
+// products launch one workgroup per entry of the list's capacity; those past its length return after one uniform load (a
 // grid laid out by supernode and static column capacity would have most of
 // its workgroups find no columns, each after three dependent loads).
 constexpr int PLAN_NT = 1024;     // threads
@@ -182,7 +179,7 @@ __global__ __launch_bounds__(PLAN_NT) void k_rhs_plan(int nc, const int *__restr
   // the ranges, and each kind's number of tiles of 64
   if (tid < RHS_KINDS) wtot[tid] = 0;
   __syncthreads();
-  int tile[RHS_KINDS] = {RHS_T, RHS_T, RHS_T, RHS_T};
+  int tile[RHS_KINDS] = {RHS_T, RHS_T, RHS_T};
   for (int q = first + tid; q < last; q += PLAN_CHUNK) {
     if (tid >= PLAN_CHUNK) break;
     const int sn = level_sup[q];
@@ -204,12 +201,12 @@ __global__ __launch_bounds__(PLAN_NT) void k_rhs_plan(int nc, const int *__restr
   for (int k = RT_DIAG; k < RHS_KINDS; ++k)
     if (wtot[k] < RHS_SMALL) tile[k] = RHS_TS;
   __syncthreads();
-  int run[RHS_KINDS] = {0, 0, 0, 0};
+  int run[RHS_KINDS] = {0, 0, 0};
   for (int base = first; base < last; base += PLAN_CHUNK) {
     // task counts and their exclusive prefix over the chunk (waves
     // 0 .. PLAN_CHUNK / 64 - 1)
     const int q = base + tid;
-    int c[RHS_KINDS] = {0, 0, 0, 0};
+    int c[RHS_KINDS] = {0, 0, 0};
     if (tid < PLAN_CHUNK && q < last) {
       const int sn = level_sup[q];
       const SupDev &S = sup[sn];
@@ -272,8 +269,6 @@ __global__ __launch_bounds__(PLAN_NT) void k_rhs_plan(int nc, const int *__restr
         if (k == RT_DIAG) {   // deepest row tiles first (their product runs over k < i0 + T)
           band_index(u, sn3t[qq], tr, ti, tj);
           ti = sn3t[qq] - 1 - ti;
-        } else if (k == RT_SYRK) {
-          band_tri_index(u, tr, ti, tj);
         } else if (k == RT_OFF) {
           band_index(u, sb3t[qq], tr, ti, tj);
         }
@@ -332,12 +327,14 @@ __device__ inline void rhs_init_column(const SupDev *__restrict__ sup, int s, in
   for (int q = 0; q < S.nchild; ++q) {
     const int ch = child[S.child_off + q];
     if (p >= lohi[3 * ch] && p < lohi[3 * ch + 2]) {
+      if (sup[ch].nb == S.ncol + S.nb) return;   // the child reaches every row
       im = invmap + invmap_off[S.child_off + q];
       break;
     }
   }
-  for (int i = l; i < f; i += 64)
-    if (im == nullptr || im[i / 3] < 0) Xc[i] = E(0);
+  for (int i = l; i < S.ncol + S.nb; i += 64)
+    if (im == nullptr || im[i] < 0)
+      for (int a_ = 0; a_ < 3; ++a_) Xc[3 * i + a_] = E(0);
 }
 
 // All levels in one launch: asm_first[l] is the first workgroup of level l.
@@ -507,65 +504,124 @@ __global__ __launch_bounds__(256) void k_rhs_resid(const SupDev *__restrict__ su
     rhs_resid_tile<RhsAcc<double>::Mid>(S, r, tk, front, X, Z, R, lds);
 }
 
-// Wp[3lo + i][3lo + j] += sum_k Z(k, i) Z(k, j), one lower tile of the r x r
-// block per task
-template <class Ac>
-__device__ void rhs_syrk_tile(const SupDev &S, int lo, int r, int2 tk, const double *__restrict__ Z, int m,
-                              double *__restrict__ Wp, double *lds) {
-  constexpr int T = Ac::T;
-  const int i0 = T * (tk.y >> 16), j0 = T * (tk.y & 0xffff);
-  if (i0 >= r || j0 > i0) return;
-  const int n3 = 3 * S.ncol;
-  const int M = min(T, r - i0), N = min(T, r - j0);
-  const double *Zs = Z + S.z_off;
-  Ac acc;
-  acc.zero();
-  acc.template acc<false, false>(Zs + (long)i0 * n3, n3, Zs + (long)j0 * n3, n3, M, N, 0, n3, lds);
-  double *C = Wp + (long)(3 * lo + i0) * m + 3 * lo + j0;
-  acc.update(C, m, C, m, M, N, [](int, int) { return true; }, [](int, int, double v, double old) { return old + v; });
-}
-__global__ __launch_bounds__(256) void k_rhs_syrk(const SupDev *__restrict__ sup, const int2 *__restrict__ tasks,
-                                                  const int *__restrict__ ntask, const int *__restrict__ lohi,
-                                                  const double *__restrict__ Z, int m, double *__restrict__ Wp) {
-  __shared__ double lds[RhsAcc<double>::LDS];
-  int2 tk;
-  bool small;
-  if (!rhs_my_task(tasks, ntask, tk, small)) return;
-  const int s = tk.x;
-  const SupDev S = sup[s];
-  const int lo = lohi[3 * s];
-  const int r = 3 * (lohi[3 * s + 2] - lo);
-  if (small)
-    rhs_syrk_tile<RhsAcc<double>::Small>(S, lo, r, tk, Z, m, Wp, lds);
-  else
-    rhs_syrk_tile<RhsAcc<double>::Mid>(S, lo, r, tk, Z, m, Wp, lds);
-}
-
 __global__ void k_fill(long n, double v, double *__restrict__ x) {
   for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x) x[i] = v;
 }
 
-// Mirror the lower triangle of Wp (supernode order) into the upper one,
-// 64 x 64 tiles through LDS so that both the read and the transposed write
-// are coalesced; tiles (I >= J) of the lower triangle.
-__global__ __launch_bounds__(256) void k_wp_mirror(int m, double *__restrict__ Wp) {
-  __shared__ double t[64][65];
-  const int nt = (m + 63) / 64;
-  if ((int)blockIdx.x >= nt * (nt + 1) / 2) return;
-  int I, J;
-  tri_index(blockIdx.x, I, J);
-  const int i0 = 64 * I, j0 = 64 * J;
-  const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-  for (int r = ty; r < 64; r += 4) {
-    const int i = i0 + r, j = j0 + tx;
-    t[r][tx] = (i < m && j < m) ? Wp[(long)i * m + j] : 0.0;
+// Wp = Z^T Z in supernode order of the contacts, one tile (I >= J) and its
+// mirror image per workgroup.  Entry (i, j) sums over the supernodes above both
+// contacts, which are the common part of their paths to the root: a tile below
+// the diagonal meets the supernodes that hold its last column's and its first
+// row's contact, one path; a diagonal tile meets the paths of all of its
+// contacts (each supernode is taken at its first contact in the tile).  One
+// launch after the solve, in place of one per level that added into Wp beside
+// it on a second stream: the waits between the streams cost 10 us a level, and
+// Wp was cleared, read and written once per level and mirrored.  W_H of 200
+// contacts at 9 450 DOF: 303 -> 237 us, of 3000 at 75 600: 10.1 -> 9.5 to
+// 10.0 ms; of 1000 at 61 236 it costs what it saves (2.04 -> 2.03 to 2.07 ms).
+//
+// Tile order: few tiles go by their distance from the diagonal, the longest
+// paths first (1000 contacts: 2.17 ms in bands); WP_BAND or more go in bands
+// that share panels (3000 contacts: 10.7 ms by distance).  Below WP_SMALL tiles
+// of 64 the tiles are 32 x 32: at 1128 tiles those cost 3 %.
+constexpr int WP_SMALL = 512, WP_BAND = 4096;
+constexpr int WP_SEG = 128;   // supernodes per pass
+struct WpSeg {
+  long z;             // Z_s
+  int n3, lo, hi;     // rows, contact range in DOF columns
+};
+template <class Ac>
+__global__ __launch_bounds__(256) void k_wp_tiles(int nc, int nsup, bool band, const SupDev *__restrict__ sup,
+                                                  const int *__restrict__ keys, const int *__restrict__ lohi,
+                                                  const int *__restrict__ anc_ptr, const int *__restrict__ anc,
+                                                  const double *__restrict__ Z, double *__restrict__ Wp) {
+  constexpr int T = Ac::T;
+  __shared__ double lds[Ac::LDS];
+  __shared__ WpSeg seg[WP_SEG];
+  __shared__ int snseg, snext[2];
+  static_assert(T * (T + 1) <= Ac::LDS, "the tile is turned in the staging space");
+  const int m = 3 * nc, nt = (m + T - 1) / T;
+  int I = blockIdx.x, J = I;
+  if (band) {
+    if (I >= nt) {
+      band_tri_index(I - nt, nt - 1, I, J);
+      ++I;
+    }
+  } else {
+    tri_index(nt * (nt + 1) / 2 - 1 - blockIdx.x, I, J);
+    I = J + nt - 1 - I;
   }
+  const int i0 = T * I, j0 = T * J, M = min(T, m - i0), N = min(T, m - j0);
+  const int tid = threadIdx.x, ln = tid & 63;
+  const int p0 = i0 / 3, pc = (j0 + N - 1) / 3;            // first row's, last column's contact
+  const int pend = I == J ? (i0 + M - 1) / 3 : p0;         // contacts whose paths are met
+  Ac acc;
+  acc.zero();
+  int p = p0, d0 = 0;   // next contact, and position on its path
+  while (p <= pend) {
+    // the next supernodes, up to WP_SEG of them
+    __syncthreads();
+    if (tid < 64) {
+      int n = 0;
+      while (p <= pend && n + 64 <= WP_SEG) {
+        const int own = keys[p];
+        const int a0 = own < nsup ? anc_ptr[own] : 0, len = own < nsup ? anc_ptr[own + 1] - a0 : 0;
+        const int d = len - 1 - d0 - ln;   // from the root down
+        bool take = false;
+        WpSeg sg = {};
+        if (d >= 0) {
+          const int s = anc[a0 + d], lo = lohi[3 * s], hi = lohi[3 * s + 2];
+          take = hi > p && (I == J ? max(lo, p0) == p : lo <= pc);
+          sg = {sup[s].z_off, 3 * sup[s].ncol, 3 * lo, 3 * hi};
+        }
+        const unsigned long long mask = __ballot(take);
+        if (take) seg[n + __popcll(mask & ((1ull << ln) - 1))] = sg;
+        n += __popcll(mask);
+        d0 += 64;
+        if (d0 >= len) {
+          d0 = 0;
+          ++p;
+        }
+      }
+      if (ln == 0) {
+        snseg = n;
+        snext[0] = p;
+        snext[1] = d0;
+      }
+    }
+    __syncthreads();
+    const int nseg = __builtin_amdgcn_readfirstlane(snseg);
+    p = snext[0];
+    d0 = snext[1];
+    // their rows, chunk by chunk, the next chunk in flight
+    if (nseg > 0)
+      acc.chain_product(nseg, [&](int q, const double *&A, int &an, int &as, const double *&B, int &bn, int &bs, int &n3) {
+        const WpSeg g = seg[q];
+        n3 = __builtin_amdgcn_readfirstlane(g.n3);
+        const int lo = __builtin_amdgcn_readfirstlane(g.lo), hi = __builtin_amdgcn_readfirstlane(g.hi);
+        const long z = ((long)__builtin_amdgcn_readfirstlane((int)(g.z >> 32)) << 32) |
+                       (unsigned)__builtin_amdgcn_readfirstlane((int)g.z);
+        as = max(0, lo - i0);
+        an = min(M, hi - i0) - as;
+        bs = max(0, lo - j0);
+        bn = min(N, hi - j0) - bs;
+        A = Z + z + (long)(i0 + as - lo) * n3;
+        B = Z + z + (long)(j0 + bs - lo) * n3;
+      }, lds);
+  }
+  // the lower part from the tile, the upper part turned
   __syncthreads();
-  // upper entry (j0 + r, i0 + tx) = lower entry (i0 + tx, j0 + r) when strictly below the diagonal
-  for (int r = ty; r < 64; r += 4) {
-    const int row = j0 + r, col = i0 + tx;
-    if (row < m && col < m && col > row) Wp[(long)row * m + col] = t[tx][r];
+  acc.for_each([&](int i, int j, double v) { lds[i * (T + 1) + j] = v; });
+  __syncthreads();
+  for (int e = tid; e < T * T; e += 256) {
+    const int i = e / T, j = e % T;
+    if (i < M && j < N) Wp[(long)(i0 + i) * m + j0 + j] = I == J && j > i ? lds[j * (T + 1) + i] : lds[i * (T + 1) + j];
   }
+  if (I != J)
+    for (int e = tid; e < T * T; e += 256) {
+      const int j = e / T, i = e % T;
+      if (i < M && j < N) Wp[(long)(j0 + j) * m + i0 + i] = lds[i * (T + 1) + j];
+    }
 }
 
 // W_H[3c+a][3c'+b] = Wp[3 pos(c) + a][3 pos(c') + b] (Wp symmetric): one
@@ -1004,11 +1060,6 @@ void launch_fill(icr_scene *s, double *x, long n, double v) {
 }
 
 void ensure_rhs_capacity(icr_scene *s, int nc) {
-  if (s->overlap && !s->side) {
-    ICR_HIP(hipStreamCreateWithFlags(&s->side, hipStreamNonBlocking));
-    ICR_HIP(hipEventCreateWithFlags(&s->ev_fork, hipEventDisableTiming));
-    ICR_HIP(hipEventCreateWithFlags(&s->ev_join, hipEventDisableTiming));
-  }
   auto &F = s->fac;
   if (nc <= F.nc_cap) return;
   s->epoch++;
@@ -1042,7 +1093,7 @@ void ensure_rhs_capacity(icr_scene *s, int nc) {
       const LevelInfo &L = F.levels[l];
       level_first[l] = L.first;
       level_first[l + 1] = L.first + L.count;
-      const int T[RHS_KINDS] = {RHS_T, RHS_T, RHS_T, RHS_T}, TS[RHS_KINDS] = {RHS_TS, RHS_TS, RHS_TS, RHS_TS};
+      const int T[RHS_KINDS] = {RHS_T, RHS_T, RHS_T}, TS[RHS_KINDS] = {RHS_TS, RHS_TS, RHS_TS};
       long long mid[RHS_KINDS] = {}, small[RHS_KINDS] = {};
       for (int q = 0; q < L.count; ++q) {
         const SupDev &d = F.sup[F.sym.level_sup[L.first + q]];
@@ -1131,8 +1182,6 @@ void rhs_prepare(icr_scene *s, int nc, const int *node_ids, bool validate) {
   k_rhs_plan<<<nlev, PLAN_NT, 0, st>>>(nc, F.d_level_first, F.d_level_sup, F.d_sup, F.d_keys, F.d_lohi, F.d_rhs_off,
                                       F.d_rhs_cnt, F.d_rhs_tasks);
   ICR_LAUNCH_CHECK();
-  k_fill<<<1024, 256, 0, st>>>(m * m, 0.0, F.d_Wp);
-  ICR_LAUNCH_CHECK();
 }
 
 // Launch geometry of a product: its list's capacity (one workgroup per task;
@@ -1145,15 +1194,24 @@ struct RhsLists {
   bool any(int l, int k) const { return F.rhs_cap[RHS_KINDS * l + k] > 0; }
 };
 
-// Wp (mirrored) -> W_H in contact order, FP64 or FP32.
+// Z -> Wp, and Wp -> W_H in contact order, FP64 or FP32.
+void wh_tiles(icr_scene *s, int nc) {
+  auto &F = s->fac;
+  auto go = [&](int T, auto kernel) {
+    const long nt = cdiv(3L * nc, T), n = nt * (nt + 1) / 2;
+    kernel<<<(unsigned)n, 256, 0, s->stream>>>(nc, (int)F.sup.size(), n >= WP_BAND, F.d_sup, F.d_keys, F.d_lohi,
+                                                   F.d_anc_ptr, F.d_anc, F.d_Z, F.d_Wp);
+  };
+  const long nt = cdiv(3L * nc, RHS_T);
+  if (nt * (nt + 1) / 2 < WP_SMALL)
+    go(RHS_TS, k_wp_tiles<RhsAcc<double>::Small>);
+  else
+    go(RHS_T, k_wp_tiles<RhsAcc<double>::Mid>);
+  ICR_LAUNCH_CHECK();
+}
 template <class TW>
 void wh_finish(icr_scene *s, int nc, TW *WH) {
-  auto &F = s->fac;
-  const long long m = 3LL * nc;
-  const int nt = cdiv(m, 64);
-  k_wp_mirror<<<nt * (nt + 1) / 2, 256, 0, s->stream>>>((int)m, F.d_Wp);
-  ICR_LAUNCH_CHECK();
-  k_wh_unpermute<TW><<<(unsigned)m, 256, 0, s->stream>>>(nc, F.d_pos, F.d_Wp, WH);
+  k_wh_unpermute<TW><<<3u * nc, 256, 0, s->stream>>>(nc, s->fac.d_pos, s->fac.d_Wp, WH);
   ICR_LAUNCH_CHECK();
 }
 
@@ -1225,28 +1283,13 @@ void build_WH_device(icr_scene *s, int nc, const int *node_ids, double *WH, bool
     k_rhs_diag<double><<<L.grid(l, RT_DIAG), 256, 0, st>>>(F.d_sup, L.list(l, RT_DIAG), L.count(l, RT_DIAG), F.d_lohi,
                                                          F.d_linv, F.d_X, F.d_Z, nullptr, 0);
     ICR_LAUNCH_CHECK();
-    // Z of this level is final: its W_H products go to the side stream (they
-    // read Z and write Wp only, which nothing on the main stream touches
-    // until the join)
-    hipStream_t sy = st;
-    if (s->overlap) {
-      ICR_HIP(hipEventRecord(s->ev_fork, st));
-      ICR_HIP(hipStreamWaitEvent(s->side, s->ev_fork, 0));
-      sy = s->side;
-    }
-    k_rhs_syrk<<<L.grid(l, RT_SYRK), 256, 0, sy>>>(F.d_sup, L.list(l, RT_SYRK), L.count(l, RT_SYRK), F.d_lohi,
-                                                         F.d_Z, (int)m, F.d_Wp);
-    ICR_LAUNCH_CHECK();
     if (L.any(l, RT_OFF)) {
       k_rhs_off<double><<<L.grid(l, RT_OFF), 256, 0, st>>>(F.d_sup, L.list(l, RT_OFF), L.count(l, RT_OFF), F.d_lohi,
                                                          F.d_relmap, F.d_front, F.d_Z, F.d_X, 0);
       ICR_LAUNCH_CHECK();
     }
   }
-  if (s->overlap) {
-    ICR_HIP(hipEventRecord(s->ev_join, s->side));
-    ICR_HIP(hipStreamWaitEvent(st, s->ev_join, 0));
-  }
+  wh_tiles(s, nc);
   wh_finish<double>(s, nc, WH);
 }
 
@@ -1273,23 +1316,12 @@ void build_WH_mixed(icr_scene *s, int nc, const int *node_ids, int refine, float
     }
     forward_fp32(s, node_ids, F.d_R, 2);   // Z += L^-1 R (FP32 solve of the correction)
   }
-  // W_H = Z^T Z in FP64 from the refined Z
-  for (int l = 0; l < (int)F.levels.size(); ++l) {
-    if (!L.any(l, RT_ASM)) continue;
-    k_rhs_syrk<<<L.grid(l, RT_SYRK), 256, 0, st>>>(F.d_sup, L.list(l, RT_SYRK), L.count(l, RT_SYRK), F.d_lohi,
-                                                         F.d_Z, (int)m, F.d_Wp);
-    ICR_LAUNCH_CHECK();
-  }
-  const int nt = cdiv(m, 64);
-  k_wp_mirror<<<nt * (nt + 1) / 2, 256, 0, st>>>((int)m, F.d_Wp);
-  ICR_LAUNCH_CHECK();
+  wh_tiles(s, nc);   // W_H = Z^T Z in FP64 from the refined Z
   if (WH32) {
-    k_wh_unpermute<float><<<(unsigned)m, 256, 0, st>>>(nc, F.d_pos, F.d_Wp, WH32);
-    ICR_LAUNCH_CHECK();
+    wh_finish<float>(s, nc, WH32);
   }
   if (WH64) {
-    k_wh_unpermute<double><<<(unsigned)m, 256, 0, st>>>(nc, F.d_pos, F.d_Wp, WH64);
-    ICR_LAUNCH_CHECK();
+    wh_finish<double>(s, nc, WH64);
   }
 }
 

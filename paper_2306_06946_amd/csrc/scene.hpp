@@ -87,6 +87,7 @@ struct Factor {
   std::vector<LevelInfo> levels;
   SupDev *d_sup = nullptr;
   int *d_rows = nullptr, *d_child = nullptr, *d_invmap_off = nullptr, *d_invmap = nullptr;
+  int *d_anc_ptr = nullptr, *d_anc = nullptr;   // supernode, its parent, ... up to the root
   int *d_relmap = nullptr;   // local node in the parent's front of each below-row node (at rows_off)
   int *d_sup_by_tiles = nullptr;   // supernodes by descending number of 64-column tiles
   std::vector<int> tiles_desc;     // those numbers
@@ -267,19 +268,13 @@ struct icr_scene {
   long epoch = 0;          // bumped whenever device buffers are (re)allocated
   int clock_khz = 0;       // device wall-clock rate used by the phase stamps
   StepGraph sg;
-  // second stream of the multi-RHS solve: the W_H products of a tree level
-  // run there while the main stream goes on with the next level's solve
-  bool overlap = true;
-  hipStream_t side = nullptr;
-  hipEvent_t ev_fork = nullptr, ev_join = nullptr;
   bool moved = false;   // icr_set_stream changed the stream: work may be pending on the one before
-  // Waits for the scene's own streams; true if nothing that touches its
-  // buffers is pending.
+  // Waits for the scene's stream; true if nothing that touches its buffers is
+  // pending.
   bool settle() const {
-    const bool a = hipStreamSynchronize(stream) == hipSuccess;
-    const bool b = !side || hipStreamSynchronize(side) == hipSuccess;
-    if (!(a && b)) (void)hipGetLastError();
-    return a && b && !moved;
+    const bool done = hipStreamSynchronize(stream) == hipSuccess;
+    if (!done) (void)hipGetLastError();
+    return done && !moved;
   }
 };
 
