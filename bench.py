@@ -108,7 +108,7 @@ def profiled_issue(kernel):
 def serving_leg(n_scenes, rate, sweeps, slots, seconds=2.0, group=8, max_wait_ms=0.0):
     """Serving mix through icr_server: closed-loop saturation with 1, 4 and
     `slots` slots (Newton loops of the requests started together batched into
-    one launch), the same at `slots` slots without batching, then Poisson
+    together), the same at `slots` slots without batching, then Poisson
     arrivals at `rate` steps/s over `seconds` on `slots` slots, batched."""
     import torch
     from paper_2306_06946_amd import icr
@@ -281,7 +281,7 @@ def main():
     ap.add_argument("--serving-seconds", type=float, default=2.0,
                     help="length of each closed-loop window and of the Poisson run")
     ap.add_argument("--serving-group", type=int, default=8,
-                    help="requests per slot and round of the serving mix, their Newton loops in one launch "
+                    help="requests per slot and round of the serving mix, their Newton loops together "
                          "(0: one whole step per slot)")
     ap.add_argument("--serving-max-wait", type=float, default=0.0,
                     help="ms a short serving group waits for more requests while a slot runs")

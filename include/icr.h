@@ -350,8 +350,8 @@ icr_status icr_analyze(const double *nodes, int32_t N, const int32_t *tets, int3
  * (icr_server_set_batching); a slot runs its group in its stream's order: the requests whose Newton loops allow it
  * (fast scheme, ICR_FP64, no pair contacts, at most 512 contacts, untimed)
  * run their steps up to the Newton loop, then all their Newton loops
- * (Algorithm 3, steps 1-4) in one persistent launch with one workgroup per
- * scene, then the rest of their steps; other requests run icr_step(scene,
+ * (Algorithm 3, steps 1-4) together, one launch per step of an iteration for
+ * the whole group, then the rest of their steps; other requests run icr_step(scene,
  * obstacle, opts, NULL) whole.  The slot is free again when its whole group
  * completed.  Requests of one scene run in submission order; those of
  * different scenes overlap on the device.  Either way a request's results
@@ -386,7 +386,7 @@ icr_status icr_server_create(icr_server **out, int64_t hbm_budget, int32_t slots
 void icr_server_destroy(icr_server *srv); /* waits for the requests in flight */
 const char *icr_server_last_error(const icr_server *srv);
 /* group in [1, 64] (8 by default): requests a slot takes per round, their
- * Newton loops batched into one launch where the step allows it; group = 0:
+ * Newton loops batched where the step allows it; group = 0:
  * one request per slot, run as icr_step whole (the Newton loop then runs as
  * the scene's own kernels, in a captured graph when opts.graph is set).  The
  * batched loop computes every value as the per-scene kernels do, in the same

@@ -1289,6 +1289,10 @@ icr_status step_begin(icr_scene *s, const icr_obstacle *obs, const icr_step_opts
     t.status = C.d_status;
     t.sweeps = C.d_sweeps;
     t.ctl = C.pgs.ctl;
+    t.rec = C.pgs.rec;
+    t.gS = C.pgs.gS;
+    t.Sidx = C.pgs.Sidx;
+    t.nS = C.pgs.nS;
     std::memcpy(task, &t, sizeof t);
     return ICR_OK;
   });
@@ -1302,13 +1306,19 @@ icr_status step_end(icr_scene *s, const icr_step_opts *opt) {
   });
 }
 
-icr_status newton_batch(void *stream, const void *tasks, const int *idx, int n, std::string &msg) {
+icr_status newton_batch(void *stream, const void *tasks, const void *host, const int *idx, int n, std::string &msg) {
   try {
-    if (!tasks || !idx || n < 1 || n > kNewtonBatchMax) throw ArgError("newton_batch: 1..64 tasks");
+    if (!tasks || !host || !idx || n < 1 || n > kNewtonBatchMax) throw ArgError("newton_batch: 1..64 tasks");
     NewtonBatchIdx b{};
     b.n = n;
-    for (int i = 0; i < n; ++i) b.idx[i] = idx[i];
-    launch_newton_batch((hipStream_t)stream, static_cast<const NewtonTask *>(tasks), b);
+    int max_nc = 1, max_newton = 0;
+    for (int i = 0; i < n; ++i) {
+      const NewtonTask &t = static_cast<const NewtonTask *>(host)[idx[i]];
+      b.idx[i] = idx[i];
+      max_nc = std::max(max_nc, t.nc);
+      max_newton = std::max(max_newton, t.n_newton);
+    }
+    launch_newton_batch((hipStream_t)stream, static_cast<const NewtonTask *>(tasks), b, max_nc, max_newton);
     return ICR_OK;
   } catch (const ArgError &e) {
     msg = e.what();

@@ -238,12 +238,12 @@ __device__ inline void pair_frame(const double n[3], const double pc[3], const d
 // Frames C_k and gaps at p_{k-1}; d_k = delta - C_k (p - p_free); warm start
 // lambda = C_k f with f the previous world-frame force.  The first npair
 // contacts are pairs with normals pn.
-__global__ void k_directions(int nc, const StepCtx *__restrict__ ctx, const double *__restrict__ p,
-                             const double *__restrict__ pfree, const double *__restrict__ pstart,
-                             const double *__restrict__ fprev, double *__restrict__ C, double *__restrict__ dk,
-                             double *__restrict__ lam, int npair, const double *__restrict__ pn) {
-  int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= nc) return;
+__device__ __forceinline__ void directions_contact(int c, const StepCtx *__restrict__ ctx, const double *__restrict__ p,
+                                                   const double *__restrict__ pfree,
+                                                   const double *__restrict__ pstart,
+                                                   const double *__restrict__ fprev, double *__restrict__ C,
+                                                   double *__restrict__ dk, double *__restrict__ lam, int npair,
+                                                   const double *__restrict__ pn) {
   const icr_obstacle obs = ctx->obs;
   const double t0 = ctx->t0, t1 = ctx->t0 + ctx->h;
   double pc[3] = {p[3 * c], p[3 * c + 1], p[3 * c + 2]};
@@ -261,6 +261,13 @@ __global__ void k_directions(int nc, const StepCtx *__restrict__ ctx, const doub
     dk[3 * c + r] = delta[r] - (F[r][0] * dp[0] + F[r][1] * dp[1] + F[r][2] * dp[2]);
     lam[3 * c + r] = F[r][0] * fprev[3 * c] + F[r][1] * fprev[3 * c + 1] + F[r][2] * fprev[3 * c + 2];
   }
+}
+__global__ void k_directions(int nc, const StepCtx *__restrict__ ctx, const double *__restrict__ p,
+                             const double *__restrict__ pfree, const double *__restrict__ pstart,
+                             const double *__restrict__ fprev, double *__restrict__ C, double *__restrict__ dk,
+                             double *__restrict__ lam, int npair, const double *__restrict__ pn) {
+  const int c = blockIdx.x * blockDim.x + threadIdx.x;
+  if (c < nc) directions_contact(c, ctx, p, pfree, pstart, fprev, C, dk, lam, npair, pn);
 }
 
 // W_ab = C_a (W_H)_ab C_b^T.  Block (a, b) with a < b is computed as the
@@ -706,12 +713,10 @@ __device__ inline bool block_nonzero(const double *__restrict__ v, long c) {
 // contacts (v is then ignored): every block forms the entries it needs from
 // C and lambda, and block 0 also writes f for all contacts to fout.
 template <class TM>
-__global__ __launch_bounds__(SG_NT) void k_sym_gemv_sparse(int nc, const TM *__restrict__ M,
-                                                           const double *__restrict__ x0,
-                                                           const double *__restrict__ v, double h2,
-                                                           double *__restrict__ y, const double *__restrict__ C,
-                                                           const double *__restrict__ lam,
-                                                           double *__restrict__ fout) {
+__device__ __forceinline__ void sym_gemv_sparse(int nc, const TM *__restrict__ M, const double *__restrict__ x0,
+                                                const double *__restrict__ v, double h2, double *__restrict__ y,
+                                                const double *__restrict__ C, const double *__restrict__ lam,
+                                                double *__restrict__ fout) {
   __shared__ int list[SG_CHUNK];
   __shared__ double fl[3 * SG_CHUNK];   // world forces of the listed contacts (with C)
   __shared__ int wsum[SG_NW];
@@ -767,6 +772,15 @@ __global__ __launch_bounds__(SG_NT) void k_sym_gemv_sparse(int nc, const TM *__r
     for (int w = 0; w < SG_NW; ++w) t += part[w][ln];
     y[i] = x0[i] + h2 * t;
   }
+}
+template <class TM>
+__global__ __launch_bounds__(SG_NT) void k_sym_gemv_sparse(int nc, const TM *__restrict__ M,
+                                                           const double *__restrict__ x0,
+                                                           const double *__restrict__ v, double h2,
+                                                           double *__restrict__ y, const double *__restrict__ C,
+                                                           const double *__restrict__ lam,
+                                                           double *__restrict__ fout) {
+  sym_gemv_sparse<TM>(nc, M, x0, v, h2, y, C, lam, fout);
 }
 
 // Single-workgroup PGS.  g = d + W~ lambda (all contacts, own term included)
@@ -1410,13 +1424,12 @@ __device__ __forceinline__ double blk_value(long e, int nS, int nsp, const int *
 // (row q of contact i at q |S| + i: PgsRec, then the square roots of the
 // block's diagonal) and the gaps without the own term, e = g0 - W~_cc lambda_c.
 template <class TW>
-__global__ __launch_bounds__(256) void k_pgs_gather(int nc, const TW *__restrict__ W,
-                                                    const double *__restrict__ g0, const double *__restrict__ lam,
-                                                    const double *__restrict__ mu, double h2,
-                                                    int *__restrict__ Sidx_out, int *__restrict__ nS_out,
-                                                    double *__restrict__ gnSet, double *__restrict__ swn,
-                                                    double *__restrict__ Wss, double *__restrict__ rec,
-                                                    double *__restrict__ gS) {
+__device__ __forceinline__ void pgs_gather(int nc, const TW *__restrict__ W, const double *__restrict__ g0,
+                                           const double *__restrict__ lam, const double *__restrict__ mu, double h2,
+                                           int *__restrict__ Sidx_out, int *__restrict__ nS_out,
+                                           double *__restrict__ gnSet, double *__restrict__ swn,
+                                           double *__restrict__ Wss, double *__restrict__ rec,
+                                           double *__restrict__ gS) {
   __shared__ int Sidx[PGS_MAX_NC];
   __shared__ int wcount[PGS_MAX_NC / 64 + 1];
   __shared__ int nS_s;
@@ -1480,12 +1493,22 @@ __global__ __launch_bounds__(256) void k_pgs_gather(int nc, const TW *__restrict
     gS[r] = g0[cr + a] - own;
   }
 }
+template <class TW>
+__global__ __launch_bounds__(256) void k_pgs_gather(int nc, const TW *__restrict__ W,
+                                                    const double *__restrict__ g0, const double *__restrict__ lam,
+                                                    const double *__restrict__ mu, double h2,
+                                                    int *__restrict__ Sidx_out, int *__restrict__ nS_out,
+                                                    double *__restrict__ gnSet, double *__restrict__ swn,
+                                                    double *__restrict__ Wss, double *__restrict__ rec,
+                                                    double *__restrict__ gS) {
+  pgs_gather<TW>(nc, W, g0, lam, mu, h2, Sidx_out, nS_out, gnSet, swn, Wss, rec, gS);
+}
 
 // The sequential kernel's body, for one workgroup of PGS_NT threads with the
 // state L in its LDS (k_pgs_active, and each scene's workgroup of the batched
-// Newton loop).  npre: size of the set prepared by k_pgs_gather (preSidx,
-// preRec, preGS); a value above PGS_WAVE_MAX builds the first set here, from
-// g0, gnSet and swn.
+// Newton loops).  npre: size of the set prepared by pgs_gather (preSidx,
+// preRec, preGS); a value above PGS_WAVE_MAX is not prepared (the set is too
+// large for the chains, and handed over).
 template <class TW>
 __device__ __forceinline__ void pgs_active_body(PgsLds &L, int nc, const TW *__restrict__ W,
                                                 const double *__restrict__ d, const double *__restrict__ g0,
@@ -1803,8 +1826,6 @@ __global__ __launch_bounds__(PGS_NT) void k_pgs_active(int nc, const TW *__restr
                       gnSet, swn, ctl, preSidx, *preN, preRec, preGS);
 }
 
-// ---- batched Newton loops: one workgroup per scene --------------------------
-//
 // y[i] = x0[i] + h2 sum over the contacts c with a non-zero block of v
 // (ascending) of M[(3c + a) m + i] v[3c + a], by one workgroup (M symmetric,
 // rows of M read for its columns).  The order of every sum is that of
@@ -1856,13 +1877,20 @@ __device__ void wg_sym_gemv_sparse(int nc, const TM *__restrict__ M, const doubl
   }
 }
 
-// Algorithm 3's Newton loop (steps 1-4) of one scene per workgroup: frames
-// and gaps at the last proximity (the warm start in the new frames), W_k =
-// C_k W_H C_k^T, the PGS start gaps g0 = d + W~ lambda, the active-set PGS
-// (the sequential kernel's body; the first set is built in place), and the
-// world forces f = C^T lambda with the proximity p = p_free + h^2 W_H f
-// (Eq. 31).  Every value is computed as the per-scene kernels compute it, in
-// the same order, so a step's results do not depend on the path it took.
+// ---- batched Newton loops --------------------------------------------------
+//
+// Algorithm 3's Newton loops (steps 1-4) of a group of scenes, one launch per
+// step for all of them (blockIdx.y: the scene): frames and gaps at the last
+// proximity (the warm start in the new frames), W_k = C_k W_H C_k^T, the PGS
+// start gaps g0 = d + W~ lambda and the set, the active-set PGS (one workgroup
+// per scene), and the world forces f = C^T lambda with the proximity p = p_free
+// + h^2 W_H f (Eq. 31).  The bodies are those of the per-scene kernels, so a
+// step's results do not depend on the path it took.  One workgroup for a
+// scene's whole loop streamed W_H and W through a single compute unit, a third
+// of the loop's time: groups of three scenes of 10 to 500 contacts took 12.7 ms
+// a loop of five iterations, and take 9.6 ms, of which the PGS has 9.2.  The
+// iterations of a group run in step, so each waits for its largest set; that is
+// the same scene in most of them.
 // The task table as the device reads it: the same layout with every pointer
 // in the global address space, so that the code inlined below uses global
 // loads and their counters (a pointer read from memory is otherwise generic).
@@ -1874,76 +1902,62 @@ struct NewtonTaskG {
   gptr<const StepCtx> ctx;
   gptr<const double> WH, pfree, pstart, mu;
   gptr<double> W, p, f, C, dk, lam, eps;
-  gptr<double> g, Wss, gnSet, swn;
+  gptr<double> g, Wss, gnSet, swn, rec, gS;
   gptr<int8_t> status;
-  gptr<int> sweeps, ctl;
+  gptr<int> sweeps, ctl, Sidx, nS;
 };
-static_assert(sizeof(NewtonTaskG) == sizeof(NewtonTask) && offsetof(NewtonTaskG, ctl) == offsetof(NewtonTask, ctl),
+static_assert(sizeof(NewtonTaskG) == sizeof(NewtonTask) && offsetof(NewtonTaskG, nS) == offsetof(NewtonTask, nS),
               "device view of the task table");
 
-__global__ __launch_bounds__(PGS_NT) void k_newton_batch(const NewtonTask *__restrict__ tasks, NewtonBatchIdx ids) {
+// Scene blockIdx.y of the launch.
+__device__ __forceinline__ const NewtonTaskG &newton_task(const NewtonTask *__restrict__ tasks,
+                                                          const NewtonBatchIdx &ids) {
+  return reinterpret_cast<const NewtonTaskG *>(tasks)[ids.idx[blockIdx.y]];
+}
+__global__ void k_batch_directions(const NewtonTask *__restrict__ tasks, NewtonBatchIdx ids, int k) {
+  const NewtonTaskG &t = newton_task(tasks, ids);
+  const int c = blockIdx.x * blockDim.x + threadIdx.x;
+  if (k >= t.n_newton || c >= t.nc) return;
+  const gptr<const double> p = k == 0 ? t.pfree : (gptr<const double>)t.p;
+  directions_contact(c, (const StepCtx *)t.ctx, (const double *)p, (const double *)t.pfree, (const double *)t.pstart, (const double *)t.f, (double *)t.C,
+                     (double *)t.dk, (double *)t.lam, 0, nullptr);
+}
+__global__ void k_batch_update_W(const NewtonTask *__restrict__ tasks, NewtonBatchIdx ids, int k) {
+  const NewtonTaskG &t = newton_task(tasks, ids);
+  const long blk = (long)blockIdx.x * blockDim.x + threadIdx.x;
+  if (k >= t.n_newton || blk >= (long)t.nc * t.nc) return;
+  update_W_block(t.nc, (const double *)t.WH, (const double *)t.C, (double *)t.W, blk);
+}
+__global__ __launch_bounds__(SG_NT) void k_batch_gaps(const NewtonTask *__restrict__ tasks, NewtonBatchIdx ids, int k) {
+  const NewtonTaskG &t = newton_task(tasks, ids);
+  if (k >= t.n_newton || 64 * (int)blockIdx.x >= 3 * t.nc) return;
+  sym_gemv_sparse<double>(t.nc, (const double *)t.W, (const double *)t.dk, (const double *)t.lam, t.h * t.h,
+                          (double *)t.g, nullptr, nullptr, nullptr);
+}
+__global__ __launch_bounds__(SG_NT) void k_batch_proximity(const NewtonTask *__restrict__ tasks, NewtonBatchIdx ids,
+                                                           int k) {
+  const NewtonTaskG &t = newton_task(tasks, ids);
+  if (k >= t.n_newton || 64 * (int)blockIdx.x >= 3 * t.nc) return;
+  sym_gemv_sparse<double>(t.nc, (const double *)t.WH, (const double *)t.pfree, (const double *)t.lam, t.h * t.h,
+                          (double *)t.p, (const double *)t.C, (const double *)t.lam, (double *)t.f);
+}
+__global__ __launch_bounds__(256) void k_batch_gather(const NewtonTask *__restrict__ tasks, NewtonBatchIdx ids, int k) {
+  const NewtonTaskG &t = newton_task(tasks, ids);
+  if (k >= t.n_newton) return;
+  pgs_gather<double>(t.nc, (const double *)t.W, (const double *)t.g, (const double *)t.lam, (const double *)t.mu,
+                     t.h * t.h, (int *)t.Sidx, (int *)t.nS, (double *)t.gnSet, (double *)t.swn,
+                     (double *)t.Wss, (double *)t.rec, (double *)t.gS);
+}
+__global__ __launch_bounds__(PGS_NT) void k_batch_pgs(const NewtonTask *__restrict__ tasks, NewtonBatchIdx ids, int k) {
   extern __shared__ double lds_raw[];
   PgsLds &L = *reinterpret_cast<PgsLds *>(lds_raw);
-  const NewtonTaskG &tg = reinterpret_cast<const NewtonTaskG *>(tasks)[ids.idx[blockIdx.x]];
-  struct {
-    int nc, n_newton, max_sweeps, j_inner;
-    double tol, h;
-    const StepCtx *ctx;
-    const double *WH, *pfree, *pstart, *mu;
-    double *W, *p, *f, *C, *dk, *lam, *eps;
-    int8_t *status;
-    int *sweeps;
-  } t{tg.nc, tg.n_newton, tg.max_sweeps, tg.j_inner, tg.tol, tg.h, (const StepCtx *)tg.ctx,
-      (const double *)tg.WH, (const double *)tg.pfree, (const double *)tg.pstart, (const double *)tg.mu,
-      (double *)tg.W, (double *)tg.p, (double *)tg.f, (double *)tg.C, (double *)tg.dk, (double *)tg.lam,
-      (double *)tg.eps, (int8_t *)tg.status, (int *)tg.sweeps};
-  struct {
-    double *g, *Wss, *gnSet, *swn;
-    int *ctl;
-  } w{(double *)tg.g, (double *)tg.Wss, (double *)tg.gnSet, (double *)tg.swn, (int *)tg.ctl};
-  const int nc = t.nc, tid = threadIdx.x;
-  const long m = 3L * nc;
-  const double h2 = t.h * t.h;
-  for (int k = 0; k < t.n_newton; ++k) {
-    // step 1: frames and gaps at p_{k-1} (p_free for the first iteration)
-    {
-      const icr_obstacle obs = t.ctx->obs;
-      const double t0 = t.ctx->t0, t1 = t.ctx->t0 + t.ctx->h;
-      const double *p = (k == 0) ? t.pfree : t.p;
-      for (int c = tid; c < nc; c += PGS_NT) {
-        double pc[3] = {p[3 * c], p[3 * c + 1], p[3 * c + 2]};
-        double ps[3] = {t.pstart[3 * c], t.pstart[3 * c + 1], t.pstart[3 * c + 2]};
-        double F[3][3], delta[3];
-        contact_frame(obs, t0, t1, pc, ps, F, delta);
-        double dp[3] = {pc[0] - t.pfree[3 * c], pc[1] - t.pfree[3 * c + 1], pc[2] - t.pfree[3 * c + 2]};
-        for (int r = 0; r < 3; ++r) {
-          for (int a = 0; a < 3; ++a) t.C[9 * c + 3 * r + a] = F[r][a];
-          t.dk[3 * c + r] = delta[r] - (F[r][0] * dp[0] + F[r][1] * dp[1] + F[r][2] * dp[2]);
-          t.lam[3 * c + r] = F[r][0] * t.f[3 * c] + F[r][1] * t.f[3 * c + 1] + F[r][2] * t.f[3 * c + 2];
-        }
-      }
-    }
-    __syncthreads();
-    // step 2: W_k = C_k W_H C_k^T
-    for (long blk = tid; blk < (long)nc * nc; blk += PGS_NT) update_W_block(nc, t.WH, t.C, t.W, blk);
-    __syncthreads();
-    // PGS start gaps and the per-contact set data
-    wg_sym_gemv_sparse<double>(nc, t.W, t.dk, t.lam, t.lam, h2, w.g, L.ulist, &L.nu, L.lamS);
-    for (int c = tid; c < nc; c += PGS_NT) {
-      w.gnSet[c] = w.g[3 * c];
-      w.swn[c] = sqrt(h2 * t.W[(3L * c) * m + 3L * c]);
-    }
-    __syncthreads();
-    // step 3: PGS
-    pgs_active_body<double>(L, nc, t.W, t.dk, w.g, t.mu, h2, t.lam, t.status, t.max_sweeps, t.tol, t.j_inner,
-                            t.sweeps + k, t.eps + k, w.Wss, w.gnSet, w.swn, w.ctl, nullptr, PGS_WAVE_MAX + 1,
-                            nullptr, nullptr);
-    __syncthreads();
-    // step 4: world forces and the proximity update (Eq. 31)
-    for (long e = tid; e < m; e += PGS_NT) t.f[e] = world_force(t.C, t.lam, e / 3, (int)(e % 3));
-    __syncthreads();
-    wg_sym_gemv_sparse<double>(nc, t.WH, t.pfree, t.f, t.lam, h2, t.p, L.ulist, &L.nu, L.lamS);
-  }
+  const NewtonTaskG &t = newton_task(tasks, ids);
+  if (k >= t.n_newton) return;
+  pgs_active_body<double>(L, t.nc, (const double *)t.W, (const double *)t.dk, (const double *)t.g,
+                          (const double *)t.mu, t.h * t.h, (double *)t.lam, (int8_t *)t.status, t.max_sweeps,
+                          t.tol, t.j_inner, (int *)t.sweeps + k, (double *)t.eps + k, (double *)t.Wss,
+                          (double *)t.gnSet, (const double *)t.swn, (int *)t.ctl, (const int *)t.Sidx, *(const int *)t.nS,
+                          (const double *)t.rec, (const double *)t.gS);
 }
 
 // ---- directions updated before every local solve, on the register chain ----
@@ -3172,7 +3186,7 @@ void pgs_prepare() {
                               (int)pgs_pc_lds(PGS_MAX_NC)));
   ICR_HIP(hipFuncSetAttribute((const void *)k_pgs_coop<double>, hipFuncAttributeMaxDynamicSharedMemorySize,
                               (int)sizeof(PgsLds)));
-  ICR_HIP(hipFuncSetAttribute((const void *)k_newton_batch, hipFuncAttributeMaxDynamicSharedMemorySize,
+  ICR_HIP(hipFuncSetAttribute((const void *)k_batch_pgs, hipFuncAttributeMaxDynamicSharedMemorySize,
                               (int)sizeof(PgsLds)));
   ICR_HIP(hipFuncSetAttribute((const void *)k_pgs_pca, hipFuncAttributeMaxDynamicSharedMemorySize,
                               (int)sizeof(PcaLds)));
@@ -3191,11 +3205,26 @@ void pgs_prepare() {
   done |= bit;
 }
 
-void launch_newton_batch(hipStream_t st, const NewtonTask *tasks, const NewtonBatchIdx &ids) {
+void launch_newton_batch(hipStream_t st, const NewtonTask *tasks, const NewtonBatchIdx &ids, int max_nc,
+                         int max_newton) {
   if (ids.n < 1 || ids.n > kNewtonBatchMax) throw std::runtime_error("batched Newton loop: 1..64 scenes");
   pgs_prepare();
-  k_newton_batch<<<ids.n, PGS_NT, sizeof(PgsLds), st>>>(tasks, ids);
-  ICR_LAUNCH_CHECK();
+  const int nc = max_nc;
+  const dim3 one(1, ids.n), rows(cdiv(3L * nc, 64), ids.n);
+  for (int k = 0; k < max_newton; ++k) {
+    k_batch_directions<<<dim3(cdiv(nc, 128), ids.n), 128, 0, st>>>(tasks, ids, k);
+    ICR_LAUNCH_CHECK();
+    k_batch_update_W<<<dim3(cdiv((long)nc * nc, 256), ids.n), 256, 0, st>>>(tasks, ids, k);
+    ICR_LAUNCH_CHECK();
+    k_batch_gaps<<<rows, SG_NT, 0, st>>>(tasks, ids, k);
+    ICR_LAUNCH_CHECK();
+    k_batch_gather<<<dim3(std::max(32, 512 / ids.n), ids.n), 256, 0, st>>>(tasks, ids, k);
+    ICR_LAUNCH_CHECK();
+    k_batch_pgs<<<one, PGS_NT, sizeof(PgsLds), st>>>(tasks, ids, k);
+    ICR_LAUNCH_CHECK();
+    k_batch_proximity<<<rows, SG_NT, 0, st>>>(tasks, ids, k);
+    ICR_LAUNCH_CHECK();
+  }
 }
 
 void launch_world_force(hipStream_t st, int nc, const double *Cm, const double *lam, double *f) {

@@ -195,7 +195,7 @@ struct StepCtx {
   double h;
 };
 
-// One scene's Newton loop in the batched launch (k_newton_batch): sizes, its
+// One scene's Newton loop in the batched launches (k_batch_*): sizes, its
 // step options and device pointers into the scene (fast scheme, FP64, no
 // pair contacts, n_c <= kPgsWaveMax).
 struct NewtonTask {
@@ -204,9 +204,9 @@ struct NewtonTask {
   const StepCtx *ctx;
   const double *WH, *pfree, *pstart, *mu;
   double *W, *p, *f, *C, *dk, *lam, *eps;
-  double *g, *Wss, *gnSet, *swn;   // PGS work (PgsWork of the scene)
+  double *g, *Wss, *gnSet, *swn, *rec, *gS;   // PGS work (PgsWork of the scene)
   int8_t *status;
-  int *sweeps, *ctl;
+  int *sweeps, *ctl, *Sidx, *nS;
 };
 constexpr int kNewtonBatchMax = 64;   // scenes per batched launch
 struct NewtonBatchIdx {               // the table entries of one launch
@@ -346,7 +346,8 @@ constexpr inline size_t pgs_coop_blk_elems(int nc) {
 void pgs_prepare();   // kernel attributes (dynamic LDS), once per device; call outside graph capture
 // The Newton loops of the scenes tasks[ids.idx[0..n)] (device table), one
 // workgroup each, in one launch on stream st.
-void launch_newton_batch(hipStream_t st, const NewtonTask *tasks, const NewtonBatchIdx &ids);
+void launch_newton_batch(hipStream_t st, const NewtonTask *tasks, const NewtonBatchIdx &ids, int max_nc,
+                         int max_newton);
 int coop_grid();      // workgroups of the cooperative large-set PGS on this device (0: not available)
 void launch_pgs_per_constraint(hipStream_t st, int nc, const StepCtx *ctx, const double *WH, const double *pfree,
                                const double *p, const double *pstart, const double *mu, double h, double *f,

@@ -1,11 +1,10 @@
 // Serving runtime: admitted scenes, a FIFO of step requests and a fixed set
 // of slots (one HIP stream each).  The startable requests (the oldest of
 // idle scenes) are spread over the free slots, up to the group size per
-// slot, and each slot runs its group in its stream's order: with batching on, every request whose Newton loop
-// can run batched (fast scheme, FP64, no pair contacts, at most 512
-// contacts) enqueues its step up to the Newton loop, one launch runs all
-// their Newton loops (one workgroup per scene, k_newton_batch), then each
-// finishes its step; other requests run icr_step whole.  Each request ends
+// slot, and each slot runs its group in its stream's order: with batching on,
+// every request whose Newton loop can run batched (fast scheme, FP64, no pair
+// contacts, at most 512 contacts) enqueues its step up to the Newton loop, all
+// their Newton loops run together (k_batch_*), then each finishes its step; other requests run icr_step whole.  Each request ends
 // with a copy of its PGS eps values into its pinned host buffer (the step's
 // convergence status) and an event that marks its completion; the slot is
 // free again once its whole group completed.
@@ -207,10 +206,10 @@ void launch_ready(icr_server *srv) {
       sl.n++;
     }
     if (!batched.empty()) {
-      std::vector<int> idx(batched.size());
-      for (size_t q = 0; q < batched.size(); ++q) idx[q] = k * kGroupMax + batched[q];
       std::string msg;
-      const icr_status bst = icr::newton_batch(sl.stream, srv->d_tasks, idx.data(), (int)idx.size(), msg);
+      const icr_status bst =
+          icr::newton_batch(sl.stream, static_cast<char *>(srv->d_tasks) + (size_t)k * kGroupMax * srv->task_bytes,
+                            sl.task, batched.data(), (int)batched.size(), msg);
       for (int j : batched) {
         Member &m = sl.mem[j];
         SceneEntry &se = srv->scenes[m.req.scene];
