@@ -1073,10 +1073,15 @@ __global__ __launch_bounds__(1024) void k_pgs_pc(int nc, const StepCtx *__restri
 // with lambda^turn the force of S contacts before c in this sweep and after c
 // from the previous sweep.  Cauchy-Schwarz on the PSD matrix W~ bounds the
 // correction by sqrt(W~_cc) * sum_q sqrt(W~_qq) |lambda^turn_q - lambda^set_q|,
-// which settles almost every contact; the others are evaluated exactly.  On a
-// violation the violating contacts join S and the sweep restarts from its
-// start state, so the iterates are those of the full sequential sweep.  If S
-// outgrows PGS_SMAX the remaining sweeps go to k_pgs_single (ctl[0] = 1).
+// which settles almost every contact; the others are evaluated exactly, and
+// once as many have been as are skipped, all are and the sweep's end becomes
+// the reference state, from which the changes shrink as the sweeps converge.
+// (With the set's start as the only reference a warm start some way off left
+// the same contacts unsettled in every sweep: 1000 contacts of which 12 % are
+// pressed took 330 us a sweep, the chain of those 42; 30 sweeps 10.1 ms, now
+// 2.6.)  On a violation the violating contacts join S and the sweep restarts
+// from its start state, so the iterates are those of the full sequential
+// sweep.  If S outgrows PGS_SMAX the remaining sweeps go to k_pgs_single (ctl[0] = 1).
 constexpr int PGS_SMAX = 512;
 constexpr int PGS_S3 = 3 * PGS_SMAX;
 constexpr int PGS_NT = 512;   // threads of the active-set kernel
@@ -1536,6 +1541,7 @@ __device__ __forceinline__ void pgs_active_body(PgsLds &L, int nc, const TW *__r
   const int wu = __builtin_amdgcn_readfirstlane(wv);
   int sweep = 0, nS = 0, ldS = 0, nsp = 0;
   int nsweep = 0, prog = 0;   // sweeps run and contacts solved, restarted sweeps included
+  int nexact = 0;             // gaps evaluated exactly since the reference state was set
   double eps = 0.0;
   bool need_build = true, first_build = true, built = false;
   while (sweep < max_sweeps) {
@@ -1772,22 +1778,61 @@ __device__ __forceinline__ void pgs_active_body(PgsLds &L, int nc, const TW *__r
         if (!(g - rb > 1e-13 * (fabs(g) + rb))) L.ulist[atomicAdd(&L.nu, 1)] = (unsigned short)c;
       }
       __syncthreads();
-      const int nu = L.nu;
-      for (int u = wv; u < nu; u += PGS_NW) {   // exact gap at the turn of the unsettled contacts
-        const int c = L.ulist[u];
-        double a = 0.0;
+      int nu = L.nu;
+      nexact += nu;
+      const bool rebase = nexact >= nc - nS;
+      if (rebase) {   // all of them
+        nexact = 0;
+        __syncthreads();
+        if (tid == 0) L.nu = 0;
+        __syncthreads();
+        for (int c = tid; c < nc; c += PGS_NT)
+          if (!L.inS[c]) L.ulist[atomicAdd(&L.nu, 1)] = (unsigned short)c;
+        __syncthreads();
+        nu = L.nu;
+      }
+      // exact gaps at the contacts' turn (at) and at the sweep's end (ae), four
+      // contacts at a time, their rows of W in flight together
+      for (int u = 4 * wv; u < nu; u += 4 * PGS_NW) {
+        int c[4];
+        double at[4] = {0.0, 0.0, 0.0, 0.0}, ae[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) c[k] = L.ulist[min(u + k, nu - 1)];
         for (int q = ln; q < ldS; q += 64) {
-          const double lt = (L.Sidx[q / 3] < c) ? L.lamS[q] : L.lamS0[q];
-          a = fma(h2 * (double)W[(3L * c) * m + 3L * L.Sidx[q / 3] + q % 3], lt - L.lamSet[q], a);
+          const int s = L.Sidx[q / 3];
+          const double set = L.lamSet[q], de = L.lamS[q] - set, d0 = L.lamS0[q] - set;
+          const long col = 3L * s + q % 3;
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            const double w = h2 * (double)W[(3L * c[k]) * m + col];
+            at[k] = fma(w, s < c[k] ? de : d0, at[k]);
+            ae[k] = fma(w, de, ae[k]);
+          }
         }
-        for (int o = 32; o > 0; o >>= 1) a += __shfl_xor(a, o, 64);
-        if (ln == 0 && gnSet[c] + a < 0.0) {
-          L.inS[c] = 1;
-          L.flag = 1;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          for (int o = 32; o > 0; o >>= 1) {
+            at[k] += __shfl_xor(at[k], o, 64);
+            ae[k] += __shfl_xor(ae[k], o, 64);
+          }
+          if (ln == 0 && u + k < nu) {
+            const double g = gnSet[c[k]];
+            if (g + at[k] < 0.0) {
+              L.inS[c[k]] = 1;
+              L.flag = 1;
+            }
+            if (rebase) gnSet[c[k]] = g + ae[k];
+          }
         }
       }
       __syncthreads();
       grow = L.flag != 0 && !perr;
+      if (rebase && !grow) {
+        for (int r = tid; r < ldS; r += PGS_NT) L.lamSet[r] = L.lamS[r];
+        built = true;   // a new settle threshold
+        __threadfence_block();
+        __syncthreads();
+      }
     }
     if (grow) {
       // a skipped contact was not a no-op: restart the sweep with a larger S
@@ -3123,7 +3168,10 @@ void launch_pgs(hipStream_t st, int nc, const TW *W, const double *d, const doub
   // its buffers) the single-workgroup sweep
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   ICR_HIP(hipStreamIsCapturing(st, &cap));
-  const int G = coop_grid();
+  // one pushing workgroup to two chunks of gap rows at most: they poll and are
+  // polled at device level, and 127 of them slowed the lead's chain (1500
+  // contacts, 12 blocks: 81 us a block, 62 with 36)
+  const int G = std::min(coop_grid(), 1 + cdiv(3L * nc, 128));
   if (nc > PGS_WAVE_MAX && wk.Wblk != nullptr && G > 1 && cap == hipStreamCaptureStatusNone) {
     CoopArgs a{nc, W, d, mu, h * h, lam, status, max_sweeps, tol, j_inner, sweeps_dev, eps_dev, wk.ctl, wk.g,
                wk.recAll, wk.Wblk, wk.dl, wk.chg, wk.csync};
