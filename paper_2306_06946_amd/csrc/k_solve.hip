@@ -24,57 +24,54 @@ namespace {
 
 // ---- contact ordering -------------------------------------------------------
 
-// Sort the contacts by (supernode, node, index) with a bitonic network on a
-// packed 64-bit key.  Invalid ids (out of range, clamped) get the key nsup,
-// outside every supernode range, and duplicates are flagged; both make the
-// call fail on the host.
+// Sort the contacts by (supernode, node, index): SORT_C contacts per
+// workgroup, each one's place being the number of smaller packed 64-bit keys
+// (they are distinct), counted by 16 waves over a sixteenth of the keys in LDS
+// each.  (A bitonic network in one workgroup took 10, 19 and 61 us for 200,
+// 1000 and 3000 contacts; SORT_FIGURES.)  Invalid ids (out of range, clamped)
+// get the key nsup, outside every supernode range, and duplicates are flagged;
+// both make the call fail on the host.
+constexpr int SORT_C = 64;
 __global__ __launch_bounds__(1024) void k_sort_contacts(int nc, int N, int nsup, const int *__restrict__ node_ids,
                                                         const int *__restrict__ sup_of_node,
                                                         const uint8_t *__restrict__ fixed,
                                                         int *__restrict__ keys_sorted, int *__restrict__ order,
                                                         int *__restrict__ pos, int *__restrict__ cerr) {
   __shared__ unsigned long long kv[8192];
-  int n2 = 1;
-  while (n2 < nc) n2 <<= 1;
-  for (int i = threadIdx.x; i < n2; i += blockDim.x) {
-    unsigned long long v = ~0ull;
-    if (i < nc) {
-      int node = node_ids[i];
-      unsigned long long key = (unsigned long long)nsup, nd = 0;
-      if (node < 0 || node >= N || fixed[node]) {
-        atomicMax(cerr, 1);
-      } else {
-        key = (unsigned long long)sup_of_node[node];
-        nd = (unsigned long long)node;
-      }
-      v = (key << 37) | (nd << 13) | (unsigned long long)i;
+  __shared__ int part[16][SORT_C];
+  const int tid = threadIdx.x, ln = tid & 63, wv = tid >> 6;
+  for (int i = tid; i < nc; i += 1024) {
+    const int node = node_ids[i];
+    unsigned long long key = (unsigned long long)nsup, nd = 0;
+    if (node < 0 || node >= N || fixed[node]) {
+      atomicMax(cerr, 1);
+    } else {
+      key = (unsigned long long)sup_of_node[node];
+      nd = (unsigned long long)node;
     }
-    kv[i] = v;
+    kv[i] = (key << 37) | (nd << 13) | (unsigned long long)i;
   }
   __syncthreads();
-  for (int k = 2; k <= n2; k <<= 1) {
-    for (int j = k >> 1; j > 0; j >>= 1) {
-      for (int i = threadIdx.x; i < n2; i += blockDim.x) {
-        int l = i ^ j;
-        if (l > i) {
-          unsigned long long a = kv[i], b = kv[l];
-          bool up = ((i & k) == 0);
-          if ((a > b) == up) {
-            kv[i] = b;
-            kv[l] = a;
-          }
-        }
-      }
-      __syncthreads();
-    }
+  const int i = SORT_C * blockIdx.x + ln;
+  const unsigned long long mine = i < nc ? kv[i] : 0ull;
+  const int per = (nc + 15) / 16, j1 = min(nc, (wv + 1) * per);
+  int below = 0;
+  bool twin = false;
+#pragma unroll 4
+  for (int j = wv * per; j < j1; ++j) {
+    const unsigned long long v = kv[j];   // one key for the whole wave
+    below += v < mine ? 1 : 0;
+    twin |= (v >> 13) == (mine >> 13) && v != mine;
   }
-  for (int p = threadIdx.x; p < nc; p += blockDim.x) {
-    unsigned long long v = kv[p];
-    int c = (int)(v & 0x1fffull);
-    order[p] = c;
-    keys_sorted[p] = (int)(v >> 37);
-    pos[c] = p;
-    if (p > 0 && (kv[p - 1] >> 13) == (v >> 13) && (int)(v >> 37) < nsup) atomicMax(cerr, 2);
+  part[wv][ln] = below;
+  if (twin && i < nc && (int)(mine >> 37) < nsup) atomicMax(cerr, 2);
+  __syncthreads();
+  if (wv == 0 && i < nc) {
+    int p = 0;
+    for (int w = 0; w < 16; ++w) p += part[w][ln];
+    order[p] = i;
+    keys_sorted[p] = (int)(mine >> 37);
+    pos[i] = p;
   }
 }
 
@@ -102,20 +99,14 @@ enum { RT_ASM = 0, RT_DIAG = 1, RT_OFF = 2, RHS_KINDS = 3 };
 constexpr int RHS_T = 64, RHS_TS = 32;
 constexpr int RHS_SMALL = 512;
 
-// Tasks of the multi-RHS products of one supernode with r RHS columns, n3
-// DOF columns and b3 below rows, for tiles of edge T[kind]: set X up (4
-// columns per task), L_ss^{-1} X (row tile x column tile), L_21 Z (below-row
-// tile x column tile).  The host evaluates the same counts at r = rmax for the
-// list capacities.
-__host__ __device__ inline void rhs_task_counts(int r, int n3, int b3, const int T[RHS_KINDS], int c[RHS_KINDS]) {
-  if (r <= 0) {
-    c[RT_ASM] = c[RT_DIAG] = c[RT_OFF] = 0;
-    return;
-  }
-  auto tiles = [&](int len, int k) { return (len + T[k] - 1) / T[k]; };
-  c[RT_ASM] = (r + 3) / 4;
-  c[RT_DIAG] = tiles(n3, RT_DIAG) * tiles(r, RT_DIAG);
-  c[RT_OFF] = tiles(b3, RT_OFF) * tiles(r, RT_OFF);
+// Tasks of one kind of one supernode with r RHS columns, n3 DOF columns and
+// b3 below rows, for tiles of edge T: set X up (4 columns per task), L_ss^{-1}
+// X (row tile x column tile), L_21 Z (below-row tile x column tile).  The host
+// evaluates the same counts at r = rmax for the list capacities.
+__host__ __device__ inline int rhs_task_count(int kind, int r, int n3, int b3, int T) {
+  if (r <= 0) return 0;
+  if (kind == RT_ASM) return (r + 3) / 4;
+  return ((kind == RT_DIAG ? n3 : b3) + T - 1) / T * ((r + T - 1) / T);
 }
 
 // Order of tiles: bands of RHS_BAND columns (rows for Z^T Z) of tiles, across
@@ -145,15 +136,18 @@ __device__ inline void band_tri_index(int u, int n, int &i, int &j) {
   }
 }
 
-// k_rhs_plan (one block per height level): the contact range [lo, own, hi)
-// of every supernode of the level (contacts are sorted by supernode; a range
-// over the supernode's capacity, reachable only with duplicate ids, which are
-// flagged, is emptied), then the level's task lists: one entry (supernode,
-// tile row << 16 | tile column) per tile that has work, in supernode order,
-// and the list lengths (2 x length + 1 if its tiles are the small ones).  The
-// products launch one workgroup per entry of the list's capacity; those past its length return after one uniform load (a
-// grid laid out by supernode and static column capacity would have most of
-// its workgroups find no columns, each after three dependent loads).
+// k_rhs_plan (one workgroup per height level and kind): the contact range
+// [lo, own, hi) of every supernode of the level (contacts are sorted by
+// supernode; a range over the supernode's capacity, reachable only with
+// duplicate ids, which are flagged, is emptied), then the level's list of the
+// kind's tasks: one entry (supernode, tile row << 16 | tile column) per tile
+// that has work, in supernode order, and the list's length (2 x length + 1 if
+// its tiles are the small ones).  The products launch one workgroup per entry
+// of the list's capacity; those past its length return after one uniform load
+// (a grid laid out by supernode and static column capacity would have most of
+// its workgroups find no columns, each after three dependent loads).  8, 13 and
+// 15 us for 200, 1000 and 3000 contacts; 13, 19 and 30 with a workgroup for all
+// kinds of a level.
 constexpr int PLAN_NT = 1024;     // threads
 constexpr int PLAN_CHUNK = 256;   // supernodes per chunk (levels with more take several)
 constexpr int PLAN_KEYS = 4096;
@@ -162,123 +156,104 @@ __global__ __launch_bounds__(PLAN_NT) void k_rhs_plan(int nc, const int *__restr
                                                       const SupDev *__restrict__ sup, const int *__restrict__ keys,
                                                       int *__restrict__ lohi, const int *__restrict__ task_off,
                                                       int *__restrict__ task_cnt, int2 *__restrict__ tasks) {
-  __shared__ int pre[RHS_KINDS][PLAN_CHUNK];
-  __shared__ int wsum[RHS_KINDS][PLAN_CHUNK / 64];
-  __shared__ int wtot[RHS_KINDS];
-  __shared__ int ssup[PLAN_CHUNK], sr[PLAN_CHUNK], sn3t[PLAN_CHUNK], sb3t[PLAN_CHUNK];
+  __shared__ int pre[PLAN_CHUNK];
+  __shared__ int wsum[PLAN_CHUNK / 64];
+  __shared__ int wtot;
+  __shared__ int ssup[PLAN_CHUNK], sr[PLAN_CHUNK], snt[PLAN_CHUNK];
   __shared__ int skeys[PLAN_KEYS];
-  const int l = blockIdx.x, tid = threadIdx.x, ln = tid & 63, wv = tid >> 6;
+  const int l = blockIdx.x, k = blockIdx.y, tid = threadIdx.x, ln = tid & 63, wv = tid >> 6;
   const int first = level_first[l], last = level_first[l + 1];
   // the sorted keys are searched in LDS when they fit
   const int *kp = keys;
   if (nc <= PLAN_KEYS) {
     for (int i = tid; i < nc; i += PLAN_NT) skeys[i] = keys[i];
-    __syncthreads();
     kp = skeys;
   }
-  // the ranges, and each kind's number of tiles of 64
-  if (tid < RHS_KINDS) wtot[tid] = 0;
+  if (tid == 0) wtot = 0;
   __syncthreads();
-  int tile[RHS_KINDS] = {RHS_T, RHS_T, RHS_T};
-  for (int q = first + tid; q < last; q += PLAN_CHUNK) {
-    if (tid >= PLAN_CHUNK) break;
+  // the kind's number of tiles of 64 (the workgroup of kind 0 stores the ranges)
+  auto range = [&](const SupDev &S, int sn, int &lo, int &own, int &hi) {
+    lo = lower_bound_i(kp, nc, S.first_desc);
+    own = lower_bound_i(kp, nc, sn);
+    hi = lower_bound_i(kp, nc, sn + 1);
+    if (3 * (hi - lo) > S.rmax) own = hi = lo;
+  };
+  for (int q = first + tid; q < last; q += PLAN_NT) {
     const int sn = level_sup[q];
     const SupDev &S = sup[sn];
-    const int lo = lower_bound_i(kp, nc, S.first_desc);
-    int own = lower_bound_i(kp, nc, sn);
-    int hi = lower_bound_i(kp, nc, sn + 1);
-    if (3 * (hi - lo) > S.rmax) own = hi = lo;
-    lohi[3 * sn + 0] = lo;
-    lohi[3 * sn + 1] = own;
-    lohi[3 * sn + 2] = hi;
-    int c[RHS_KINDS];
-    rhs_task_counts(3 * (hi - lo), 3 * S.ncol, 3 * S.nb, tile, c);
-    for (int k = 0; k < RHS_KINDS; ++k)
-      if (c[k]) atomicAdd(&wtot[k], c[k]);
+    int lo, own, hi;
+    range(S, sn, lo, own, hi);
+    if (k == 0) {
+      lohi[3 * sn + 0] = lo;
+      lohi[3 * sn + 1] = own;
+      lohi[3 * sn + 2] = hi;
+    }
+    const int c = rhs_task_count(k, 3 * (hi - lo), 3 * S.ncol, 3 * S.nb, RHS_T);
+    if (c) atomicAdd(&wtot, c);
   }
   __syncthreads();
-#pragma unroll
-  for (int k = RT_DIAG; k < RHS_KINDS; ++k)
-    if (wtot[k] < RHS_SMALL) tile[k] = RHS_TS;
+  const int T = k != RT_ASM && wtot < RHS_SMALL ? RHS_TS : RHS_T;
   __syncthreads();
-  int run[RHS_KINDS] = {0, 0, 0};
+  int run = 0;
   for (int base = first; base < last; base += PLAN_CHUNK) {
     // task counts and their exclusive prefix over the chunk (waves
     // 0 .. PLAN_CHUNK / 64 - 1)
     const int q = base + tid;
-    int c[RHS_KINDS] = {0, 0, 0};
-    if (tid < PLAN_CHUNK && q < last) {
-      const int sn = level_sup[q];
-      const SupDev &S = sup[sn];
-      const int r = 3 * (lohi[3 * sn + 2] - lohi[3 * sn]), n3 = 3 * S.ncol, b3 = 3 * S.nb;
-      rhs_task_counts(r, n3, b3, tile, c);
-      ssup[tid] = sn;
-      sr[tid] = r;
-      sn3t[tid] = (n3 + tile[RT_DIAG] - 1) / tile[RT_DIAG];
-      sb3t[tid] = (b3 + tile[RT_OFF] - 1) / tile[RT_OFF];
-    }
-    int v[RHS_KINDS];
-#pragma unroll
-    for (int k = 0; k < RHS_KINDS; ++k) v[k] = c[k];
+    int c = 0, v = 0;
     if (tid < PLAN_CHUNK) {
+      if (q < last) {
+        const int sn = level_sup[q];
+        const SupDev &S = sup[sn];
+        int lo, own, hi;
+        range(S, sn, lo, own, hi);
+        const int r = 3 * (hi - lo), n3 = 3 * S.ncol, b3 = 3 * S.nb;
+        c = rhs_task_count(k, r, n3, b3, T);
+        ssup[tid] = sn;
+        sr[tid] = (r + T - 1) / T;
+        snt[tid] = ((k == RT_DIAG ? n3 : b3) + T - 1) / T;
+      }
+      v = c;
       for (int o = 1; o < 64; o <<= 1) {
-#pragma unroll
-        for (int k = 0; k < RHS_KINDS; ++k) {
-          const int t = __shfl_up(v[k], o, 64);
-          if (ln >= o) v[k] += t;
-        }
+        const int t = __shfl_up(v, o, 64);
+        if (ln >= o) v += t;
       }
-      if (ln == 63) {
-#pragma unroll
-        for (int k = 0; k < RHS_KINDS; ++k) wsum[k][wv] = v[k];
-      }
+      if (ln == 63) wsum[wv] = v;
     }
     __syncthreads();
-    if (tid < RHS_KINDS) {
+    if (tid == 0) {
       int acc = 0;
       for (int w = 0; w < PLAN_CHUNK / 64; ++w) {
-        const int t = wsum[tid][w];
-        wsum[tid][w] = acc;
+        const int t = wsum[w];
+        wsum[w] = acc;
         acc += t;
       }
-      wtot[tid] = acc;
+      wtot = acc;
     }
     __syncthreads();
-    if (tid < PLAN_CHUNK) {
-#pragma unroll
-      for (int k = 0; k < RHS_KINDS; ++k) pre[k][tid] = wsum[k][wv] + v[k] - c[k];
-    }
+    if (tid < PLAN_CHUNK) pre[tid] = wsum[wv] + v - c;
     __syncthreads();
     // the chunk's tasks, all threads
-    const int nq = min(PLAN_CHUNK, last - base);
-    for (int k = 0; k < RHS_KINDS; ++k) {
-      const int tot = wtot[k];
-      int2 *out = tasks + task_off[RHS_KINDS * l + k] + run[k];
-      for (int t = tid; t < tot; t += PLAN_NT) {
-        int a = 0, b = nq;   // first q with pre > t; the task's supernode is the one before
-        while (a < b) {
-          const int mid = (a + b) >> 1;
-          if (pre[k][mid] <= t)
-            a = mid + 1;
-          else
-            b = mid;
-        }
-        const int qq = a - 1, u = t - pre[k][qq];
-        int ti = u, tj = 0;
-        const int tr = (sr[qq] + tile[k] - 1) / tile[k];
-        if (k == RT_DIAG) {   // deepest row tiles first (their product runs over k < i0 + T)
-          band_index(u, sn3t[qq], tr, ti, tj);
-          ti = sn3t[qq] - 1 - ti;
-        } else if (k == RT_OFF) {
-          band_index(u, sb3t[qq], tr, ti, tj);
-        }
-        out[t] = make_int2(ssup[qq], (ti << 16) | tj);
+    const int nq = min(PLAN_CHUNK, last - base), tot = wtot;
+    int2 *out = tasks + task_off[RHS_KINDS * l + k] + run;
+    for (int t = tid; t < tot; t += PLAN_NT) {
+      int a = 0, b = nq;   // first q with pre > t; the task's supernode is the one before
+      while (a < b) {
+        const int mid = (a + b) >> 1;
+        if (pre[mid] <= t)
+          a = mid + 1;
+        else
+          b = mid;
       }
-      run[k] += tot;
+      const int qq = a - 1, u = t - pre[qq];
+      int ti = u, tj = 0;
+      if (k != RT_ASM) band_index(u, snt[qq], sr[qq], ti, tj);
+      if (k == RT_DIAG) ti = snt[qq] - 1 - ti;   // deepest row tiles first (their product runs over k < i0 + T)
+      out[t] = make_int2(ssup[qq], (ti << 16) | tj);
     }
+    run += tot;
     __syncthreads();
   }
-  if (tid < RHS_KINDS) task_cnt[RHS_KINDS * l + tid] = 2 * run[tid] + (tile[tid] == RHS_TS ? 1 : 0);
+  if (tid == 0) task_cnt[RHS_KINDS * l + k] = 2 * run + (T == RHS_TS ? 1 : 0);
 }
 
 // ---- multi-RHS forward ------------------------------------------------------
@@ -1093,15 +1068,13 @@ void ensure_rhs_capacity(icr_scene *s, int nc) {
       const LevelInfo &L = F.levels[l];
       level_first[l] = L.first;
       level_first[l + 1] = L.first + L.count;
-      const int T[RHS_KINDS] = {RHS_T, RHS_T, RHS_T}, TS[RHS_KINDS] = {RHS_TS, RHS_TS, RHS_TS};
       long long mid[RHS_KINDS] = {}, small[RHS_KINDS] = {};
       for (int q = 0; q < L.count; ++q) {
         const SupDev &d = F.sup[F.sym.level_sup[L.first + q]];
-        int c[RHS_KINDS];
-        rhs_task_counts(d.rmax, 3 * d.ncol, 3 * d.nb, T, c);
-        for (int k = 0; k < RHS_KINDS; ++k) mid[k] += c[k];
-        rhs_task_counts(d.rmax, 3 * d.ncol, 3 * d.nb, TS, c);
-        for (int k = 0; k < RHS_KINDS; ++k) small[k] += c[k];
+        for (int k = 0; k < RHS_KINDS; ++k) {
+          mid[k] += rhs_task_count(k, d.rmax, 3 * d.ncol, 3 * d.nb, RHS_T);
+          small[k] += rhs_task_count(k, d.rmax, 3 * d.ncol, 3 * d.nb, RHS_TS);
+        }
       }
       for (int k = 0; k < RHS_KINDS; ++k) {
         // a list of small tiles has fewer than 4 RHS_SMALL entries
@@ -1175,12 +1148,12 @@ void rhs_prepare(icr_scene *s, int nc, const int *node_ids, bool validate) {
   const long long m = 3LL * nc;
   s->last_build_nc = nc;
   if (validate) ICR_HIP(hipMemsetAsync(F.d_cerr, 0, sizeof(int), st));
-  k_sort_contacts<<<1, 1024, 0, st>>>(nc, s->mesh.N, nsup, node_ids, F.d_sup_of_node, s->mesh.d_fixed, F.d_keys,
-                                      F.d_order, F.d_pos, F.d_cerr);
+  k_sort_contacts<<<cdiv(nc, SORT_C), 1024, 0, st>>>(nc, s->mesh.N, nsup, node_ids, F.d_sup_of_node, s->mesh.d_fixed,
+                                                     F.d_keys, F.d_order, F.d_pos, F.d_cerr);
   ICR_LAUNCH_CHECK();
   const int nlev = (int)F.levels.size();
-  k_rhs_plan<<<nlev, PLAN_NT, 0, st>>>(nc, F.d_level_first, F.d_level_sup, F.d_sup, F.d_keys, F.d_lohi, F.d_rhs_off,
-                                      F.d_rhs_cnt, F.d_rhs_tasks);
+  k_rhs_plan<<<dim3(nlev, RHS_KINDS), PLAN_NT, 0, st>>>(nc, F.d_level_first, F.d_level_sup, F.d_sup, F.d_keys, F.d_lohi,
+                                                        F.d_rhs_off, F.d_rhs_cnt, F.d_rhs_tasks);
   ICR_LAUNCH_CHECK();
 }
 
