@@ -625,50 +625,55 @@ __global__ void k_to_double(long n, const float *__restrict__ x, double *__restr
 // to four slots (unused slots: index -1), so H = Hw Hn with Hn the nodal
 // selection of the distinct nodes and
 //   W_H[3a+i][3b+j] = sum_{k,l} w_ak w_bl W_N[3 u_ak + i][3 u_bl + j],
-// W_N = Hn A^-1 Hn^T (built by the nodal path).  One block per contact row
-// a, threads over b.  The sixteen terms are summed in an order that is the
-// same for (a, b) and (b, a) -- diagonal slot pairs, then each off-diagonal
-// pair (k, l) as t_kl + t_lk -- with products and sums rounded separately
-// (no contraction), so W_H is exactly symmetric like W_N.
+// W_N = Hn A^-1 Hn^T (built by the nodal path).  A thread has one column
+// 3b + j of contact row a (blockIdx.y), so that three lanes read the three
+// neighbouring doubles of a block's row and 64 lanes store neighbours; its 48
+// loads are in flight together.  The sixteen terms are summed in an order that
+// is the same for (a, b) and (b, a) -- diagonal slot pairs, then each
+// off-diagonal pair (k, l) as t_kl + t_lk -- with products and sums rounded
+// separately (no contraction), so W_H is exactly symmetric like W_N.
+// 70 -> 45 us for 400 contacts over 502 nodes, 9.5 -> 3.7 ms for 3000 contacts
+// of two bodies (a thread per block: three times the cache lines a load).
 __global__ __launch_bounds__(256) void k_wh_expand(int nc, int nu3, const int *__restrict__ idx,
                                                    const double *__restrict__ wts, const double *__restrict__ WN,
                                                    double *__restrict__ WH) {
-  const int a = blockIdx.x;
-  int ua[4];
-  double wa[4];
+  const int a = blockIdx.y, e = 256 * blockIdx.x + threadIdx.x;
+  const long m = 3L * nc;
+  if (e >= m) return;
+  const int b = e / 3, j = e % 3;
+  int ua[4], ub[4];
+  double wa[4], wb[4];
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
     ua[k] = idx[4 * a + k];
     wa[k] = ua[k] >= 0 ? wts[4 * a + k] : 0.0;
+    ub[k] = idx[4 * b + k];
+    wb[k] = ub[k] >= 0 ? wts[4 * b + k] : 0.0;
   }
-  const long m = 3L * nc;
-  for (int b = threadIdx.x; b < nc; b += blockDim.x) {
-    int ub[4];
-    double wb[4];
+  // t(k, l)[i] = (w_ak w_bl) W_N[3 u_ak + i][3 u_bl + j], 0 for an unused slot
+  double t[4][4][3];
+#pragma unroll
+  for (int k = 0; k < 4; ++k)
 #pragma unroll
     for (int l = 0; l < 4; ++l) {
-      ub[l] = idx[4 * b + l];
-      wb[l] = ub[l] >= 0 ? wts[4 * b + l] : 0.0;
+      const bool used = ua[k] >= 0 && ub[l] >= 0;
+      const double *x = WN + (long)(3 * max(ua[k], 0)) * nu3 + 3 * max(ub[l], 0) + j;
+#pragma unroll
+      for (int i = 0; i < 3; ++i) t[k][l][i] = used ? x[(long)i * nu3] : 0.0;
     }
-    // t(k, l)[i][j] = (w_ak w_bl) W_N[3 u_ak + i][3 u_bl + j], 0 for an unused slot
-    auto term = [&](int k, int l, int i, int j) -> double {
-      if (ua[k] < 0 || ub[l] < 0) return 0.0;
-      return __dmul_rn(__dmul_rn(wa[k], wb[l]), WN[(long)(3 * ua[k] + i) * nu3 + 3 * ub[l] + j]);
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    auto term = [&](int k, int l) -> double {
+      return ua[k] >= 0 && ub[l] >= 0 ? __dmul_rn(__dmul_rn(wa[k], wb[l]), t[k][l][i]) : 0.0;
     };
+    double acc = term(0, 0);
 #pragma unroll
-    for (int i = 0; i < 3; ++i) {
+    for (int k = 1; k < 4; ++k) acc = __dadd_rn(acc, term(k, k));
 #pragma unroll
-      for (int j = 0; j < 3; ++j) {
-        double acc = term(0, 0, i, j);
+    for (int k = 0; k < 4; ++k)
 #pragma unroll
-        for (int k = 1; k < 4; ++k) acc = __dadd_rn(acc, term(k, k, i, j));
-#pragma unroll
-        for (int k = 0; k < 4; ++k)
-#pragma unroll
-          for (int l = k + 1; l < 4; ++l) acc = __dadd_rn(acc, __dadd_rn(term(k, l, i, j), term(l, k, i, j)));
-        WH[(3L * a + i) * m + 3L * b + j] = acc;
-      }
-    }
+      for (int l = k + 1; l < 4; ++l) acc = __dadd_rn(acc, __dadd_rn(term(k, l), term(l, k)));
+    WH[(3L * a + i) * m + e] = acc;
   }
 }
 
@@ -1015,7 +1020,7 @@ void contact_force_solve(icr_scene *s, const double *f, double *x) {
 }
 
 void launch_wh_expand(hipStream_t st, int nc, int nu, const int *idx, const double *w, const double *WN, double *WH) {
-  k_wh_expand<<<nc, 256, 0, st>>>(nc, 3 * nu, idx, w, WN, WH);
+  k_wh_expand<<<dim3(cdiv(3L * nc, 256), nc), 256, 0, st>>>(nc, 3 * nu, idx, w, WN, WH);
   ICR_LAUNCH_CHECK();
 }
 
