@@ -632,7 +632,7 @@ __global__ void k_to_double(long n, const float *__restrict__ x, double *__restr
 // is the same for (a, b) and (b, a) -- diagonal slot pairs, then each
 // off-diagonal pair (k, l) as t_kl + t_lk -- with products and sums rounded
 // separately (no contraction), so W_H is exactly symmetric like W_N.
-// 70 -> 45 us for 400 contacts over 502 nodes, 9.5 -> 3.7 ms for 3000 contacts
+// 70 -> 45 us for 400 contacts over 502 nodes, 9.5 -> 2.5 ms for 3000 contacts
 // of two bodies (a thread per block: three times the cache lines a load).
 __global__ __launch_bounds__(256) void k_wh_expand(int nc, int nu3, const int *__restrict__ idx,
                                                    const double *__restrict__ wts, const double *__restrict__ WN,
