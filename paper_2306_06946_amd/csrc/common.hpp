@@ -130,13 +130,17 @@ struct AccMT {
 #pragma unroll
         for (int q = 0; q < NE; ++q) off[q] = BUF_OUT;
     }
-    // the chunk of kc <= KC columns at p
+    // the chunk of kc <= KC columns at p (zeros if kc <= 0)
+    __device__ __forceinline__ __amdgpu_buffer_rsrc_t chunk(int kc) const {
+      return buf_make(p, kc <= 0 ? 0L : (long)sizeof(E) * (F ? (long)(kc - 1) * ld + n : (long)(n - 1) * ld + kc));
+    }
+    __device__ __forceinline__ E load(__amdgpu_buffer_rsrc_t b, int kc, int q) const {
+      return buf_load<E>(b, !F && k >= kc ? BUF_OUT : off[q]);   // rows contiguous: past the buffer's end
+    }
     __device__ __forceinline__ void load(E (&r)[NE], int kc) const {
-      const __amdgpu_buffer_rsrc_t b =
-          buf_make(p, (long)sizeof(E) * (F ? (long)(kc - 1) * ld + n : (long)(n - 1) * ld + kc));
-      const bool out = !F && k >= kc;   // rows contiguous: past the buffer's end
+      const __amdgpu_buffer_rsrc_t b = chunk(kc);
 #pragma unroll
-      for (int q = 0; q < NE; ++q) r[q] = buf_load<E>(b, out ? BUF_OUT : off[q]);
+      for (int q = 0; q < NE; ++q) r[q] = load(b, kc, q);
     }
     __device__ __forceinline__ void next() { p += F ? KC * ld : (long)KC; }
     __device__ __forceinline__ void store(const E (&r)[NE], E *lds) const {
@@ -165,35 +169,83 @@ struct AccMT {
       sa.store(ra, lds);
       sb.store(rb, lds + KC * TP);
       __syncthreads();
-      if (kb + KC < k1) {
-        const int kc = min(KC, k1 - kb - KC);
-        sa.next();
-        sb.next();
-        sa.load(ra, kc);
-        sb.load(rb, kc);
-      }
-      products(lds, KC);
+      sa.next();
+      sb.next();
+      products(lds, KC, sa, ra, sb, rb, min(KC, k1 - kb - KC));
       __syncthreads();
     }
   }
-  // c += the staged chunk, its first have columns (in sixteens)
-  __device__ __forceinline__ void products(const E *lds, int have) {
+  // c += the staged chunk, its first have columns (in sixteens), and the loads
+  // of the next chunk of kc columns.  In the 64 x 64 FP64 tile they are spread
+  // over the products: a wave issues in order, and 16 loads in a row keep it
+  // from its first product (W_H of 1000 contacts 2.01 -> 1.96 ms, of 3000 9.67
+  // -> 9.53; the 32 x 32 tile, one product a step, and FP32 were 1 to 4 %
+  // slower with it).
+  template <class SA, class SB>
+  __device__ __forceinline__ void products(const E *lds, int have, const SA &sa, E (&ra)[NE], const SB &sb, E (&rb)[NE],
+                                           int kc) {
     const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
     const int r0 = (T / 2) * (w >> 1), c0 = (T / 2) * (w & 1);
     const int li = l & 15, lk = l >> 4;
+    if constexpr (WB == 1 || sizeof(E) == 4) {
+      if (kc > 0) {
+        sa.load(ra, kc);
+        sb.load(rb, kc);
+      }
 #pragma unroll
-    for (int kk = 0; kk < KC; kk += 4) {
-      if (kk % 16 == 0 && kk >= have) break;
-      const int k = kk + lk;
-      E av[WB], bv[WB];
+      for (int kk = 0; kk < KC; kk += 4) {
+        if (kk % 16 == 0 && kk >= have) break;
+        const int k = kk + lk;
+        E av[WB], bv[WB];
 #pragma unroll
-      for (int a = 0; a < WB; ++a) av[a] = lds[k * TP + r0 + 16 * a + li];
+        for (int a = 0; a < WB; ++a) av[a] = lds[k * TP + r0 + 16 * a + li];
 #pragma unroll
-      for (int b = 0; b < WB; ++b) bv[b] = lds[KC * TP + k * TP + c0 + 16 * b + li];
+        for (int b = 0; b < WB; ++b) bv[b] = lds[KC * TP + k * TP + c0 + 16 * b + li];
 #pragma unroll
-      for (int a = 0; a < WB; ++a)
+        for (int a = 0; a < WB; ++a)
 #pragma unroll
-        for (int b = 0; b < WB; ++b) c[a][b] = Mfma<E>::op(av[a], bv[b], c[a][b]);
+          for (int b = 0; b < WB; ++b) c[a][b] = Mfma<E>::op(av[a], bv[b], c[a][b]);
+      }
+      return;
+    }
+    constexpr int STEPS = KC / 4, PER = 2 * NE / STEPS;   // loads per step
+    static_assert(PER * STEPS == 2 * NE && KC % 16 == 0, "loads spread evenly");
+    const __amdgpu_buffer_rsrc_t ba = sa.chunk(kc), bb = sb.chunk(kc);
+    auto loads = [&](int s) {
+#pragma unroll
+      for (int q = s * PER; q < (s + 1) * PER; ++q) {
+        if (q < NE)
+          ra[q] = sa.load(ba, kc, q);
+        else
+          rb[q - NE] = sb.load(bb, kc, q - NE);
+      }
+    };
+    E av[2][WB], bv[2][WB];
+    auto read = [&](int s, int z) {
+      const int k = 4 * s + lk;
+#pragma unroll
+      for (int a = 0; a < WB; ++a) av[z][a] = lds[k * TP + r0 + 16 * a + li];
+#pragma unroll
+      for (int b = 0; b < WB; ++b) bv[z][b] = lds[KC * TP + k * TP + c0 + 16 * b + li];
+    };
+#pragma unroll
+    for (int g = 0; g < STEPS; g += 4) {
+      if (4 * g < have) {
+        read(g, 0);
+#pragma unroll
+        for (int s = g; s < g + 4; ++s) {
+          if (s + 1 < g + 4) read(s + 1, (s + 1) & 1);
+          loads(s);
+#pragma unroll
+          for (int a = 0; a < WB; ++a)
+#pragma unroll
+            for (int b = 0; b < WB; ++b) c[a][b] = Mfma<E>::op(av[s & 1][a], bv[s & 1][b], c[a][b]);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      } else {
+#pragma unroll
+        for (int s = g; s < g + 4; ++s) loads(s);
+      }
     }
   }
   // c += sum over q < n of A_q^T B_q; get(q, A, an, as, B, bn, bs, rows) names
@@ -223,12 +275,8 @@ struct AccMT {
         sa = Stage<false>(A, left, an, 0, as);
         sb = Stage<false>(B, left, bn, 0, bs);
       }
-      if (q < n) {
-        kc = min(KC, left);
-        sa.load(ra, kc);
-        sb.load(rb, kc);
-      }
-      products(lds, have);
+      kc = q < n ? min(KC, left) : 0;
+      products(lds, have, sa, ra, sb, rb, kc);
       __syncthreads();
     }
   }
