@@ -1123,7 +1123,7 @@ __device__ inline double readlane_f64(double v, int lane) {
 // of a wave's five loads of a column's group is contiguous.  (With the nine
 // doubles of a lane side by side every load touched all 40 cache lines of the
 // group, which cost sets of several waves a third of their time.)
-constexpr int BLK_GROUP = 64 * PGS_BLK;
+constexpr int BLK_GROUP = kPgsGroup;
 __host__ __device__ constexpr inline int blk_entry(int l, int j) {
   return j < 8 ? 128 * (j / 2) + 2 * l + (j & 1) : 512 + l;
 }
@@ -1138,8 +1138,8 @@ struct BlkCol {
 };
 // A buffer of blocked couplings: column groups are read with the column's
 // byte offset in a scalar register and per-lane constants in vector
-// registers, so a load needs no address arithmetic.  Reads past its end
-// return zero.
+// registers, so a load needs no address arithmetic.  The scalar offset is not
+// range checked: it has to be that of a column (PgsColumns).
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 struct BlkBuf {
@@ -1163,8 +1163,7 @@ __device__ __forceinline__ void blk_apply(double (&e)[3], const BlkCol &X, doubl
 }
 // Columns of a group in flight ahead of the one in use.  A stick visit takes
 // 0.17 us, an L2 hit 0.07 us and a miss 0.35 us; two columns were as fast as
-// four on sets that stay in L2, eight no faster.  The loads run past the last
-// column (they return zero), so no visit computes a clamped address.
+// four on sets that stay in L2, eight no faster.
 constexpr int PGS_AHEAD = kPgsAhead;
 
 // The chain's state of one contact, in one lane's registers.
@@ -1291,19 +1290,17 @@ __device__ __forceinline__ void chain_visit(ChainLane &c, const BlkCol &X, int l
 
 // The n contacts of this wave's lanes 0 .. n-1 in order (and, up to a
 // multiple of PGS_AHEAD, lanes beyond them, whose gap and force are zero);
-// off: byte offset of their first column's group of this wave's rows, stride
-// between columns.  prog: the count of solved contacts after this lane's.
+// cols: their columns' groups of this wave's rows.  prog: the count of solved contacts after this lane's.
 template <int J, bool PUB>
-__device__ __forceinline__ void chain_solve(ChainLane &c, int n, const BlkBuf &B, unsigned off, unsigned stride,
-                                            int me, int prog, PgsLds &L, int j_inner, int ln) {
+__device__ __forceinline__ void chain_solve(ChainLane &c, int n, const BlkBuf &B, PgsColumns cols, int me, int prog,
+                                            PgsLds &L, int j_inner, int ln) {
   ChainMasks k{__ballot((c.l[0] != 0.0) | (c.l[1] != 0.0) | (c.l[2] != 0.0)), __ballot(c.rc.it00 > 0.0), 0ull,
                __ballot(c.e[0] >= 0.0)};
   const unsigned at = lds_addr(L.lamS + 3 * me), pat = lds_addr(&L.cprog);
   BlkCol X[PGS_AHEAD];
 #pragma unroll
   for (int u = 0; u < PGS_AHEAD; ++u) {
-    blk_load(X[u], B, off, ln);
-    off += stride;
+    blk_load(X[u], B, cols.take(), ln);
     __builtin_amdgcn_sched_barrier(0);   // in column order: the first use waits for the first column only
   }
   for (int i = 0; i < n; i += PGS_AHEAD) {
@@ -1313,8 +1310,7 @@ __device__ __forceinline__ void chain_solve(ChainLane &c, int n, const BlkBuf &B
       // the mask of the comparison is ready behind the loads
       k.open = __ballot(c.e[0] >= 0.0);
       __builtin_amdgcn_sched_barrier(0);
-      blk_load(X[u], B, off, ln);
-      off += stride;
+      blk_load(X[u], B, cols.take(), ln);
     }
   }
   // visits that ended at once have published nothing: the whole count
@@ -1353,13 +1349,12 @@ __device__ __forceinline__ void ring_wait(PgsLds &L, int prog, int &seen) {
 // The applying part: the changes of contacts b .. b + n - 1 of the LDS arrays,
 // solved by another wave, added to this wave's gaps in contact order.  prog0:
 // the count before the first one.
-__device__ __forceinline__ void ring_apply(ChainLane &c, int n, const BlkBuf &B, unsigned off, unsigned stride, int b,
-                                           int prog0, PgsLds &L, int ln) {
+__device__ __forceinline__ void ring_apply(ChainLane &c, int n, const BlkBuf &B, PgsColumns cols, int b, int prog0,
+                                           PgsLds &L, int ln) {
   BlkCol X[PGS_AHEAD];
 #pragma unroll
   for (int u = 0; u < PGS_AHEAD; ++u) {
-    blk_load(X[u], B, off, ln);
-    off += stride;
+    blk_load(X[u], B, cols.take(), ln);
     __builtin_amdgcn_sched_barrier(0);
   }
   int seen = prog0;
@@ -1370,8 +1365,7 @@ __device__ __forceinline__ void ring_apply(ChainLane &c, int n, const BlkBuf &B,
         ring_wait(L, prog0 + i + u + 1, seen);
         const double *l = L.lamS + 3 * (b + i + u), *l0 = L.lamS0 + 3 * (b + i + u);
         blk_apply(c.e, X[u], l[0] - l0[0], l[1] - l0[1], l[2] - l0[2]);
-        blk_load(X[u], B, off, ln);
-        off += stride;
+        blk_load(X[u], B, cols.take(), ln);
       }
     }
   }
@@ -1387,17 +1381,18 @@ __device__ __forceinline__ void chain_sweep(ChainLane &c, int nS, int nsp, const
   const unsigned stride = 8u * PGS_BLK * (unsigned)nsp, col = 8u * BLK_GROUP * (unsigned)w;
   const int me = o + 64 * w + ln, prog = prog0 + 64 * w + ln + 1;
   if (!PUB) {
-    chain_solve<J, false>(c, nS, B, col, stride, me, prog, L, j_inner, ln);
+    chain_solve<J, false>(c, nS, B, PgsColumns(col, stride, nS), me, prog, L, j_inner, ln);
     return;
   }
   for (int b = 0; b < nS; b += 64) {
     const int n = min(64, nS - b);
+    const PgsColumns cols(col + stride * (unsigned)b, stride, n);
     if (b == 64 * w) {
       __builtin_amdgcn_s_setprio(3);   // the solving wave first on its SIMD
-      chain_solve<J, true>(c, n, B, col + stride * (unsigned)b, stride, me, prog, L, j_inner, ln);
+      chain_solve<J, true>(c, n, B, cols, me, prog, L, j_inner, ln);
       __builtin_amdgcn_s_setprio(0);
     } else {
-      ring_apply(c, n, B, col + stride * (unsigned)b, stride, o + b, prog0 + b, L, ln);
+      ring_apply(c, n, B, cols, o + b, prog0 + b, L, ln);
     }
   }
 }

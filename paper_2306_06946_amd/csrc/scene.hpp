@@ -8,6 +8,7 @@
 #include <vector>
 
 #include "common.hpp"
+#include "pgs_layout.hpp"
 
 namespace icr {
 
@@ -322,27 +323,6 @@ template <class TW>
 void launch_update_W(hipStream_t st, int nc, const TW *WH, const double *C, TW *W);
 constexpr int kPgsMaxContacts = 4096;
 constexpr int kMaxNewton = 256;   // Newton iterations per step (per-iteration sweeps, eps, stamps)
-// Layout of the PGS work buffers: per-contact records of kPgsRecWidth rows,
-// the blocked coupling matrix of an active set of up to kPgsWaveMax contacts
-// in 3x3 blocks of kPgsBlk doubles, padded to pgs_wave_pad contacts.
-constexpr int kPgsRecWidth = 20;
-constexpr int kPgsWaveMax = 512;
-constexpr int kPgsBlk = 9;
-constexpr int kPgsAhead = 4;   // columns of it in flight ahead of a sweep
-__host__ __device__ constexpr inline int pgs_wave_pad(int nS) { return 64 * ((nS + 63) / 64); }
-// doubles of the blocked coupling matrix of an active set (n_c contacts)
-constexpr inline size_t pgs_wss_elems(int nc) {
-  return (size_t)(nc < kPgsWaveMax ? nc : kPgsWaveMax) * pgs_wave_pad(nc < kPgsWaveMax ? nc : kPgsWaveMax) * kPgsBlk;
-}
-// doubles of the prepared records (and gaps) of a first active set
-constexpr inline size_t pgs_rec_elems(int nc) { return (size_t)(nc < kPgsWaveMax ? nc : kPgsWaveMax) * kPgsRecWidth; }
-// Block Gauss-Seidel over the whole GPU (sets beyond kPgsWaveMax contacts):
-// blocks of kPgsCoopB contacts, each block's couplings padded like a wave set.
-constexpr int kPgsCoopB = 128;
-constexpr int kPgsCoopSync = 256;   // ints of sync words
-constexpr inline size_t pgs_coop_blk_elems(int nc) {
-  return (size_t)((nc + kPgsCoopB - 1) / kPgsCoopB) * kPgsCoopB * kPgsCoopB * kPgsBlk;
-}
 void pgs_prepare();   // kernel attributes (dynamic LDS), once per device; call outside graph capture
 // The Newton loops of the scenes tasks[ids.idx[0..n)] (device table), one
 // workgroup each, in one launch on stream st.

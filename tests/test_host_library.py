@@ -124,3 +124,16 @@ def test_analysis_under_address_and_undefined_behaviour_sanitizers(tmp_path):
         assert r.returncode == 0 and r.stdout.startswith("ok "), (r.stdout, r.stderr[-2000:])
         a = icr.analyze(sc["nodes"], sc["tets"])
         assert r.stdout.split()[1:] == [str(len(a["sup"])), str(len(a["rows"]))]
+
+
+def test_column_loads_of_the_contact_chains_stay_in_their_buffer(tmp_path):
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("g++ not available")
+    exe = str(tmp_path / "pgs_columns_check")
+    r = subprocess.run([gxx, "-std=c++17", "-O1", "-I", os.path.join(ROOT, "paper_2306_06946_amd", "csrc"),
+                        os.path.join(ROOT, "tests", "host", "pgs_columns_check.cpp"), "-o", exe],
+                       capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    r = subprocess.run([exe], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout
