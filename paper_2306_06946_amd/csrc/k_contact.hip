@@ -1313,8 +1313,10 @@ __device__ __forceinline__ void chain_solve(ChainLane &c, int n, const BlkBuf &B
       blk_load(X[u], B, cols.take(), ln);
     }
   }
-  // visits that ended at once have published nothing: the whole count
-  if (PUB && ln == n - 1) __hip_atomic_store(&L.cprog, prog, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  // Visits that ended at once have published nothing: the whole count.  The
+  // last visit may have published it, and then the next wave may be past it:
+  // the count never goes back.
+  if (PUB && ln == n - 1) __hip_atomic_fetch_max(&L.cprog, prog, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
   __atomic_signal_fence(__ATOMIC_SEQ_CST);
   // a contact that sticks has a positive normal force
   c.st = ((k.slip >> ln) & 1ull) ? ICR_SLIP : L.lamS[3 * (ln < n ? me : me - ln)] != 0.0 ? ICR_STICK : ICR_SEPARATE;

@@ -84,3 +84,18 @@ def test_long_run_of_separated_contacts():
         lam0 = np.where(np.repeat(rng.uniform(size=nc) < 0.95, 3), 1e-4, 0.0)   # the start set has nearly all contacts
         lam0.reshape(-1, 3)[:, 1:] = 0.0
         _check(W, d, mu, lam0, 4)
+
+
+@pytest.mark.parametrize("nc", [65, 66, 68, 70, 129, 194, 513, 514, 642])
+def test_short_last_block_that_is_passed_over(nc):
+    """The last wave's (or block's) few contacts open in the first sweep and are passed over from then on, so that wave
+    ends its sweep while the one before it may not have ended its own: the count of solved contacts must not go back (a
+    wait for it would run out, and eps be NaN)."""
+    rng = np.random.default_rng(40 + nc)
+    W, d, mu, lam0 = random_contact_problem(nc, rng)
+    last = (nc - 1) // (64 if nc <= 512 else 128) * (64 if nc <= 512 else 128)
+    d[::3] = -np.abs(d[::3])
+    lam0[::3] = 1e-4
+    d[3 * last::3] = 10.0 * np.abs(d).max()
+    st = _check(W, d, mu, lam0, 60 if nc <= 512 else 20)
+    assert np.all(st[last:] == 0) and np.any(st[:last] != 0)
