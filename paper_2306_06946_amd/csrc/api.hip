@@ -168,6 +168,11 @@ void ensure_contact_buffers(icr_scene *s, int nc) {
   if (nc <= C.nc_cap) return;
   s->epoch++;
   ICR_HIP(hipStreamSynchronize(s->stream));
+  // an allocation below may fail: no capacity until all are there, and then no
+  // results of the last step either
+  const bool stepped = s->stepped;
+  C.nc_cap = 0;
+  s->stepped = false;
   C.arena.release(s->settle());
   const long m = 3L * nc;
   C.d_nodes_c = C.arena.alloc<int>(nc);
@@ -207,6 +212,7 @@ void ensure_contact_buffers(icr_scene *s, int nc) {
   C.d_sweeps = C.arena.alloc<int>(kMaxNewton);
   C.d_eps = C.arena.alloc<double>(kMaxNewton);
   C.nc_cap = nc;
+  s->stepped = stepped;
 }
 
 // Buffers and expansion maps of a step with n_contacts = nc when pairs are
@@ -218,6 +224,7 @@ void ensure_pair_step(icr_scene *s, int nc) {
   if (Pr.count == 0 || Pr.step_nc == nc) return;
   ICR_HIP(hipStreamSynchronize(s->stream));
   s->epoch++;
+  Pr.step_nc = 0;   // an allocation below may fail
   Pr.step_arena.release(s->settle());
   const int P = Pr.count, nu = Pr.nu + nc - P;
   std::vector<int> idx(4L * nc, -1);
@@ -714,12 +721,14 @@ icr_status icr_build_WH(icr_scene *s, int32_t n_c, const int32_t *node_ids, cons
       if (ids[e] >= 0) idx[e] = (int)(std::lower_bound(nodes.begin(), nodes.end(), ids[e]) - nodes.begin());
     if (n_c > s->map_nc_cap || nu > s->map_nu_cap) {
       ICR_HIP(hipStreamSynchronize(st));
+      const int nc_cap = std::max(n_c, s->map_nc_cap), nu_cap = std::max(nu, s->map_nu_cap);
+      s->map_nc_cap = s->map_nu_cap = 0;   // an allocation below may fail
       s->map_arena.release(s->settle());
-      s->map_nc_cap = std::max(n_c, s->map_nc_cap);
-      s->map_nu_cap = std::max(nu, s->map_nu_cap);
-      s->d_map_nodes = s->map_arena.alloc<int>(s->map_nu_cap);
-      s->d_map_idx = s->map_arena.alloc<int>(4L * s->map_nc_cap);
-      s->d_map_WN = s->map_arena.alloc<double>(9L * s->map_nu_cap * s->map_nu_cap);
+      s->d_map_nodes = s->map_arena.alloc<int>(nu_cap);
+      s->d_map_idx = s->map_arena.alloc<int>(4L * nc_cap);
+      s->d_map_WN = s->map_arena.alloc<double>(9L * nu_cap * nu_cap);
+      s->map_nc_cap = nc_cap;
+      s->map_nu_cap = nu_cap;
     }
     ICR_HIP(hipMemcpyAsync(s->d_map_nodes, nodes.data(), sizeof(int) * nu, hipMemcpyHostToDevice, st));
     ICR_HIP(hipMemcpyAsync(s->d_map_idx, idx.data(), sizeof(int) * idx.size(), hipMemcpyHostToDevice, st));
@@ -818,8 +827,6 @@ icr_status icr_set_pairs(icr_scene *s, int32_t count, const int32_t *node_ids, c
     Pr.step_arena.release(settled);
     Pr = Pairs();
     if (count == 0) return ICR_OK;
-    Pr.count = count;
-    Pr.nodes = nodes;
     Pr.nu = (int)nodes.size();
     Pr.idx.assign(4L * count, -1);
     Pr.w.assign(4L * count, 0.0);
@@ -847,6 +854,8 @@ icr_status icr_set_pairs(icr_scene *s, int32_t count, const int32_t *node_ids, c
     Pr.d_csr_ptr = A.upload(cnt, st);
     Pr.d_csr_slot = A.upload(csr, st);
     ICR_HIP(hipStreamSynchronize(st));
+    Pr.nodes = nodes;
+    Pr.count = count;   // an allocation above may have failed: then there are no pairs
     return ICR_OK;
   });
 }
@@ -869,15 +878,18 @@ icr_status icr_set_candidates(icr_scene *s, int32_t count, const int32_t *nodes,
       mu_node[v] = mu[i];
     }
     auto &C = s->con;
-    C.count = count;
     // ascending node id: the selection kernel places its contacts in list order
-    C.nodes.assign(nodes, nodes + count);
-    std::sort(C.nodes.begin(), C.nodes.end());
+    std::vector<int> cand(nodes, nodes + count);
+    std::sort(cand.begin(), cand.end());
     auto &B = s->state_arena;
     s->epoch++;
-    C.d_cand = B.upload(C.nodes, s->stream);
-    C.d_mu_node = B.upload(mu_node, s->stream);
+    int *d_cand = B.upload(cand, s->stream);
+    double *d_mu_node = B.upload(mu_node, s->stream);
     ICR_HIP(hipStreamSynchronize(s->stream));
+    C.count = count;   // an allocation above may have failed: then the former list stays
+    C.nodes = std::move(cand);
+    C.d_cand = d_cand;
+    C.d_mu_node = d_mu_node;
     s->has_candidates = true;
     return ICR_OK;
   });

@@ -1044,6 +1044,7 @@ void ensure_rhs_capacity(icr_scene *s, int nc) {
   s->epoch++;
   ICR_HIP(hipStreamSynchronize(s->stream));
   const bool settled = s->settle();
+  F.nc_cap = 0;   // an allocation below may fail
   F.rhs_arena.release(settled);
   long long xo = 0, zo = 0;
   for (int i = 0; i < (int)F.sup.size(); ++i) {
@@ -1240,6 +1241,7 @@ void ensure_mixed(icr_scene *s) {
   }
   if (F.mixed_cap != F.nc_cap) {
     ICR_HIP(hipStreamSynchronize(st));
+    F.mixed_cap = 0;   // an allocation below may fail
     F.mixed_arena.release(s->settle());
     F.d_X32 = F.mixed_arena.alloc<float>(F.x_elems);
     F.d_Z32 = F.mixed_arena.alloc<float>(F.z_elems);

@@ -137,3 +137,31 @@ def test_column_loads_of_the_contact_chains_stay_in_their_buffer(tmp_path):
     assert r.returncode == 0, r.stderr
     r = subprocess.run([exe], capture_output=True, text=True)
     assert r.returncode == 0, r.stdout
+
+
+@pytest.fixture(scope="module")
+def runtime_check(tmp_path_factory):
+    """The host program tests/host/runtime_check.cpp, whose stand-in for the HIP runtime takes the library's calls."""
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("g++ not available")
+    icr.lib()
+    pkg = os.path.dirname(os.path.abspath(icr.__file__))
+    exe = str(tmp_path_factory.mktemp("host") / "runtime_check")
+    r = subprocess.run([gxx, "-std=c++17", "-O1", "-I", os.path.join(ROOT, "include"), "-I", "/opt/rocm/include",
+                        "-Wno-attributes", os.path.join(ROOT, "tests", "host", "runtime_check.cpp"),
+                        os.path.join(pkg, "libicr.so"), "-Wl,-rpath," + pkg, "-pthread", "-o", exe],
+                       capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    return exe
+
+
+def _scenario(exe, name):
+    r = subprocess.run([exe, name], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0 and r.stdout.endswith("ok\n"), (r.stdout[-3000:], r.stderr[-1000:])
+
+
+def test_a_failed_growth_leaves_no_released_buffer_in_use(runtime_check):
+    """Every allocation of a growing call fails in turn: the call says so, and the next, smaller one works on memory of
+    its own; lists of pairs and candidates that could not be stored are not in force."""
+    _scenario(runtime_check, "regrow")
