@@ -65,7 +65,9 @@ enum { ICR_SEPARATE = 0, ICR_STICK = 1, ICR_SLIP = 2 };
  * the null stream) on the current device.  *out is NULL on failure. */
 icr_status icr_create(icr_scene **out, void *stream);
 
-/* Free every library-owned buffer.  Safe on NULL. */
+/* Release every library-owned buffer, after all work of the device (on any
+ * stream).  Safe on NULL.  Up to 4 GiB of the memory stays with the process
+ * for the next scene. */
 void icr_destroy(icr_scene *s);
 /* Frees the device memory that destroyed scenes left for the next ones (any
  * thread; scenes in use are not touched).  An allocation that fails does the

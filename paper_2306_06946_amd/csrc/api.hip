@@ -21,15 +21,24 @@ namespace icr {
 // 96 ms once the cleared memory was used up.  At most kIdleBytes per device
 // stay idle, the oldest go first, a block idle for kIdleSeconds goes with the
 // next allocation or release, and all of a device's go when an allocation
-// fails.  A block is kept only if its scene waited for its own streams and was
-// never moved to another (a wait for the device would end any stream capture
-// of the process); so every stream may use it next.  Others are freed.
+// fails.  A block is kept only after a wait for the whole device, as freeing it
+// would have been: work on it may be pending on any stream (the one that the
+// scene had before icr_set_stream, one on which a caller replays a graph), and
+// every stream may use it next.  hipDeviceSynchronize ends any stream capture of
+// the process, also in the relaxed mode; hipFree in that mode does not, so a
+// small block is allocated and freed for the wait (1.5 us on an idle device).
 namespace {
 constexpr size_t kIdleBytes = size_t(4) << 30;
 constexpr double kIdleSeconds = 10.0;
 struct IdleBlock {
   DeviceBlock b;
   std::chrono::steady_clock::time_point since;
+};
+// Calls that a capture on any stream would forbid, on this thread.
+struct RelaxedCapture {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+  ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
 };
 struct Idle {
   std::mutex mtx;
@@ -56,12 +65,21 @@ Idle &idle() {   // lives as long as the process: the runtime may be gone before
 }
 }  // namespace
 
+bool device_settle() {
+  const RelaxedCapture relaxed;
+  void *p = nullptr;
+  const bool done = hipMalloc(&p, 4096) == hipSuccess && hipFree(p) == hipSuccess;
+  if (!done) (void)hipGetLastError();
+  return done;
+}
+
 DeviceBlock device_alloc(size_t bytes) {
   int dev = 0;
   ICR_HIP(hipGetDevice(&dev));
   const size_t grain = bytes < (size_t(1) << 20) ? 4096 : size_t(65536);
   const size_t size = (bytes + grain - 1) / grain * grain;
   Idle &I = idle();
+  const RelaxedCapture relaxed;
   {
     std::lock_guard<std::mutex> lock(I.mtx);
     I.drop_old();
@@ -92,12 +110,15 @@ DeviceBlock device_alloc(size_t bytes) {
 
 void device_release(const std::vector<DeviceBlock> &blocks, bool settled) {
   Idle &I = idle();
+  const RelaxedCapture relaxed;
   std::lock_guard<std::mutex> lock(I.mtx);
   I.drop_old();
   const auto now = std::chrono::steady_clock::now();
+  int dev = -1;   // the device that was waited for
+  if (hipGetDevice(&dev) != hipSuccess) dev = -1;
   for (const DeviceBlock &b : blocks) {
     bool kept = false;
-    if (settled && b.size <= kIdleBytes) {
+    if (settled && b.dev == dev && b.size <= kIdleBytes) {
       size_t held = 0;
       for (const IdleBlock &i : I.blocks) held += i.b.dev == b.dev ? i.b.size : 0;
       size_t over = held + b.size > kIdleBytes ? held + b.size - kIdleBytes : 0;
@@ -173,7 +194,7 @@ void ensure_contact_buffers(icr_scene *s, int nc) {
   const bool stepped = s->stepped;
   C.nc_cap = 0;
   s->stepped = false;
-  C.arena.release(s->settle());
+  C.arena.release(device_settle());
   const long m = 3L * nc;
   C.d_nodes_c = C.arena.alloc<int>(nc);
   C.d_mu = C.arena.alloc<double>(nc);
@@ -225,7 +246,7 @@ void ensure_pair_step(icr_scene *s, int nc) {
   ICR_HIP(hipStreamSynchronize(s->stream));
   s->epoch++;
   Pr.step_nc = 0;   // an allocation below may fail
-  Pr.step_arena.release(s->settle());
+  Pr.step_arena.release(device_settle());
   const int P = Pr.count, nu = Pr.nu + nc - P;
   std::vector<int> idx(4L * nc, -1);
   std::vector<double> w(4L * nc, 0.0);
@@ -398,7 +419,7 @@ void prepare_factor(icr_scene *s) {
   for (int q = 0; q < ns; ++q) F.tiles_desc[q] = tiles(by_tiles[q]);
   F.max_tiles = F.tiles_desc[0];
 
-  const bool settled = s->settle();
+  const bool settled = device_settle();
   s->fac_arena.release(settled);
   F.rhs_arena.release(settled);
   F.nc_cap = 0;
@@ -464,13 +485,14 @@ icr_status icr_create(icr_scene **out, void *stream) {
 
 void icr_release_idle(void) {
   Idle &I = idle();
+  const RelaxedCapture relaxed;
   std::lock_guard<std::mutex> lock(I.mtx);
   I.drop([](const IdleBlock &) { return true; });
 }
 
 void icr_destroy(icr_scene *s) {
   if (!s) return;
-  const bool settled = s->settle();
+  const bool settled = device_settle();
   s->sg.reset();
   if (s->sg.cap) (void)hipStreamDestroy(s->sg.cap);
   s->con.arena.release(settled);
@@ -490,7 +512,6 @@ const char *icr_last_error(const icr_scene *s) { return s ? s->err.c_str() : "nu
 
 icr_status icr_set_stream(icr_scene *s, void *stream) {
   return guarded(s, [&] {
-    s->moved |= s->stream != (hipStream_t)stream;
     s->stream = (hipStream_t)stream;
     return ICR_OK;
   });
@@ -520,7 +541,7 @@ icr_status icr_assemble(icr_scene *s, const double *nodes, int32_t N, const int3
     ICR_HIP(hipStreamSynchronize(s->stream));
     s->epoch++;
     s->sg.reset();
-    const bool settled = s->settle();
+    const bool settled = device_settle();
     s->assembled = s->factored = s->has_candidates = s->stepped = false;
     s->con.arena.release(settled);
     s->con.nc_cap = 0;
@@ -723,7 +744,7 @@ icr_status icr_build_WH(icr_scene *s, int32_t n_c, const int32_t *node_ids, cons
       ICR_HIP(hipStreamSynchronize(st));
       const int nc_cap = std::max(n_c, s->map_nc_cap), nu_cap = std::max(nu, s->map_nu_cap);
       s->map_nc_cap = s->map_nu_cap = 0;   // an allocation below may fail
-      s->map_arena.release(s->settle());
+      s->map_arena.release(device_settle());
       s->d_map_nodes = s->map_arena.alloc<int>(nu_cap);
       s->d_map_idx = s->map_arena.alloc<int>(4L * nc_cap);
       s->d_map_WN = s->map_arena.alloc<double>(9L * nu_cap * nu_cap);
@@ -822,7 +843,7 @@ icr_status icr_set_pairs(icr_scene *s, int32_t count, const int32_t *node_ids, c
     ICR_HIP(hipStreamSynchronize(s->stream));
     s->epoch++;
     auto &Pr = s->pairs;
-    const bool settled = s->settle();
+    const bool settled = device_settle();
     Pr.arena.release(settled);
     Pr.step_arena.release(settled);
     Pr = Pairs();

@@ -1043,7 +1043,7 @@ void ensure_rhs_capacity(icr_scene *s, int nc) {
   if (nc <= F.nc_cap) return;
   s->epoch++;
   ICR_HIP(hipStreamSynchronize(s->stream));
-  const bool settled = s->settle();
+  const bool settled = device_settle();
   F.nc_cap = 0;   // an allocation below may fail
   F.rhs_arena.release(settled);
   long long xo = 0, zo = 0;
@@ -1230,7 +1230,7 @@ void ensure_mixed(icr_scene *s) {
   auto &F = s->fac;
   hipStream_t st = s->stream;
   if (!F.have32) {
-    F.fac32_arena.release(s->settle());
+    F.fac32_arena.release(device_settle());
     F.d_front32 = F.fac32_arena.alloc<float>(F.front_elems);
     F.d_linv32 = F.fac32_arena.alloc<float>(F.linv_elems);
     k_to_float<<<2048, 256, 0, st>>>(F.front_elems, F.d_front, F.d_front32);
@@ -1242,7 +1242,7 @@ void ensure_mixed(icr_scene *s) {
   if (F.mixed_cap != F.nc_cap) {
     ICR_HIP(hipStreamSynchronize(st));
     F.mixed_cap = 0;   // an allocation below may fail
-    F.mixed_arena.release(s->settle());
+    F.mixed_arena.release(device_settle());
     F.d_X32 = F.mixed_arena.alloc<float>(F.x_elems);
     F.d_Z32 = F.mixed_arena.alloc<float>(F.z_elems);
     F.d_R = F.mixed_arena.alloc<double>(F.z_elems);

@@ -19,8 +19,10 @@ struct DeviceBlock {
   int dev;
 };
 DeviceBlock device_alloc(size_t bytes);   // throws HipError
-// settled: no work that touches the blocks is pending, so they may be handed
-// out again at once; else they go back to the driver.  Never throws.
+// Waits for all work of the current device, as hipFree does; true if it could.
+bool device_settle();
+// settled: device_settle() has waited, so the blocks may be handed out again at
+// once; else they go back to the driver.  Never throws.
 void device_release(const std::vector<DeviceBlock> &blocks, bool settled);
 
 // Device allocations owned by a scene; freed together.
@@ -269,14 +271,6 @@ struct icr_scene {
   long epoch = 0;          // bumped whenever device buffers are (re)allocated
   int clock_khz = 0;       // device wall-clock rate used by the phase stamps
   StepGraph sg;
-  bool moved = false;   // icr_set_stream changed the stream: work may be pending on the one before
-  // Waits for the scene's stream; true if nothing that touches its buffers is
-  // pending.
-  bool settle() const {
-    const bool done = hipStreamSynchronize(stream) == hipSuccess;
-    if (!done) (void)hipGetLastError();
-    return done && !moved;
-  }
 };
 
 namespace icr {

@@ -20,7 +20,7 @@ inline size_t bytes = 0;          // live device bytes
 inline long mallocs = 0, launches = 0;
 inline long fail_in = -1;         // the allocation that fails, counted down; < 0: none
 inline long stale = 0;            // copies and clears outside live memory
-inline long device_waits = 0;     // waits for the whole device
+inline long frees = 0;            // of device memory: each waits for the whole device
 inline bool is_live(const void *p, size_t n) {
   auto it = live.upper_bound((char *)p);
   if (it == live.begin()) return false;
@@ -55,6 +55,7 @@ hipError_t hipFree(void *p) {
   std::lock_guard<std::mutex> l(fake::mtx);
   auto it = fake::live.find((char *)p);
   if (it == fake::live.end()) return hipErrorInvalidValue;
+  ++fake::frees;
   fake::bytes -= it->second;
   fake::live.erase(it);
   std::free(p);
@@ -74,7 +75,7 @@ hipError_t hipMemsetAsync(void *d, int v, size_t n, hipStream_t) {
   if (!fake::stale) std::memset(d, v, n);
   return hipSuccess;
 }
-hipError_t hipDeviceSynchronize() { return ++fake::device_waits, hipSuccess; }
+hipError_t hipDeviceSynchronize() { return hipSuccess; }
 hipError_t hipThreadExchangeStreamCaptureMode(hipStreamCaptureMode *) { return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
 hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned) { return *s = (hipStream_t)0x10, hipSuccess; }

@@ -189,10 +189,36 @@ static void scenario_regrow() {
   icr_destroy(s);
 }
 
+// Memory that is kept for the next scene: closing one, or growing its buffers,
+// waits for the device first, as freeing the memory would.
+static void scenario_close() {
+  const Grid grid(8);
+  for (bool moved : {false, true}) {
+    icr_scene *s = grid.scene();
+    if (moved) CHECK(icr_set_stream(s, (void *)0x30) == ICR_OK, "stream");
+    const size_t held = fake::bytes;
+    long frees = fake::frees;
+    CHECK(icr_reserve(s, 20, ICR_FP64) == ICR_OK && icr_reserve(s, 40, ICR_FP64) == ICR_OK, "%s", icr_last_error(s));
+    CHECK(fake::frees > frees, "no wait before the buffers of 20 contacts were handed on");
+    frees = fake::frees;
+    icr_destroy(s);
+    CHECK(fake::frees > frees, "no wait before the scene's memory was handed on");
+    CHECK(fake::bytes >= held, "nothing kept of %zu bytes", held);
+    const size_t kept = fake::bytes;
+    s = grid.scene();
+    CHECK(fake::bytes == kept, "%zu bytes, then %zu with a scene of the same size", kept, fake::bytes);
+    icr_destroy(s);
+    icr_release_idle();
+    CHECK(fake::bytes == 0, "%zu bytes left", fake::bytes);
+  }
+}
+
 int main(int argc, char **argv) {
   const std::string what = argc > 1 ? argv[1] : "";
   if (what == "regrow")
     scenario_regrow();
+  else if (what == "close")
+    scenario_close();
   else
     return 2;
   CHECK(fake::stale == 0, "%ld", fake::stale);

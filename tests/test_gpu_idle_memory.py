@@ -85,3 +85,66 @@ def test_bounded_and_given_back():
     assert 0 < kept <= (4 << 30) + (256 << 20)
     icr.release_idle()
     assert base - _free() <= 256 << 20
+
+
+def test_close_waits_for_every_stream():
+    """A closed scene's memory goes to the next scene, so closing waits for work that may use it: on the scene's stream,
+    on the one it had before, and on one the library never saw."""
+    from paper_2306_06946_amd import icr
+    sc = make_scene("tiny")
+    streams = [torch.cuda.Stream() for _ in range(3)]
+    for busy in range(3):
+        s = icr.Scene(streams[0].cuda_stream)
+        s.assemble(sc)
+        s.factor()
+        s.set_stream(streams[1].cuda_stream)
+        torch.cuda.synchronize()
+        done = torch.cuda.Event()
+        with torch.cuda.stream(streams[busy]):
+            torch.cuda._sleep(100_000_000)
+            done.record()
+        s.close()
+        assert done.query(), busy
+
+
+@pytest.mark.parametrize("mode", ["global", "thread_local"])
+def test_close_and_reuse_beside_a_capture(mode):
+    """Another thread closes scenes, takes their memory and gives it back while a graph is captured."""
+    from paper_2306_06946_amd import icr
+    sc = make_scene("tiny")
+    x, y = torch.ones(1000, device="cuda"), torch.zeros(1000, device="cuda")
+    y.add_(x)
+    y.zero_()
+
+    def scene():
+        s = icr.Scene(torch.cuda.Stream().cuda_stream)
+        s.assemble(sc)
+        s.factor()
+        return s
+
+    live = [scene() for _ in range(3)]
+    torch.cuda.synchronize()
+    graph, stream, errs = torch.cuda.CUDAGraph(), torch.cuda.Stream(), []
+
+    def work():
+        try:
+            for s in live:
+                s.close()
+            icr.release_idle()
+        except Exception as e:   # noqa: BLE001 - reported by the assert below
+            errs.append(e)
+
+    with torch.cuda.stream(stream):
+        graph.capture_begin(capture_error_mode=mode)
+        y.add_(x)
+        t = threading.Thread(target=work)
+        t.start()
+        t.join()
+        y.add_(x)
+        graph.capture_end()
+    torch.cuda.synchronize()
+    assert not errs
+    for k in range(1, 4):
+        graph.replay()
+        torch.cuda.synchronize()
+        assert float(y[0]) == 2.0 * k

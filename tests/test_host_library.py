@@ -165,3 +165,7 @@ def test_a_failed_growth_leaves_no_released_buffer_in_use(runtime_check):
     """Every allocation of a growing call fails in turn: the call says so, and the next, smaller one works on memory of
     its own; lists of pairs and candidates that could not be stored are not in force."""
     _scenario(runtime_check, "regrow")
+
+
+def test_closing_waits_before_memory_is_handed_on(runtime_check):
+    _scenario(runtime_check, "close")
