@@ -17,8 +17,9 @@
  *   - "host" pointers are read during the call and copied; "device" pointers
  *     are caller-owned GPU buffers (e.g. torch tensors) that the library never
  *     frees.  Library-owned device memory (mesh, factor, work arenas, state)
- *     lives until icr_destroy; up to 4 GiB of it then stays with the process
- *     for the next scene (icr_release_idle gives it back).
+ *     lives until icr_destroy; up to 4 GiB per device of it then stays with
+ *     the process for the next scene, for 10 s at most (icr_release_idle gives
+ *     it back at once).
  *   - Device work is enqueued on the scene's stream (icr_create).  Calls that
  *     return host values (sweeps, eps, reports) synchronise that stream.
  *   - Arrays are row-major, float64 unless stated; node ids are int32,
@@ -67,11 +68,13 @@ icr_status icr_create(icr_scene **out, void *stream);
 
 /* Release every library-owned buffer, after all work of the device (on any
  * stream).  Safe on NULL.  Up to 4 GiB of the memory stays with the process
- * for the next scene. */
+ * for the next scene; what no scene takes within 10 s is freed then. */
 void icr_destroy(icr_scene *s);
 /* Frees the device memory that destroyed scenes left for the next ones (any
- * thread; scenes in use are not touched).  An allocation that fails does the
- * same for its device by itself. */
+ * thread; scenes in use are not touched).  An allocation of the library that
+ * fails does the same for its device by itself; another allocator of the
+ * process that needs the memory within those 10 s calls this first.  The memory
+ * is in no scene's device_bytes and not part of a server's budget. */
 void icr_release_idle(void);
 
 /* Last error message of this scene ("" if none); valid until the next call. */

@@ -1,12 +1,18 @@
 // C ABI entry points (include/icr.h): argument checks, host planning, and the
 // launch sequence of each call on the scene's stream.
+#include <pthread.h>
+#include <signal.h>
+
 #include <algorithm>
 #include <chrono>
 #include <cmath>
+#include <condition_variable>
+#include <cstdlib>
 #include <cstring>
 #include <exception>
 #include <mutex>
 #include <numeric>
+#include <thread>
 
 #include "scene.hpp"
 #include "server_hooks.hpp"
@@ -19,20 +25,22 @@ namespace icr {
 // same few gigabytes each time, and the driver clears what is freed before it
 // hands it out again: set-ups of 28 ms each at 61 236 DOF (3.5 GB) fell to
 // 96 ms once the cleared memory was used up.  At most kIdleBytes per device
-// stay idle, the oldest go first, a block idle for kIdleSeconds goes with the
-// next allocation or release, and all of a device's go when an allocation
-// fails.  A block is kept only after a wait for the whole device, as freeing it
-// would have been: work on it may be pending on any stream (the one that the
-// scene had before icr_set_stream, one on which a caller replays a graph), and
-// every stream may use it next.  hipDeviceSynchronize ends any stream capture of
-// the process, also in the relaxed mode; hipFree in that mode does not, so a
-// small block is allocated and freed for the wait (1.5 us on an idle device).
+// stay idle, the oldest go first, a block idle for kIdleTime is freed by a
+// thread that lives while there are idle blocks, and all of a device's go when
+// an allocation fails.  A block is kept only after a wait for the whole device,
+// as freeing it would have been: work on it may be pending on any stream (the
+// one that the scene had before icr_set_stream, one on which a caller replays a
+// graph), and every stream may use it next.  hipDeviceSynchronize ends any
+// stream capture of the process, also in the relaxed mode; hipFree in that mode
+// does not, so a small block is allocated and freed for the wait (1.5 us on an
+// idle device).
 namespace {
 constexpr size_t kIdleBytes = size_t(4) << 30;
-constexpr double kIdleSeconds = 10.0;
+constexpr auto kIdleTime = std::chrono::seconds(10);
+typedef std::chrono::steady_clock Clock;
 struct IdleBlock {
   DeviceBlock b;
-  std::chrono::steady_clock::time_point since;
+  Clock::time_point since;
 };
 // Calls that a capture on any stream would forbid, on this thread.
 struct RelaxedCapture {
@@ -40,28 +48,88 @@ struct RelaxedCapture {
   RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
   ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
 };
+void free_blocks(const std::vector<DeviceBlock> &blocks) {
+  if (blocks.empty()) return;
+  const RelaxedCapture relaxed;
+  for (const DeviceBlock &b : blocks) (void)hipFree(b.p);
+}
+// Blocks are freed without the lock: a free waits for the device.
 struct Idle {
   std::mutex mtx;
+  std::condition_variable changed;
   std::vector<IdleBlock> blocks;   // oldest first
+  bool watched = false;            // the thread runs
+  bool freeing = false;            // it is inside hipFree
+  bool closing = false;            // the process ends: no more calls of the runtime
   template <class F>
-  void drop(F &&which) {   // frees the blocks for which which(block) holds
+  std::vector<DeviceBlock> take(F &&which) {   // the blocks for which which(block) holds
+    std::vector<DeviceBlock> out;
+    out.reserve(blocks.size());
     size_t k = 0;
-    for (size_t i = 0; i < blocks.size(); ++i) {
-      if (which(blocks[i]))
-        (void)hipFree(blocks[i].b.p);
+    for (const IdleBlock &i : blocks) {
+      if (which(i))
+        out.push_back(i.b);
       else
-        blocks[k++] = blocks[i];
+        blocks[k++] = i;
     }
     blocks.resize(k, IdleBlock{});
+    return out;
   }
-  void drop_old() {
-    const auto now = std::chrono::steady_clock::now();
-    drop([&](const IdleBlock &i) { return std::chrono::duration<double>(now - i.since).count() > kIdleSeconds; });
+  void watch() {
+    std::unique_lock<std::mutex> lock(mtx);
+    while (!closing && !blocks.empty()) {
+      const auto due = blocks.front().since + kIdleTime;
+      if (Clock::now() < due) {
+        changed.wait_until(lock, due);
+        continue;
+      }
+      std::vector<DeviceBlock> old;
+      try {
+        old = take([now = Clock::now()](const IdleBlock &i) { return now - i.since >= kIdleTime; });
+      } catch (...) {   // no host memory for the list: one at a time
+        (void)hipFree(blocks.front().b.p);
+        blocks.erase(blocks.begin());
+        continue;
+      }
+      freeing = true;
+      lock.unlock();
+      free_blocks(old);
+      lock.lock();
+      freeing = false;
+      changed.notify_all();
+    }
+    watched = false;
   }
+  // Starts the thread if there is none (it takes no signals of the program);
+  // false if it cannot be.  With the lock.
+  bool start_watch();
 };
 Idle &idle() {   // lives as long as the process: the runtime may be gone before static destructors
   static Idle *i = new Idle;
   return *i;
+}
+bool Idle::start_watch() {
+  if (watched) return true;
+  if (closing) return false;
+  // runs before the runtime's own clean-up, which was registered earlier
+  static const bool registered = std::atexit([] {
+                                   Idle &I = idle();
+                                   std::unique_lock<std::mutex> lock(I.mtx);
+                                   I.closing = true;
+                                   I.changed.notify_all();
+                                   I.changed.wait(lock, [&] { return !I.freeing; });
+                                 }) == 0;
+  if (!registered) return false;
+  sigset_t all, old;
+  sigfillset(&all);
+  if (pthread_sigmask(SIG_SETMASK, &all, &old) != 0) return false;
+  try {
+    std::thread([this] { watch(); }).detach();
+    watched = true;
+  } catch (...) {
+  }
+  (void)pthread_sigmask(SIG_SETMASK, &old, nullptr);
+  return watched;
 }
 }  // namespace
 
@@ -82,7 +150,6 @@ DeviceBlock device_alloc(size_t bytes) {
   const RelaxedCapture relaxed;
   {
     std::lock_guard<std::mutex> lock(I.mtx);
-    I.drop_old();
     size_t best = I.blocks.size();   // the smallest that fits, an eighth too large at most
     for (size_t i = 0; i < I.blocks.size(); ++i) {
       const DeviceBlock &b = I.blocks[i].b;
@@ -100,8 +167,12 @@ DeviceBlock device_alloc(size_t bytes) {
   hipError_t e = hipMalloc(&p, size);
   if (e != hipSuccess) {
     (void)hipGetLastError();
-    std::lock_guard<std::mutex> lock(I.mtx);
-    I.drop([&](const IdleBlock &i) { return i.b.dev == dev; });
+    std::vector<DeviceBlock> all;
+    {
+      std::lock_guard<std::mutex> lock(I.mtx);
+      all = I.take([&](const IdleBlock &i) { return i.b.dev == dev; });
+    }
+    free_blocks(all);
     e = hipMalloc(&p, size);
   }
   if (e != hipSuccess) throw HipError(e, "hipMalloc(" + std::to_string(size) + " bytes)");
@@ -110,32 +181,43 @@ DeviceBlock device_alloc(size_t bytes) {
 
 void device_release(const std::vector<DeviceBlock> &blocks, bool settled) {
   Idle &I = idle();
-  const RelaxedCapture relaxed;
-  std::lock_guard<std::mutex> lock(I.mtx);
-  I.drop_old();
-  const auto now = std::chrono::steady_clock::now();
   int dev = -1;   // the device that was waited for
   if (hipGetDevice(&dev) != hipSuccess) dev = -1;
-  for (const DeviceBlock &b : blocks) {
-    bool kept = false;
-    if (settled && b.dev == dev && b.size <= kIdleBytes) {
+  size_t done = 0;   // blocks kept or freed
+  if (settled) {
+    std::vector<DeviceBlock> out;   // to be freed
+    try {
+      std::lock_guard<std::mutex> lock(I.mtx);
+      out.reserve(I.blocks.size() + blocks.size());
+      I.blocks.reserve(I.blocks.size() + blocks.size());   // nothing below throws
+      const bool watched = I.start_watch();
+      const auto now = Clock::now();
       size_t held = 0;
-      for (const IdleBlock &i : I.blocks) held += i.b.dev == b.dev ? i.b.size : 0;
-      size_t over = held + b.size > kIdleBytes ? held + b.size - kIdleBytes : 0;
-      if (over)
-        I.drop([&](const IdleBlock &i) {
-          if (over == 0 || i.b.dev != b.dev) return false;
-          over -= std::min(over, i.b.size);
-          return true;
-        });
-      try {
+      for (const IdleBlock &i : I.blocks) held += i.b.dev == dev ? i.b.size : 0;
+      for (const DeviceBlock &b : blocks) {
+        ++done;
+        if (!watched || b.dev != dev || b.size > kIdleBytes) {
+          out.push_back(b);
+          continue;
+        }
+        held += b.size;
+        for (size_t i = 0; held > kIdleBytes;) {   // the device's oldest go
+          if (I.blocks[i].b.dev != dev) {
+            ++i;
+            continue;
+          }
+          held -= I.blocks[i].b.size;
+          out.push_back(I.blocks[i].b);
+          I.blocks.erase(I.blocks.begin() + i);
+        }
         I.blocks.push_back(IdleBlock{b, now});
-        kept = true;
-      } catch (...) {
       }
+    } catch (...) {   // no host memory: nothing was kept
     }
-    if (!kept) (void)hipFree(b.p);
+    free_blocks(out);
   }
+  const RelaxedCapture relaxed;
+  for (; done < blocks.size(); ++done) (void)hipFree(blocks[done].p);
 }
 
 }  // namespace icr
@@ -484,10 +566,16 @@ icr_status icr_create(icr_scene **out, void *stream) {
 }
 
 void icr_release_idle(void) {
-  Idle &I = idle();
-  const RelaxedCapture relaxed;
-  std::lock_guard<std::mutex> lock(I.mtx);
-  I.drop([](const IdleBlock &) { return true; });
+  try {
+    std::vector<DeviceBlock> all;
+    {
+      Idle &I = idle();
+      std::lock_guard<std::mutex> lock(I.mtx);
+      all = I.take([](const IdleBlock &) { return true; });
+    }
+    free_blocks(all);
+  } catch (...) {   // no host memory for the list: the blocks go when their time is up
+  }
 }
 
 void icr_destroy(icr_scene *s) {

@@ -254,7 +254,14 @@ icr_status icr_server_create(icr_server **out, int64_t hbm_budget, int32_t slots
   srv->budget = hbm_budget;
   srv->slots.resize(slots);
   srv->task_bytes = icr::newton_task_bytes();   // the table's entry stride, as the kernel indexes it
-  if (hipMalloc(&srv->d_tasks, srv->task_bytes * kGroupMax * slots) != hipSuccess) {
+  const size_t table = srv->task_bytes * kGroupMax * slots;
+  bool room = hipMalloc(&srv->d_tasks, table) == hipSuccess;
+  if (!room) {
+    (void)hipGetLastError();
+    icr_release_idle();
+    room = hipMalloc(&srv->d_tasks, table) == hipSuccess;
+  }
+  if (!room) {
     srv->d_tasks = nullptr;
     icr_server_destroy(srv);
     return ICR_E_HIP;

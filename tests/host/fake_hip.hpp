@@ -21,6 +21,8 @@ inline long mallocs = 0, launches = 0;
 inline long fail_in = -1;         // the allocation that fails, counted down; < 0: none
 inline long stale = 0;            // copies and clears outside live memory
 inline long frees = 0;            // of device memory: each waits for the whole device
+inline bool ended = false;        // the runtime is gone
+inline long late = 0;             // calls after that
 inline bool is_live(const void *p, size_t n) {
   auto it = live.upper_bound((char *)p);
   if (it == live.begin()) return false;
@@ -53,6 +55,7 @@ hipError_t hipMalloc(void **p, size_t n) {
 }
 hipError_t hipFree(void *p) {
   std::lock_guard<std::mutex> l(fake::mtx);
+  if (fake::ended) ++fake::late;
   auto it = fake::live.find((char *)p);
   if (it == fake::live.end()) return hipErrorInvalidValue;
   ++fake::frees;

@@ -1,7 +1,9 @@
 // The library's host side against a stand-in for the HIP runtime (no GPU),
 // built and run by tests/test_host_library.py: runtime_check <scenario>.
+#include <chrono>
 #include <functional>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "fake_hip.hpp"
@@ -213,12 +215,53 @@ static void scenario_close() {
   }
 }
 
+// Memory that no scene takes is freed ten seconds later, without a call of the
+// library, also when others are closed and opened meanwhile.
+static void scenario_idle_time() {
+  using namespace std::chrono;
+  const Grid small(5), large(8);
+  auto held = [] {
+    std::lock_guard<std::mutex> l(fake::mtx);
+    return fake::bytes;
+  };
+  icr_scene *s = large.scene();
+  const auto t0 = steady_clock::now();
+  icr_destroy(s);
+  const size_t big = held();
+  CHECK(big > 0, "nothing kept");
+  std::this_thread::sleep_until(t0 + seconds(5));
+  icr_scene *live = small.scene();
+  s = small.scene();
+  icr_destroy(s);
+  CHECK(held() >= big, "freed before its time");
+  std::this_thread::sleep_until(t0 + milliseconds(12000));
+  CHECK(held() < big, "%zu of %zu bytes still there", held(), big);
+  std::this_thread::sleep_until(t0 + milliseconds(16500));
+  icr_factor_info info{};
+  CHECK(icr_get_factor_info(live, &info) == ICR_OK, "info");
+  CHECK(held() < (size_t)info.device_bytes + (2u << 20), "%zu bytes beside a scene of %lld", held(),
+        (long long)info.device_bytes);
+  icr_destroy(live);
+  icr_release_idle();
+  CHECK(held() == 0, "%zu bytes left", held());
+  // the process ends with idle memory: no call of the runtime after its end
+  // (its clean-up was registered before the library's first release: see main)
+  icr_destroy(large.scene());
+}
+
 int main(int argc, char **argv) {
   const std::string what = argc > 1 ? argv[1] : "";
+  std::atexit([] {   // as the runtime's clean-up
+    fake::ended = true;
+    std::this_thread::sleep_for(std::chrono::milliseconds(200));
+    if (fake::late) std::_Exit(3);
+  });
   if (what == "regrow")
     scenario_regrow();
   else if (what == "close")
     scenario_close();
+  else if (what == "idle_time")
+    scenario_idle_time();
   else
     return 2;
   CHECK(fake::stale == 0, "%ld", fake::stale);

@@ -1,6 +1,7 @@
 """Device memory of closed scenes, kept for the next ones: scenes made in turn and from two threads at once compute what
 the first scene of a process computes, and the memory is bounded and given back."""
 import threading
+import time
 
 import numpy as np
 import pytest
@@ -144,6 +145,38 @@ def test_close_and_reuse_beside_a_capture(mode):
         graph.capture_end()
     torch.cuda.synchronize()
     assert not errs
+    for k in range(1, 4):
+        graph.replay()
+        torch.cuda.synchronize()
+        assert float(y[0]) == 2.0 * k
+
+
+def test_idle_memory_goes_when_its_time_is_up_also_beside_a_capture():
+    from paper_2306_06946_amd import icr
+    sc = make_scene("tiny")
+    x, y = torch.ones(1000, device="cuda"), torch.zeros(1000, device="cuda")
+    y.add_(x)
+    y.zero_()
+    icr.release_idle()
+    base = _free()
+    s = icr.Scene()
+    s.assemble(sc)
+    s.factor()
+    s.reserve(1200)
+    closed = time.monotonic()
+    s.close()
+    kept = base - _free()
+    assert kept > 256 << 20
+    graph, stream = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    time.sleep(max(0.0, closed + 9.5 - time.monotonic()))
+    with torch.cuda.stream(stream):
+        graph.capture_begin()   # in the mode that forbids most calls of every thread
+        y.add_(x)
+        time.sleep(max(0.0, closed + 11.5 - time.monotonic()))
+        y.add_(x)
+        graph.capture_end()
+    torch.cuda.synchronize()
+    assert base - _free() < kept // 4
     for k in range(1, 4):
         graph.replay()
         torch.cuda.synchronize()

@@ -169,3 +169,9 @@ def test_a_failed_growth_leaves_no_released_buffer_in_use(runtime_check):
 
 def test_closing_waits_before_memory_is_handed_on(runtime_check):
     _scenario(runtime_check, "close")
+
+
+def test_idle_memory_is_freed_when_its_time_is_up(runtime_check):
+    """Without another call of the library, by a thread that ends with the last idle block and never frees while the
+    process ends."""
+    _scenario(runtime_check, "idle_time")
