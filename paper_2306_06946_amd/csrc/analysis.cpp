@@ -66,7 +66,8 @@ struct ND {
   const double *xyz;
   const MeshGraph *g;
   int leaf_max;
-  double reach[3] = {0.0, 0.0, 0.0};   // longest edge along each axis
+  // longest edge along each axis; infinite if a coordinate is not finite
+  double reach[3] = {0.0, 0.0, 0.0};
   std::vector<int> stamp;   // region marker
   int cur = 0;
   Symbolic *sym;
@@ -85,9 +86,26 @@ struct ND {
     return s;
   }
 
-  // The region's nodes sorted along each axis (coordinate, then id): the lists
-  // of the root are sorted once and split stably on the way down.
+  // The region's nodes sorted along each axis (coordinate, then id; a NaN as
+  // +infinity): the lists of the root are sorted once and split stably on the
+  // way down.
   typedef std::array<std::vector<int>, 3> Sorted;
+
+  // Extent of a sorted list along its axis, without the NaNs.
+  double extent(const std::vector<int> &v, int a) const {
+    double lo = 1e300, hi = -1e300;
+    auto add = [&](int node) {
+      lo = std::min(lo, xyz[3 * node + a]);
+      hi = std::max(hi, xyz[3 * node + a]);
+    };
+    if (std::isinf(reach[a])) {
+      for (int node : v) add(node);
+    } else {
+      add(v.front());
+      add(v.back());
+    }
+    return hi - lo;
+  }
 
   int rec(Sorted by) {
     const int n = (int)by[0].size();
@@ -96,10 +114,10 @@ struct ND {
       return make_sup(by[0], {});
     }
     int ax = 0;
-    double ext = -1.0;
-    for (int a = 0; a < 3; ++a) {
-      const double e = xyz[3 * by[a].back() + a] - xyz[3 * by[a].front() + a];
-      if (a == 0 || e > ext) {
+    double ext = extent(by[0], 0);
+    for (int a = 1; a < 3; ++a) {
+      const double e = extent(by[a], a);
+      if (e > ext) {
         ax = a;
         ext = e;
       }
@@ -120,7 +138,8 @@ struct ND {
     const int left = ++cur, right = ++cur;
     for (int k = 0; k < n; ++k) stamp[nodes[k]] = k < best ? left : right;
     // (no edge is longer along the axis than reach, so only nodes that close to
-    // the other side can have a neighbour there)
+    // the other side can have a neighbour there; with an infinite reach all are
+    // looked at, also those whose distance is a NaN)
     auto at_cut = [&](int v, int other, std::vector<int> &sep) {
       for (int e = g->ptr[v]; e < g->ptr[v + 1]; ++e)
         if (stamp[g->adj[e]] == other) {
@@ -130,8 +149,8 @@ struct ND {
     };
     std::vector<int> sepL, sepR;
     const double xl = xyz[3 * nodes[best - 1] + ax], xr = xyz[3 * nodes[best] + ax];
-    for (int k = best - 1; k >= 0 && xr - xyz[3 * nodes[k] + ax] <= reach[ax]; --k) at_cut(nodes[k], right, sepL);
-    for (int k = best; k < n && xyz[3 * nodes[k] + ax] - xl <= reach[ax]; ++k) at_cut(nodes[k], left, sepR);
+    for (int k = best - 1; k >= 0 && !(xr - xyz[3 * nodes[k] + ax] > reach[ax]); --k) at_cut(nodes[k], right, sepL);
+    for (int k = best; k < n && !(xyz[3 * nodes[k] + ax] - xl > reach[ax]); ++k) at_cut(nodes[k], left, sepR);
     std::vector<int> S = sepL.size() <= sepR.size() ? std::move(sepL) : std::move(sepR);
     const int sepmark = ++cur;
     if (S.empty()) {   // disconnected halves: any single node separates them
@@ -172,8 +191,10 @@ void analyze(const double *xyz, const MeshGraph &g, int leaf_max, Symbolic &sym)
   nd.stamp.assign(N, 0);
   for (int v = 0; v < N; ++v)
     for (int e = g.ptr[v]; e < g.ptr[v + 1]; ++e)
-      for (int a = 0; a < 3; ++a)
-        nd.reach[a] = std::max(nd.reach[a], std::fabs(xyz[3 * v + a] - xyz[3 * g.adj[e] + a]));
+      for (int a = 0; a < 3; ++a) {   // (a node is its own neighbour: inf - inf)
+        const double d = std::fabs(xyz[3 * v + a] - xyz[3 * g.adj[e] + a]);
+        nd.reach[a] = std::max(nd.reach[a], std::isnan(d) ? HUGE_VAL : d);
+      }
   nd.sym = &sym;
   // connected components are dissected separately and become sibling roots
   std::vector<int> comp(N, -1);
@@ -201,7 +222,7 @@ void analyze(const double *xyz, const MeshGraph &g, int leaf_max, Symbolic &sym)
     ND::Sorted by;
     for (int a = 0; a < 3; ++a) {
       key.clear();
-      for (int v : c) key.emplace_back(xyz[3 * v + a], v);
+      for (int v : c) key.emplace_back(std::isnan(xyz[3 * v + a]) ? HUGE_VAL : xyz[3 * v + a], v);
       std::sort(key.begin(), key.end());
       by[a].reserve(c.size());
       for (const auto &k : key) by[a].push_back(k.second);

@@ -78,6 +78,25 @@ def test_supernodal_structure_contains_true_fill(cfg):
         assert fill[j] <= allowed, (j, s)
 
 
+@pytest.mark.parametrize("values", [[np.nan], [np.inf], [-np.inf, np.inf], [np.nan, np.inf, -np.inf]], ids=str)
+@pytest.mark.parametrize("share", [0.002, 0.2, 1.0])
+def test_coordinates_that_are_not_finite_give_a_valid_structure(values, share):
+    """The coordinates only choose the order of elimination: any values give a permutation whose supernodes hold the
+    true fill."""
+    sc = make_scene("medium", 0)
+    rng = np.random.default_rng(7)
+    nodes = sc["nodes"].copy()
+    hit = rng.uniform(size=nodes.shape) < share
+    nodes[hit] = rng.choice(values, size=int(hit.sum()))
+    a = icr.analyze(nodes, sc["tets"])
+    perm, sup, rp, rows = a["perm"], a["sup"], a["rows_ptr"], a["rows"]
+    assert np.array_equal(np.sort(perm), np.arange(len(nodes)))
+    owner = np.repeat(np.arange(len(sup)), sup[:, 1])
+    for j, fill in enumerate(_true_fill(perm, nodes, sc["tets"])):
+        s = owner[j]
+        assert fill <= set(range(j + 1, sup[s, 0] + sup[s, 1])) | set(rows[rp[s]:rp[s + 1]].tolist()), (j, s)
+
+
 def test_analyze_rejects_bad_ids():
     L = icr.lib()
     nodes = np.zeros((4, 3))
