@@ -75,13 +75,52 @@ __global__ void k_front_add_A(const AScatter *__restrict__ list, int count, cons
     for (int j = 0; j < 3; ++j) F[(long)(3 * a.lr + i) + (long)(3 * a.lc + j) * f] += Ab[9L * a.blk + 3 * i + j];
 }
 
-// acc -= (lane LANE of this lane's row of 16 of src) * b.  The wait states
-// that a DPP operand written by the previous instructions needs are the
-// caller's.
-template <int LANE>
-__device__ __forceinline__ void fmac_bcast_neg(double &acc, double src, double b) {
-  asm("v_fmac_f64_dpp %0, %1, -%2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(acc) : "v"(src), "v"(b), "n"(LANE));
+// The two wait states between the write of a DPP operand and its use are in the
+// statement of the use: the compiler does not know that it has to keep them and
+// may put a copy of the operand right before the statement.  One wait covers
+// the statement's up to four multiply-adds.
+#define ICR_FMAC_BCAST(D, S, B, L) "v_fmac_f64_dpp " D ", " S ", -" B " row_newbcast:" L " row_mask:0xf bank_mask:0xf\n\t"
+// a[J + i] -= (lane J + i of this lane's row of 16 of b) * b, 0 <= i < N
+template <int J, int N>
+__device__ __forceinline__ void fmac_bcast_column(double *a, double b) {
+  if constexpr (N == 4)
+    asm("s_nop 1\n\t" ICR_FMAC_BCAST("%0", "%4", "%4", "%5") ICR_FMAC_BCAST("%1", "%4", "%4", "%6")
+            ICR_FMAC_BCAST("%2", "%4", "%4", "%7") ICR_FMAC_BCAST("%3", "%4", "%4", "%8")
+        : "+&v"(a[J]), "+&v"(a[J + 1]), "+&v"(a[J + 2]), "+&v"(a[J + 3])
+        : "v"(b), "n"(J), "n"(J + 1), "n"(J + 2), "n"(J + 3));
+  else if constexpr (N == 3)
+    asm("s_nop 1\n\t" ICR_FMAC_BCAST("%0", "%3", "%3", "%4") ICR_FMAC_BCAST("%1", "%3", "%3", "%5")
+            ICR_FMAC_BCAST("%2", "%3", "%3", "%6")
+        : "+&v"(a[J]), "+&v"(a[J + 1]), "+&v"(a[J + 2])
+        : "v"(b), "n"(J), "n"(J + 1), "n"(J + 2));
+  else if constexpr (N == 2)
+    asm("s_nop 1\n\t" ICR_FMAC_BCAST("%0", "%2", "%2", "%3") ICR_FMAC_BCAST("%1", "%2", "%2", "%4")
+        : "+&v"(a[J]), "+&v"(a[J + 1])
+        : "v"(b), "n"(J), "n"(J + 1));
+  else if constexpr (N == 1)
+    asm("s_nop 1\n\t" ICR_FMAC_BCAST("%0", "%1", "%1", "%2") : "+&v"(a[J]) : "v"(b), "n"(J));
 }
+// s -= sum over 0 <= i < N, in order, of (lane LANE of this lane's row of 16 of a[i]) * x[i]
+template <int LANE, int N>
+__device__ __forceinline__ void fmac_bcast_row(double &s, const double *a, const double *x) {
+  if constexpr (N == 4)
+    asm("s_nop 1\n\t" ICR_FMAC_BCAST("%0", "%1", "%5", "%9") ICR_FMAC_BCAST("%0", "%2", "%6", "%9")
+            ICR_FMAC_BCAST("%0", "%3", "%7", "%9") ICR_FMAC_BCAST("%0", "%4", "%8", "%9")
+        : "+&v"(s)
+        : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3]), "n"(LANE));
+  else if constexpr (N == 3)
+    asm("s_nop 1\n\t" ICR_FMAC_BCAST("%0", "%1", "%4", "%7") ICR_FMAC_BCAST("%0", "%2", "%5", "%7")
+            ICR_FMAC_BCAST("%0", "%3", "%6", "%7")
+        : "+&v"(s)
+        : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(x[0]), "v"(x[1]), "v"(x[2]), "n"(LANE));
+  else if constexpr (N == 2)
+    asm("s_nop 1\n\t" ICR_FMAC_BCAST("%0", "%1", "%3", "%5") ICR_FMAC_BCAST("%0", "%2", "%4", "%5")
+        : "+&v"(s)
+        : "v"(a[0]), "v"(a[1]), "v"(x[0]), "v"(x[1]), "n"(LANE));
+  else if constexpr (N == 1)
+    asm("s_nop 1\n\t" ICR_FMAC_BCAST("%0", "%1", "%2", "%3") : "+&v"(s) : "v"(a[0]), "v"(x[0]), "n"(LANE));
+}
+#undef ICR_FMAC_BCAST
 template <int I, int N, class F>
 __device__ __forceinline__ void static_for(F &&f) {
   if constexpr (I < N) {
@@ -128,22 +167,19 @@ __device__ __forceinline__ int potrf16(double *D, double *X) {
     r[c] = rsqrt2(d);
     const double lc = l > c ? a[c] * r[c] : l == c ? d * r[c] : 0.0;
     a[c] = lc;
-    double w = lc;
-    asm("s_nop 1" : "+v"(w));   // a value just written as DPP operand: two wait states
-    static_for<c + 1, 16>([&](auto jj) {
-      constexpr int j = decltype(jj)::value;
-      fmac_bcast_neg<j>(a[j], w, lc);
+    static_for<0, (15 - c + 3) / 4>([&](auto gg) {
+      constexpr int j = c + 1 + 4 * decltype(gg)::value;
+      fmac_bcast_column<j, j + 4 <= 16 ? 4 : 16 - j>(a, lc);
     });
   });
   // column l of the inverse: x_i = (delta_il - sum_{q<i} L(i, q) x_q) / L(i, i)
   double x[16];
-  asm("s_nop 1" : "+v"(a[15]), "+v"(a[14]));
   static_for<0, 16>([&](auto ii) {
     constexpr int i = decltype(ii)::value;
     double s = l == i ? 1.0 : 0.0;
-    static_for<0, i>([&](auto qq) {
-      constexpr int q = decltype(qq)::value;
-      fmac_bcast_neg<i>(s, a[q], x[q]);
+    static_for<0, (i + 3) / 4>([&](auto gg) {
+      constexpr int q = 4 * decltype(gg)::value;
+      fmac_bcast_row<i, q + 4 <= i ? 4 : i - q>(s, a + q, x + q);
     });
     x[i] = s * r[i];
   });

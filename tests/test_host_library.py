@@ -194,3 +194,18 @@ def test_idle_memory_is_freed_when_its_time_is_up(runtime_check):
     """Without another call of the library, by a thread that ends with the last idle block and never frees while the
     process ends."""
     _scenario(runtime_check, "idle_time")
+
+
+def test_broadcast_operands_of_the_factor_wait_in_their_own_statement(tmp_path):
+    """A DPP operand needs two wait states after its write, and inside asm the compiler keeps none: every asm statement
+    with such an operand starts with the wait, in the code as built."""
+    from paper_2306_06946_amd import build
+    out = str(tmp_path / "k_factor.s")
+    r = subprocess.run([build.hipcc()] + build.HIP_FLAGS + build.COMMON +
+                       ["--cuda-device-only", "-S", os.path.join(build.CSRC, "k_factor.hip"), "-o", out],
+                       capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    blocks = re.findall(r";;#ASMSTART\n(.*?);;#ASMEND", open(out).read(), flags=re.S)
+    blocks = [[line.strip() for line in b.strip().splitlines()] for b in blocks if "_dpp" in b]
+    assert sum(sum("_dpp" in line for line in b) for b in blocks) == 240
+    assert all(b[0] == "s_nop 1" for b in blocks)
