@@ -181,3 +181,44 @@ def test_idle_memory_goes_when_its_time_is_up_also_beside_a_capture():
         graph.replay()
         torch.cuda.synchronize()
         assert float(y[0]) == 2.0 * k
+
+
+STEPS = {   # scene, options of its steps
+    "fast": ("medium", dict(graph=False)),
+    "graph": ("medium", dict()),
+    "standard": ("tiny", dict(standard=True)),
+    "per constraint": ("tiny", dict(per_constraint=True)),
+    "mixed": ("medium", "mixed"),
+    "pairs": ("stacked_small", dict()),
+}
+
+
+@pytest.mark.parametrize("kind", STEPS)
+def test_steps_on_used_memory(kind):
+    """A time step gives the same bits on memory that other scenes' steps left as on fresh memory."""
+    from paper_2306_06946_amd import icr
+    cfg, opts = STEPS[kind]
+    opts = dict(precision=icr.FP32_IR) if opts == "mixed" else opts
+
+    def run(cfg, opts, poison=False):
+        sc = make_scene(cfg)
+        s = icr.scene_from_dict(sc)
+        for _ in range(2):
+            s.step(sc["obstacle"], sc["n_contacts"], 3, 20, 0.0, 8, report=False, **opts)
+        q, v, _ = s.get_state()
+        r = s.step_results(sc["n_contacts"], with_WH=True)
+        out = [x.cpu() for x in (q, v, *r.values())]
+        if poison:
+            s.set_state(torch.full_like(q, float("nan")), torch.full_like(v, float("nan")), 0.0)
+        s.close()
+        return out
+
+    print(f"[gpu] used memory {kind}", flush=True)
+    icr.release_idle()
+    want = run(cfg, opts)
+    icr.release_idle()
+    for other in STEPS:   # every kind's buffers, some of them of this scene's sizes
+        c, o = STEPS[other]
+        run(c, dict(precision=icr.FP32_IR) if o == "mixed" else o, poison=True)
+    for a, b in zip(run(cfg, opts), want):
+        assert torch.equal(a, b)

@@ -222,3 +222,36 @@ def test_serving_scene_matches_oracle(seed):
         assert _rel(res["lam"].cpu().numpy(), rec[-1]["lam"]) <= 1e-10
         assert _rel(q.cpu().numpy() - sim.q_rest, out["q"] - sim.q_rest) <= 1e-10
         assert _rel(v.cpu().numpy(), out["v"]) <= 1e-10
+
+
+def test_one_group_with_mixed_options_equals_alone():
+    """The scenes of a group differ in Newton iterations, sweep limits and tolerances: each step is the one it takes
+    alone, bit for bit."""
+    icr = _icr()
+    scs = [make_scene("serving", sd) for sd in SEEDS]
+    opts = [(1, 5, 1e-3), (6, 40, 0.0), (3, 2, 1e-12)]
+    for turn in range(3):
+        opts = opts[1:] + opts[:1]
+        alone = []
+        for sc, o in zip(scs, opts):
+            s = icr.scene_from_dict(sc)
+            for _ in range(2):
+                s.step(sc["obstacle"], sc["n_contacts"], *o, sc["j_inner"], report=False)
+            alone.append([x.cpu() for x in (*s.get_state()[:2], s.step_results(sc["n_contacts"])["lam"])])
+        _say(f"[gpu] serving one group, options {opts}")
+        srv = icr.Server(hbm_budget=64 << 30, slots=1, batching=8)
+        scenes = [icr.scene_from_dict(sc) for sc in scs]
+        ids = [srv.admit(s) for s in scenes]
+        for _ in range(2):
+            for sid, sc, o in zip(ids, scs, opts):
+                srv.submit(sid, sc["obstacle"], sc["n_contacts"], *o, sc["j_inner"])
+        done = []
+        while len(done) < 6:
+            done += srv.poll(wait=True)[0]
+        assert all(c["status"] in (icr.OK, icr.WARN_NOT_CONVERGED) for c in done)
+        torch.cuda.synchronize()
+        for s, sc, ref in zip(scenes, scs, alone):
+            s.set_stream(torch.cuda.current_stream().cuda_stream)
+            got = [x.cpu() for x in (*s.get_state()[:2], s.step_results(sc["n_contacts"])["lam"])]
+            assert all(torch.equal(a, b) for a, b in zip(got, ref))
+        srv.close()
