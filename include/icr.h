@@ -356,7 +356,8 @@ icr_status icr_analyze(const double *nodes, int32_t N, const int32_t *tets, int3
  * (fast scheme, ICR_FP64, no pair contacts, at most 512 contacts, untimed)
  * run their steps up to the Newton loop, then all their Newton loops
  * (Algorithm 3, steps 1-4) together, one launch per step of an iteration for
- * the whole group, then the rest of their steps; other requests run icr_step(scene,
+ * the whole group (and one for all iterations that only scenes of few contacts
+ * have), then the rest of their steps; other requests run icr_step(scene,
  * obstacle, opts, NULL) whole.  The slot is free again when its whole group
  * completed.  Requests of one scene run in submission order; those of
  * different scenes overlap on the device.  Either way a request's results

@@ -1432,14 +1432,15 @@ icr_status newton_batch(void *stream, const void *tasks, const void *host, const
     if (!tasks || !host || !idx || n < 1 || n > kNewtonBatchMax) throw ArgError("newton_batch: 1..64 tasks");
     NewtonBatchIdx b{};
     b.n = n;
-    int max_nc = 1, max_newton = 0;
+    int max_nc = 1, max_newton = 0, wide = 0;   // wide: iterations of the scenes beyond kNewtonSmall contacts
     for (int i = 0; i < n; ++i) {
       const NewtonTask &t = static_cast<const NewtonTask *>(host)[idx[i]];
       b.idx[i] = idx[i];
       max_nc = std::max(max_nc, t.nc);
       max_newton = std::max(max_newton, t.n_newton);
+      if (t.nc > kNewtonSmall) wide = std::max(wide, t.n_newton);
     }
-    launch_newton_batch((hipStream_t)stream, static_cast<const NewtonTask *>(tasks), b, max_nc, max_newton);
+    launch_newton_batch((hipStream_t)stream, static_cast<const NewtonTask *>(tasks), b, max_nc, wide, max_newton);
     return ICR_OK;
   } catch (const ArgError &e) {
     msg = e.what();

@@ -1922,7 +1922,8 @@ __device__ void wg_sym_gemv_sparse(int nc, const TM *__restrict__ M, const doubl
 // ---- batched Newton loops --------------------------------------------------
 //
 // Algorithm 3's Newton loops (steps 1-4) of a group of scenes, one launch per
-// step for all of them (blockIdx.y: the scene): frames and gaps at the last
+// step for all of them (blockIdx.y: the scene; the iterations that only scenes
+// of few contacts have are one launch, k_batch_small): frames and gaps at the last
 // proximity (the warm start in the new frames), W_k = C_k W_H C_k^T, the PGS
 // start gaps g0 = d + W~ lambda and the set, the active-set PGS (one workgroup
 // per scene), and the world forces f = C^T lambda with the proximity p = p_free
@@ -2000,6 +2001,53 @@ __global__ __launch_bounds__(PGS_NT) void k_batch_pgs(const NewtonTask *__restri
                           t.tol, t.j_inner, (int *)t.sweeps + k, (double *)t.eps + k, (double *)t.Wss,
                           (double *)t.gnSet, (const double *)t.swn, (int *)t.ctl, (const int *)t.Sidx, *(const int *)t.nS,
                           (const double *)t.rec, (const double *)t.gS);
+}
+
+// The iterations from k0 on of scenes of few contacts, in one launch: a
+// workgroup runs its scene's whole loop, one step after the other.
+__global__ __launch_bounds__(PGS_NT) void k_batch_small(const NewtonTask *__restrict__ tasks, NewtonBatchIdx ids,
+                                                        int k0) {
+  extern __shared__ double lds_raw[];
+  PgsLds &L = *reinterpret_cast<PgsLds *>(lds_raw);
+  const NewtonTaskG &tg = newton_task(tasks, ids);
+  struct {
+    int nc, n_newton, max_sweeps, j_inner;
+    double tol, h;
+    const StepCtx *ctx;
+    const double *WH, *pfree, *pstart, *mu;
+    double *W, *p, *f, *C, *dk, *lam, *eps;
+    double *g, *Wss, *gnSet, *swn;
+    int8_t *status;
+    int *sweeps, *ctl;
+  } t{tg.nc, tg.n_newton, tg.max_sweeps, tg.j_inner, tg.tol, tg.h, (const StepCtx *)tg.ctx,
+      (const double *)tg.WH, (const double *)tg.pfree, (const double *)tg.pstart, (const double *)tg.mu,
+      (double *)tg.W, (double *)tg.p, (double *)tg.f, (double *)tg.C, (double *)tg.dk, (double *)tg.lam,
+      (double *)tg.eps, (double *)tg.g, (double *)tg.Wss, (double *)tg.gnSet, (double *)tg.swn,
+      (int8_t *)tg.status, (int *)tg.sweeps, (int *)tg.ctl};
+  const int nc = t.nc, tid = threadIdx.x;
+  const long m = 3L * nc;
+  const double h2 = t.h * t.h;
+  for (int k = k0; k < t.n_newton; ++k) {
+    for (int c = tid; c < nc; c += PGS_NT)
+      directions_contact(c, t.ctx, k == 0 ? t.pfree : t.p, t.pfree, t.pstart, t.f, t.C, t.dk, t.lam, 0, nullptr);
+    __syncthreads();
+    for (long blk = tid; blk < (long)nc * nc; blk += PGS_NT) update_W_block(nc, t.WH, t.C, t.W, blk);
+    __syncthreads();
+    wg_sym_gemv_sparse<double>(nc, t.W, t.dk, t.lam, t.lam, h2, t.g, L.ulist, &L.nu, L.lamS);
+    for (int c = tid; c < nc; c += PGS_NT) {
+      t.gnSet[c] = t.g[3 * c];
+      t.swn[c] = sqrt(h2 * t.W[(3L * c) * m + 3L * c]);
+    }
+    __syncthreads();
+    // no prepared set: the body builds it
+    pgs_active_body<double>(L, nc, t.W, t.dk, t.g, t.mu, h2, t.lam, t.status, t.max_sweeps, t.tol, t.j_inner,
+                            t.sweeps + k, t.eps + k, t.Wss, t.gnSet, t.swn, t.ctl, nullptr, PGS_WAVE_MAX + 1,
+                            nullptr, nullptr);
+    __syncthreads();
+    for (long e = tid; e < m; e += PGS_NT) t.f[e] = world_force(t.C, t.lam, e / 3, (int)(e % 3));
+    __syncthreads();
+    wg_sym_gemv_sparse<double>(nc, t.WH, t.pfree, t.f, t.lam, h2, t.p, L.ulist, &L.nu, L.lamS);
+  }
 }
 
 // ---- directions updated before every local solve, on the register chain ----
@@ -3231,8 +3279,8 @@ void pgs_prepare() {
                               (int)pgs_pc_lds(PGS_MAX_NC)));
   ICR_HIP(hipFuncSetAttribute((const void *)k_pgs_coop<double>, hipFuncAttributeMaxDynamicSharedMemorySize,
                               (int)sizeof(PgsLds)));
-  ICR_HIP(hipFuncSetAttribute((const void *)k_batch_pgs, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              (int)sizeof(PgsLds)));
+  for (const void *f : {(const void *)k_batch_pgs, (const void *)k_batch_small})
+    ICR_HIP(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(PgsLds)));
   ICR_HIP(hipFuncSetAttribute((const void *)k_pgs_pca, hipFuncAttributeMaxDynamicSharedMemorySize,
                               (int)sizeof(PcaLds)));
   ICR_HIP(hipFuncSetAttribute((const void *)k_pgs_coop<float>, hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -3250,13 +3298,13 @@ void pgs_prepare() {
   done |= bit;
 }
 
-void launch_newton_batch(hipStream_t st, const NewtonTask *tasks, const NewtonBatchIdx &ids, int max_nc,
+void launch_newton_batch(hipStream_t st, const NewtonTask *tasks, const NewtonBatchIdx &ids, int max_nc, int wide,
                          int max_newton) {
   if (ids.n < 1 || ids.n > kNewtonBatchMax) throw std::runtime_error("batched Newton loop: 1..64 scenes");
   pgs_prepare();
   const int nc = max_nc;
   const dim3 one(1, ids.n), rows(cdiv(3L * nc, 64), ids.n);
-  for (int k = 0; k < max_newton; ++k) {
+  for (int k = 0; k < wide; ++k) {
     k_batch_directions<<<dim3(cdiv(nc, 128), ids.n), 128, 0, st>>>(tasks, ids, k);
     ICR_LAUNCH_CHECK();
     k_batch_update_W<<<dim3(cdiv((long)nc * nc, 256), ids.n), 256, 0, st>>>(tasks, ids, k);
@@ -3268,6 +3316,10 @@ void launch_newton_batch(hipStream_t st, const NewtonTask *tasks, const NewtonBa
     k_batch_pgs<<<one, PGS_NT, sizeof(PgsLds), st>>>(tasks, ids, k);
     ICR_LAUNCH_CHECK();
     k_batch_proximity<<<rows, SG_NT, 0, st>>>(tasks, ids, k);
+    ICR_LAUNCH_CHECK();
+  }
+  if (wide < max_newton) {
+    k_batch_small<<<one, PGS_NT, sizeof(PgsLds), st>>>(tasks, ids, wide);
     ICR_LAUNCH_CHECK();
   }
 }

@@ -318,9 +318,18 @@ void launch_update_W(hipStream_t st, int nc, const TW *WH, const double *C, TW *
 constexpr int kPgsMaxContacts = 4096;
 constexpr int kMaxNewton = 256;   // Newton iterations per step (per-iteration sweeps, eps, stamps)
 void pgs_prepare();   // kernel attributes (dynamic LDS), once per device; call outside graph capture
-// The Newton loops of the scenes tasks[ids.idx[0..n)] (device table), one
-// workgroup each, in one launch on stream st.
-void launch_newton_batch(hipStream_t st, const NewtonTask *tasks, const NewtonBatchIdx &ids, int max_nc,
+// The Newton loops of the scenes tasks[ids.idx[0..n)] (device table) on stream
+// st: the first `wide` iterations as launches over all scenes and their
+// contacts, the rest, of scenes of at most kNewtonSmall contacts, in one launch
+// with a workgroup each.  Six launches an iteration take 28 us, which a scene
+// of few contacts with few sweeps does not have work for; with more contacts
+// the one workgroup's pass over W is longer.  A round of one and of eight
+// scenes, 150 iterations of one sweep: 4 contacts 4.5 and 4.8 ms in wide
+// launches, 2.1 and 3.1 in one; 40 contacts 5.0 and 6.8, 3.9 and 5.8; 64
+// contacts 5.2 and 6.6, 5.3 and 7.1; 128 contacts 5.6 and 8.5, 12.9 and 15.6.
+// With 30 sweeps an iteration the two differ by 3 % up to 64 contacts.
+constexpr int kNewtonSmall = 48;
+void launch_newton_batch(hipStream_t st, const NewtonTask *tasks, const NewtonBatchIdx &ids, int max_nc, int wide,
                          int max_newton);
 int coop_grid();      // workgroups of the cooperative large-set PGS on this device (0: not available)
 void launch_pgs_per_constraint(hipStream_t st, int nc, const StepCtx *ctx, const double *WH, const double *pfree,

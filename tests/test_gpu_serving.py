@@ -255,3 +255,34 @@ def test_one_group_with_mixed_options_equals_alone():
             got = [x.cpu() for x in (*s.get_state()[:2], s.step_results(sc["n_contacts"])["lam"])]
             assert all(torch.equal(a, b) for a, b in zip(got, ref))
         srv.close()
+
+
+@pytest.mark.parametrize("counts", [(4, 16, 48), (48, 49, 4), (1, 40, 120)], ids=str)
+@pytest.mark.parametrize("newton", [(12, 3, 1), (2, 6, 9)], ids=str)
+def test_groups_of_few_contacts_equal_alone(counts, newton):
+    """Scenes of few contacts run the iterations that no larger scene of the group has in a launch of their own: the
+    steps are those they take alone, bit for bit."""
+    icr = _icr()
+    scs = [make_scene("serving", sd) for sd in SEEDS]
+    alone = []
+    for sc, nc, nn in zip(scs, counts, newton):
+        s = icr.scene_from_dict(sc)
+        for _ in range(2):
+            s.step(sc["obstacle"], nc, nn, 4, 0.0, sc["j_inner"], report=False)
+        alone.append([x.cpu() for x in (*s.get_state()[:2], *s.step_results(nc).values())])
+    _say(f"[gpu] serving contacts {counts} iterations {newton}")
+    srv = icr.Server(hbm_budget=64 << 30, slots=1, batching=8)
+    scenes = [icr.scene_from_dict(sc) for sc in scs]
+    ids = [srv.admit(s) for s in scenes]
+    for _ in range(2):
+        for sid, sc, nc, nn in zip(ids, scs, counts, newton):
+            srv.submit(sid, sc["obstacle"], nc, nn, 4, 0.0, sc["j_inner"])
+    done = 0
+    while done < 6:
+        done += len(srv.poll(wait=True)[0])
+    torch.cuda.synchronize()
+    for s, nc, ref in zip(scenes, counts, alone):
+        s.set_stream(torch.cuda.current_stream().cuda_stream)
+        got = [x.cpu() for x in (*s.get_state()[:2], *s.step_results(nc).values())]
+        assert all(torch.equal(a, b) for a, b in zip(got, ref))
+    srv.close()
