@@ -462,8 +462,7 @@ __device__ __forceinline__ PgsRec make_record(const double w[3][3], double mu) {
 // Guarded slip pass (rare: the record's den > 0 guarantee fails, |v| = 0
 // occurred, or the unnormalised iterate left the safe range): den <= 0
 // replaced by w_nn as in the direct form, |v| = 0 keeps the direction;
-// restarts from the initial direction and normalises every pass.  Out of
-// line, so the chains' straight-line code keeps its registers.
+// restarts from the initial direction and normalises every pass.
 struct SlipIn {
   double wh0, wh1, a2, b2, m11, m12;    // record entries
   double d0, d1, d2, lt1, lt2, nt2;     // gap, stick trial
@@ -1087,7 +1086,7 @@ constexpr int PGS_S3 = 3 * PGS_SMAX;
 constexpr int PGS_NT = 512;   // threads of the active-set kernel
 constexpr int PGS_NW = PGS_NT / 64;
 constexpr int PGS_WAVE_MAX = kPgsWaveMax;   // largest set swept by the register chains (= PGS_SMAX)
-constexpr int PGS_BLK = kPgsBlk;            // doubles per 3x3 block of the blocked W~_SS (9 used, 16-byte aligned)
+constexpr int PGS_BLK = kPgsBlk;            // doubles per 3x3 block of the blocked W~_SS
 struct PgsLds {
   // gaps without the own term, current forces (written by the running sweep),
   // forces at the sweep's start and at the set's
@@ -1509,8 +1508,8 @@ __global__ __launch_bounds__(256) void k_pgs_gather(int nc, const TW *__restrict
 // The sequential kernel's body, for one workgroup of PGS_NT threads with the
 // state L in its LDS (k_pgs_active, and each scene's workgroup of the batched
 // Newton loops).  npre: size of the set prepared by pgs_gather (preSidx,
-// preRec, preGS); a value above PGS_WAVE_MAX is not prepared (the set is too
-// large for the chains, and handed over).
+// preRec, preGS); a value above PGS_WAVE_MAX builds the first set here, from
+// g0, gnSet and swn (a set too large for the chains is handed over).
 template <class TW>
 __device__ __forceinline__ void pgs_active_body(PgsLds &L, int nc, const TW *__restrict__ W,
                                                 const double *__restrict__ d, const double *__restrict__ g0,
@@ -3213,9 +3212,12 @@ void launch_pgs(hipStream_t st, int nc, const TW *W, const double *d, const doub
   // its buffers) the single-workgroup sweep
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   ICR_HIP(hipStreamIsCapturing(st, &cap));
-  // one pushing workgroup to two chunks of gap rows at most: they poll and are
-  // polled at device level, and 127 of them slowed the lead's chain (1500
-  // contacts, 12 blocks: 81 us a block, 62 with 36)
+  // One pushing workgroup to two chunks of gap rows at most: they poll and are
+  // polled at device level, and more of them slow the lead's chain, while fewer
+  // fall behind it.  Ten sweeps with every contact pressed and one, two, four
+  // and eight chunks to a workgroup: 600 contacts 2.77, 2.79, 3.18, 3.88 ms;
+  // 1000 4.75, 4.79, 5.39, 6.60; 1500 7.6, 7.5, 8.2, 10.5; 2200 12.1, 11.5,
+  // 12.4, 15.7; 3000 19.5, 16.5, 17.4, 21.6.
   const int G = std::min(coop_grid(), 1 + cdiv(3L * nc, 128));
   if (nc > PGS_WAVE_MAX && wk.Wblk != nullptr && G > 1 && cap == hipStreamCaptureStatusNone) {
     CoopArgs a{nc, W, d, mu, h * h, lam, status, max_sweeps, tol, j_inner, sweeps_dev, eps_dev, wk.ctl, wk.g,

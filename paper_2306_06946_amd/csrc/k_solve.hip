@@ -496,9 +496,14 @@ __global__ void k_fill(long n, double v, double *__restrict__ x) {
 // 10.0 ms; of 1000 at 61 236 it costs what it saves (2.04 -> 2.03 to 2.07 ms).
 //
 // Tile order: few tiles go by their distance from the diagonal, the longest
-// paths first (1000 contacts: 2.17 ms in bands); WP_BAND or more go in bands
-// that share panels (3000 contacts: 10.7 ms by distance).  Below WP_SMALL tiles
-// of 64 the tiles are 32 x 32: at 1128 tiles those cost 3 %.
+// paths first, WP_BAND or more in bands that share panels.  The two meet at
+// about 2300 tiles where the paths are long (28 x 27 x 27 nodes, by distance and
+// in bands: 1653 tiles 2.52 and 2.61 ms, 3655 tiles 4.36 and 4.10, 5886 tiles
+// 6.24 and 5.66, 10 011 tiles 9.69 and 8.40) and at about 4096 where they are
+// short (60 x 60 x 3 nodes: 2556 tiles 0.87 and 0.92, 4095 tiles 1.17 and 1.17,
+// 5886 tiles 1.59 and 1.49; 12 x 12 x 80 nodes alike): the line is the one that
+// costs neither.  Below WP_SMALL tiles of 64 the tiles are 32 x 32: at 1128
+// tiles those cost 3 %.
 constexpr int WP_SMALL = 512, WP_BAND = 4096;
 struct WpSeg {
   long z;             // Z_s
@@ -1150,7 +1155,6 @@ void rhs_prepare(icr_scene *s, int nc, const int *node_ids, bool validate) {
   auto &F = s->fac;
   hipStream_t st = s->stream;
   const int nsup = (int)F.sup.size();
-  const long long m = 3LL * nc;
   s->last_build_nc = nc;
   if (validate) ICR_HIP(hipMemsetAsync(F.d_cerr, 0, sizeof(int), st));
   k_sort_contacts<<<cdiv(nc, SORT_C), 1024, 0, st>>>(nc, s->mesh.N, nsup, node_ids, F.d_sup_of_node, s->mesh.d_fixed,
@@ -1162,8 +1166,7 @@ void rhs_prepare(icr_scene *s, int nc, const int *node_ids, bool validate) {
   ICR_LAUNCH_CHECK();
 }
 
-// Launch geometry of a product: its list's capacity (one workgroup per task;
-// the hardware keeps scheduling workgroups of both streams' launches).
+// Launch geometry of a product: its list's capacity, one workgroup per task.
 struct RhsLists {
   const Factor &F;
   unsigned grid(int l, int k) const { return (unsigned)std::max(1, F.rhs_cap[RHS_KINDS * l + k]); }
@@ -1253,7 +1256,6 @@ void ensure_mixed(icr_scene *s) {
 void build_WH_device(icr_scene *s, int nc, const int *node_ids, double *WH, bool validate, const double *frames) {
   auto &F = s->fac;
   hipStream_t st = s->stream;
-  const long long m = 3LL * nc;
   rhs_prepare(s, nc, node_ids, validate);
   RhsLists L{F};
   rhs_init<double>(s, node_ids, frames, nullptr, F.d_X);
@@ -1275,7 +1277,6 @@ void build_WH_device(icr_scene *s, int nc, const int *node_ids, double *WH, bool
 void build_WH_mixed(icr_scene *s, int nc, const int *node_ids, int refine, float *WH32, double *WH64) {
   auto &F = s->fac;
   hipStream_t st = s->stream;
-  const long long m = 3LL * nc;
   rhs_prepare(s, nc, node_ids, false);
   RhsLists L{F};
   forward_fp32(s, node_ids, nullptr, 1);   // Z32 and its FP64 copy Z

@@ -139,7 +139,7 @@ struct PgsWork {
   double *g = nullptr, *Wss = nullptr;
   double *gnSet = nullptr, *swn = nullptr;   // per contact: normal gap at the set's start state, sqrt(W~_nn)
   int *Sidx = nullptr, *nS = nullptr;         // first active set (ascending contact ids) and its size
-  double *rec = nullptr, *gS = nullptr;       // its records and gaps (sets of at most 128 contacts)
+  double *rec = nullptr, *gS = nullptr;       // its records and gaps (sets of at most kPgsWaveMax contacts)
   int *ctl = nullptr;                         // 4 control words
   // block Gauss-Seidel of sets beyond the chains (only when n_c > 512; NULL:
   // the single-workgroup sweep continues instead)
