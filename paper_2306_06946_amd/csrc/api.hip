@@ -2,6 +2,7 @@
 // launch sequence of each call on the scene's stream.
 #include <pthread.h>
 #include <signal.h>
+#include <unistd.h>
 
 #include <algorithm>
 #include <chrono>
@@ -111,8 +112,11 @@ Idle &idle() {   // lives as long as the process: the runtime may be gone before
 bool Idle::start_watch() {
   if (watched) return true;
   if (closing) return false;
-  // runs before the runtime's own clean-up, which was registered earlier
+  // runs before the runtime's own clean-up, which was registered earlier (not
+  // in a forked child, which has no such thread)
+  static const pid_t owner = getpid();
   static const bool registered = std::atexit([] {
+                                   if (getpid() != owner) return;
                                    Idle &I = idle();
                                    std::unique_lock<std::mutex> lock(I.mtx);
                                    I.closing = true;

@@ -7,11 +7,14 @@
 #define __HIP_PLATFORM_AMD__ 1
 #include <hip/hip_runtime_api.h>
 
+#include <atomic>
+#include <chrono>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
 #include <map>
 #include <mutex>
+#include <thread>
 
 namespace fake {
 inline std::mutex mtx;
@@ -21,6 +24,7 @@ inline long mallocs = 0, launches = 0;
 inline long fail_in = -1;         // the allocation that fails, counted down; < 0: none
 inline long stale = 0;            // copies and clears outside live memory
 inline long frees = 0;            // of device memory: each waits for the whole device
+inline std::atomic<int> slow_frees{0};   // so many frees take a second
 inline bool ended = false;        // the runtime is gone
 inline long late = 0;             // calls after that
 inline bool is_live(const void *p, size_t n) {
@@ -54,6 +58,7 @@ hipError_t hipMalloc(void **p, size_t n) {
   return hipSuccess;
 }
 hipError_t hipFree(void *p) {
+  if (fake::slow_frees > 0 && fake::slow_frees-- > 0) std::this_thread::sleep_for(std::chrono::seconds(1));
   std::lock_guard<std::mutex> l(fake::mtx);
   if (fake::ended) ++fake::late;
   auto it = fake::live.find((char *)p);

@@ -1,5 +1,8 @@
 // The library's host side against a stand-in for the HIP runtime (no GPU),
 // built and run by tests/test_host_library.py: runtime_check <scenario>.
+#include <sys/wait.h>
+#include <unistd.h>
+
 #include <chrono>
 #include <functional>
 #include <string>
@@ -236,7 +239,18 @@ static void scenario_idle_time() {
   CHECK(held() >= big, "freed before its time");
   std::this_thread::sleep_until(t0 + milliseconds(12000));
   CHECK(held() < big, "%zu of %zu bytes still there", held(), big);
-  std::this_thread::sleep_until(t0 + milliseconds(16500));
+  // a forked child has no such thread, and ends without waiting for it, also
+  // while the parent's is inside a free
+  fake::slow_frees = 1;
+  std::this_thread::sleep_until(t0 + milliseconds(15500));
+  const pid_t child = fork();
+  if (child == 0) {
+    alarm(5);   // ends the child if it waits
+    std::exit(0);
+  }
+  int end = 0;
+  CHECK(child > 0 && waitpid(child, &end, 0) == child && WIFEXITED(end) && WEXITSTATUS(end) == 0, "child ended with %d", end);
+  std::this_thread::sleep_until(t0 + milliseconds(19000));
   icr_factor_info info{};
   CHECK(icr_get_factor_info(live, &info) == ICR_OK, "info");
   CHECK(held() < (size_t)info.device_bytes + (2u << 20), "%zu bytes beside a scene of %lld", held(),
