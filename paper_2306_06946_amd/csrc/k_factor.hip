@@ -216,8 +216,8 @@ __device__ __forceinline__ void acc16(F &&f) {
 // tile 0) the diagonal tile factored and its inverse written into the diagonal
 // tile of L_ss^{-1} (upper part zero).  The diagonal tile goes by 16 x 16
 // blocks in LDS: one wave factors and inverts a diagonal block, the products
-// are MFMAs spread over the four waves.  20 us a tile, the latency of 64
-// dependent pivots.
+// are MFMAs spread over the four waves.  28 us a launch, most of it the latency
+// of 64 dependent pivots.
 __global__ __launch_bounds__(256) void k_panel_tile(const SupDev *__restrict__ sup, const int *__restrict__ level_sup,
                                                     int kp, int k, double *__restrict__ front,
                                                     double *__restrict__ linv, int *__restrict__ err) {
