@@ -74,7 +74,8 @@ void icr_destroy(icr_scene *s);
  * thread; scenes in use are not touched).  An allocation of the library that
  * fails does the same for its device by itself; another allocator of the
  * process that needs the memory within those 10 s calls this first.  The memory
- * is in no scene's device_bytes and not part of a server's budget. */
+ * is in no scene's device_bytes and not part of a server's budget.  Call it
+ * before hipDeviceReset. */
 void icr_release_idle(void);
 
 /* Last error message of this scene ("" if none); valid until the next call. */
